@@ -25,16 +25,32 @@
 //     never runs.
 //   * Per-coordinate sums are reduced per workgroup (DPP + LDS) and published
 //     as epoch-tagged packets (two per workgroup, double-buffered by epoch
-//     parity).  In every workgroup one wave gathers all of them -- four
+//     parity).  In every workgroup one wave gathers all of them -- up to four
 //     workgroups' records per lane, all in flight at once -- reduces them in a
 //     fixed order and takes the same scalar CCD step, which one barrier hands
 //     to the other waves: one memory round trip after the last workgroup
 //     publishes, everyone can move on.  Results are bit-reproducible.
-//   * exp() uses one global shift c (the largest X beta of the previous
-//     coordinate); ratios are shift-invariant and the objective adds c back.
+//   * Data sets of up to 32 tiles run on one XCD: their packets then stay in its
+//     L2 (an all-gather of 32 records takes 0.82 us, against 1.57 us for 20
+//     workgroups across the chip and 2.27 us for 250).
+//   * exp() uses one global shift c (within half a table step of the largest X beta
+//     of the previous coordinate); ratios are shift-invariant and the objective adds c back.
 //     A risk-set sum outside [1e-300, 1e300] stops the fit with a flag.
+//
+// What bounds it: the chain of one coordinate.  At N = 1e5, P = 1000, K = 5000 (49 tiles) a
+// coordinate takes 3.7 us, of which the exchange is about 2; at N = 1e6, P = 50, K = 5e4
+// (250 tiles) 5.65 us, of which the exchange is 2.5 and the passes 2.2 (16 row-waves per SIMD at
+// about 45 instructions a row and 4 cycles each).  A SIMD issues one wave's 64 lanes in 4
+// cycles, so what counts besides is instructions per wave: a lane step of the scans or sums
+// costs the same with one row per thread as with eight, which is why tiles are few waves of
+// several rows, the scans carry no flags (factors formed once per fit), and the LDS reads
+// and dependent chains of a thread's rows are issued side by side.  Before these (512 threads
+// of 1 row on all XCDs, flags in the scans, the table reads one after another, every
+// thread folding the eight wave totals): 4.9 us and 6.7 us; N = 1e4 in 10 strata: 6.6 us, now 3.2.
 #include <math.h>
 
+#include <array>
+#include <map>
 #include <mutex>
 #include <type_traits>
 
@@ -43,19 +59,25 @@
 
 namespace coxmi {
 
-// Per-workgroup partial record (5 doubles + an error flag).
-enum { kPC1 = 0, kPC2 = 1, kPM2 = 2, kPObj = 3, kPEtaMax = 4, kPN = 5 };
-
+// Per-workgroup partial record.
 struct Partial {
-    double v[kPN];
-    uint32_t err;
+    double c1, c2, m2, obj;   // sums of d S1/S0, d (S2/S0 - (S1/S0)^2), d S2/S0; objective part
+    uint32_t top;             // the largest X beta over real rows, as an unsigned key (see exp_rows)
+    uint32_t err;             // a risk-set sum left the normal range
 };
 
 // Stop flags decided after a coordinate.
-enum : uint32_t { kFlagNumeric = 1u, kFlagConverged = 2u, kFlagSweepLimit = 4u };
+enum : uint32_t { kFlagNumeric = 1u, kFlagConverged = 2u, kFlagSweepLimit = 4u, kFlagAbort = 8u };
+
+// What wave 0 hands to the other waves after a coordinate: one 16-byte LDS word.
+struct alignas(16) StepWord {
+    double step;
+    uint32_t top;     // Partial::top over all workgroups
+    uint32_t flags;
+};
 
 // A published record is 4 packet slots:
-//   [0] (sum d S1/S0,              epoch, float(max eta))
+//   [0] (sum d S1/S0,              epoch, top)
 //   [1] (sum d (S2/S0 - (S1/S0)^2), epoch, float(sum d S2/S0), NaN if a risk-set sum left range)
 //   [2] (objective part,            epoch, 0)   -- only when the objective is wanted
 //   [3] (sum d S2/S0,               epoch, 0)   -- only when evaluating (exact value for the caller)
@@ -97,16 +119,71 @@ void carve_sync_scratch(void *base, int grid, CcdLaunch &L)
 // ln2/64 is split in two (the high part has 30 trailing zero bits, so n times
 // it is exact) to form r without cancellation.  tab[j] = 2^(j/64), rounded
 // to nearest, built on the host.  Accuracy about 1 ulp, like the libm exp.
-__device__ __forceinline__ double exp_table(double x, const double *tab)
+//
+// All rows of a thread go through each stage together: the indices and table reads of up to
+// kExpGroup rows are issued before the first polynomial, so the LDS latency and the dependent
+// FMA chains of different rows overlap (with two waves per SIMD there is little else to hide
+// them; one row after another left pass 1 waiting on LDS).
+constexpr int kExpGroup = 8;
+
+//
+// Returns the largest k of the rows: c + kmax ln2/64 is the largest X beta to within half a
+// step of the table, which serves as the next coordinate's shift (any value near the maximum
+// does) at half an integer instruction per row.  Published as kmax + kTopBias, an unsigned key
+// whose identity is 0.
+constexpr int kTopBias = 1 << 20;
+constexpr double kTopStep = 0x1.62e42fefa39efp-7;   // ln2 / 64
+
+template <int IPT>
+__device__ __forceinline__ int exp_rows(double (&out)[IPT], const double (&eta)[IPT], double c, const double *tab)
 {
-    x = fmin(fmax(x, -746.0), 710.0);                 // keeps n an int; results saturate to 0 / inf
-    const double n = rint(x * 0x1.71547652b82fep+6);   // 64 / ln 2
-    double r = fma(-n, 0x1.62e42c0000000p-7, x);       // ln2/64, high part
-    r = fma(-n, 0x1.f7d1cf79abc9ep-30, r);             // ln2/64, low part
-    const double p = r * fma(r, fma(r, fma(r, fma(r, 1.0 / 120.0, 1.0 / 24.0), 1.0 / 6.0), 0.5), 1.0);
-    const int k = (int)n;
-    const double t = tab[k & 63];
-    return ldexp(fma(t, p, t), k >> 6);
+    constexpr int GR = IPT < kExpGroup ? IPT : kExpGroup;
+    int kmax = -kTopBias;
+#pragma unroll
+    for (int g = 0; g < IPT; g += GR) {
+        double r[GR], t[GR];
+        int k[GR];
+#pragma unroll
+        for (int i = 0; i < GR; ++i) {
+            const double x = fmin(fmax(eta[g + i] - c, -746.0), 710.0);   // keeps k an int; results saturate to 0 / inf
+            // n = rint(64 x / ln2): adding 1.5 * 2^52 leaves it in the low word, in two's complement
+            const double m = fma(x, 0x1.71547652b82fep+6, 0x1.8p52);
+            const double n = m - 0x1.8p52;
+            k[i] = (int)(uint32_t)__double_as_longlong(m);
+            t[i] = tab[k[i] & 63];
+            r[i] = fma(-n, 0x1.62e42c0000000p-7, x);                     // ln2/64, high part
+            r[i] = fma(-n, 0x1.f7d1cf79abc9ep-30, r[i]);                 // ln2/64, low part
+        }
+#pragma unroll
+        for (int i = 0; i < GR; ++i) kmax = k[i] > kmax ? k[i] : kmax;
+        __builtin_amdgcn_sched_barrier(0);
+        double p[GR];
+#pragma unroll
+        for (int i = 0; i < GR; ++i) p[i] = fma(r[i], 1.0 / 120.0, 1.0 / 24.0);
+#pragma unroll
+        for (int i = 0; i < GR; ++i) p[i] = fma(r[i], p[i], 1.0 / 6.0);
+#pragma unroll
+        for (int i = 0; i < GR; ++i) p[i] = fma(r[i], p[i], 0.5);
+#pragma unroll
+        for (int i = 0; i < GR; ++i) p[i] = fma(r[i], p[i], 1.0);
+#pragma unroll
+        for (int i = 0; i < GR; ++i) p[i] = r[i] * p[i];
+#pragma unroll
+        for (int i = 0; i < GR; ++i) out[g + i] = ldexp(fma(t[i], p[i], t[i]), k[i] >> 6);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return kmax;
+}
+
+// Order-preserving unsigned key of a float (for the shift before any weight is known), and back.
+__device__ __forceinline__ uint32_t float_key(float f)
+{
+    const uint32_t b = __float_as_uint(f);
+    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float key_float(uint32_t k)
+{
+    return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u));
 }
 
 // 1/a from the hardware estimate refined by two Newton steps (each squares
@@ -213,77 +290,81 @@ struct XCol<IPT, 2> {
 
 __device__ __forceinline__ Partial partial_identity()
 {
-    Partial r;
-    r.v[kPC1] = 0.0; r.v[kPC2] = 0.0; r.v[kPM2] = 0.0; r.v[kPObj] = 0.0;
-    r.v[kPEtaMax] = -INFINITY;
-    r.err = 0u;
-    return r;
+    return Partial{0.0, 0.0, 0.0, 0.0, 0u, 0u};
 }
 
+// OBJ: the objective part takes part too (otherwise it is not touched).
+template <bool OBJ>
 __device__ __forceinline__ void partial_combine(Partial &a, const Partial &b)
 {
-    a.v[kPC1] += b.v[kPC1];
-    a.v[kPC2] += b.v[kPC2];
-    a.v[kPM2] += b.v[kPM2];
-    a.v[kPObj] += b.v[kPObj];
-    a.v[kPEtaMax] = fmax(a.v[kPEtaMax], b.v[kPEtaMax]);
+    a.c1 += b.c1;
+    a.c2 += b.c2;
+    a.m2 += b.m2;
+    if constexpr (OBJ) a.obj += b.obj;
+    a.top = a.top > b.top ? a.top : b.top;
     a.err |= b.err;
 }
 
-template <int CTRL, int ROWS>
-__device__ __forceinline__ Partial dpp_partial(const Partial &x)
+template <int CTRL, int ROWS, bool OBJ>
+__device__ __forceinline__ void dpp_step(Partial &x)
 {
-    Partial r;
-    r.v[kPC1] = dpp_f64<CTRL, ROWS>(x.v[kPC1]);
-    r.v[kPC2] = dpp_f64<CTRL, ROWS>(x.v[kPC2]);
-    r.v[kPM2] = dpp_f64<CTRL, ROWS>(x.v[kPM2]);
-    r.v[kPObj] = dpp_f64<CTRL, ROWS>(x.v[kPObj]);
-    // lanes without a source must see the identity of max
-    r.v[kPEtaMax] = __builtin_amdgcn_update_dpp(-(double)INFINITY, x.v[kPEtaMax], CTRL, ROWS, 0xF, false);
-    r.err = dpp_u32<CTRL, ROWS>(x.err);
-    return r;
+    Partial r = x;
+    r.c1 = dpp_f64<CTRL, ROWS>(x.c1);
+    r.c2 = dpp_f64<CTRL, ROWS>(x.c2);
+    r.m2 = dpp_f64<CTRL, ROWS>(x.m2);
+    if constexpr (OBJ) r.obj = dpp_f64<CTRL, ROWS>(x.obj);
+    r.top = dpp_u32<CTRL, ROWS>(x.top);
+    r.err = 0u;
+    partial_combine<OBJ>(x, r);
 }
 
 // Wave reduction in a fixed lane order; the total ends in lane 63.
-__device__ __forceinline__ Partial wave_reduce_partial(Partial x)
+template <bool OBJ>
+__device__ __forceinline__ void wave_reduce_partial(Partial &x)
 {
-    Partial o;
-    o = dpp_partial<0x111, 0xF>(x); partial_combine(x, o);
-    o = dpp_partial<0x112, 0xF>(x); partial_combine(x, o);
-    o = dpp_partial<0x114, 0xF>(x); partial_combine(x, o);
-    o = dpp_partial<0x118, 0xF>(x); partial_combine(x, o);
-    o = dpp_partial<0x142, 0xA>(x); partial_combine(x, o);
-    o = dpp_partial<0x143, 0xC>(x); partial_combine(x, o);
+    dpp_step<0x111, 0xF, OBJ>(x);
+    dpp_step<0x112, 0xF, OBJ>(x);
+    dpp_step<0x114, 0xF, OBJ>(x);
+    dpp_step<0x118, 0xF, OBJ>(x);
+    dpp_step<0x142, 0xA, OBJ>(x);
+    dpp_step<0x143, 0xC, OBJ>(x);
+    x.err = __builtin_amdgcn_ballot_w64(x.err != 0u) != 0 ? 1u : 0u;
+}
+
+// Workgroup reduction: every wave reduces its own rows, and after one barrier lane k of wave 0
+// takes wave k's total and two or three more lane steps finish, so that the total is in lane NW - 1 of
+// wave 0 -- the only wave that needs it (the others go on to wait for the step).  The wave
+// totals stay in `red` until the barrier after the step.
+template <int NW, bool OBJ>
+__device__ __forceinline__ Partial block_reduce_partial(Partial x, Partial *red)
+{
+    static_assert(NW == 4 || NW == 8, "two or three lane steps");
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    wave_reduce_partial<OBJ>(x);
+    if (lane == kWave - 1) red[w] = x;
+    __syncthreads();
+    if (w == 0) {
+        x = red[lane & (NW - 1)];
+        dpp_step<0x111, 0xF, OBJ>(x);
+        dpp_step<0x112, 0xF, OBJ>(x);
+        if constexpr (NW == 8) dpp_step<0x114, 0xF, OBJ>(x);
+        x.err = (__builtin_amdgcn_ballot_w64(x.err != 0u) & ((1u << NW) - 1u)) != 0 ? 1u : 0u;
+    }
     return x;
 }
 
-// Workgroup reduction; every thread receives the same total.  One barrier.
-template <int NW>
-__device__ __forceinline__ Partial block_reduce_partial(const Partial &x, Partial *red)
-{
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const Partial wr = wave_reduce_partial(x);
-    if (lane == kWave - 1) red[w] = wr;
-    __syncthreads();
-    Partial tot = red[0];
-#pragma unroll
-    for (int k = 1; k < NW; ++k) partial_combine(tot, red[k]);
-    return tot;
-}
-
-// Publish this workgroup's record for `epoch` (thread 0); `extra` adds
-// slots [2] and [3].
+// Publish this workgroup's record for `epoch` (one lane); `extra` adds slots [2] and [3].
+// local: every workgroup of the launch shares one L2 (see ccd_kernel).
 __device__ __forceinline__ void publish_partial(const PacketArray &part, int G, int b, const Partial &x,
-                                                uint32_t epoch, bool extra)
+                                                uint32_t epoch, bool extra, bool local)
 {
     const uint32_t slot = (uint32_t)(kRecPackets * ((epoch & 1u) * (uint32_t)G + (uint32_t)b));
-    const float emax = (float)x.v[kPEtaMax];
-    const float m2 = x.err ? __builtin_nanf("") : (float)fmin(x.v[kPM2], 3.0e38);
-    packet_put(part, slot, x.v[kPC1], epoch, __float_as_uint(emax));
-    packet_put(part, slot + 1, x.v[kPC2], epoch, __float_as_uint(m2));
+    const float m2 = x.err ? __builtin_nanf("") : (float)fmin(x.m2, 3.0e38);
+    packet_put(part, slot, x.c1, epoch, x.top, local);
+    packet_put(part, slot + 1, x.c2, epoch, __float_as_uint(m2), local);
     if (extra) {
-        packet_put(part, slot + 2, x.v[kPObj], epoch, 0u);
-        packet_put(part, slot + 3, x.v[kPM2], epoch, 0u);
+        packet_put(part, slot + 2, x.obj, epoch, 0u, local);
+        packet_put(part, slot + 3, x.m2, epoch, 0u, local);
     }
 }
 
@@ -301,19 +382,14 @@ __device__ __forceinline__ double ccd_step(double beta, double g1, double g2, do
         *pinned = 1;
         return 0.0;
     }
-    double d;
-    if (gamma <= 0.0)
-        d = -g1 / g2;
-    else if (beta > 0.0)
-        d = -(g1 + gamma) / g2;
-    else if (beta < 0.0)
-        d = -(g1 - gamma) / g2;
-    else if (g1 + gamma < 0.0)
-        d = -(g1 + gamma) / g2;
-    else if (g1 - gamma > 0.0)
-        d = -(g1 - gamma) / g2;
-    else
-        d = 0.0;
+    // the numerator of the Newton step (0: no move), then one division
+    double num = g1;
+    if (gamma > 0.0) {
+        const double up = g1 + gamma, down = g1 - gamma;
+        num = beta > 0.0 ? up : (beta < 0.0 ? down : (up < 0.0 ? up : (down > 0.0 ? down : 0.0)));
+    }
+    const double inv = recip(g2), q = num * inv;
+    const double d = -fma(fma(-q, g2, num), inv, q);   // -num / g2, the quotient corrected once
     const double lim = *trust;
     double s = fabs(d) > lim ? lim : fabs(d);
     s = d < 0.0 ? -s : s;
@@ -326,25 +402,23 @@ __device__ __forceinline__ double ccd_step(double beta, double g1, double g2, do
     return s;
 }
 
-// One wave gathers the records of all G <= 256 workgroups for `epoch`: lane L
-// waits for the records of workgroups L, L + 64, L + 128, L + 192 (every packet of
+// One wave gathers the records of all G <= 64 PER workgroups for `epoch`: lane L
+// waits for the records of workgroups L, L + 64, ... (every packet of
 // every pending record in flight at once, re-polled together until all carry the
 // epoch), folds them in that order, and the wave reduces the lane totals in a
 // fixed DPP order -- so every workgroup obtains the same bits regardless of
 // arrival times.  Every lane of the wave receives the total.  Returns false
 // (uniformly) once a wait has timed out or another workgroup aborted.  Packets
 // first .. first + NP - 1 of each record are polled.
-constexpr int kGatherPer = kMaxGroups / kWave;
-
-template <int NP>
+template <int NP, int PER>
 __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uint32_t epoch, SyncCtl *ctl,
-                                             u32x4 (&r)[kGatherPer][NP], int first = 0)
+                                             u32x4 (&r)[PER][NP], int first = 0)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    bool done[kGatherPer];
-    uint32_t slot[kGatherPer];
+    bool done[PER];
+    uint32_t slot[PER];
 #pragma unroll
-    for (int k = 0; k < kGatherPer; ++k) {
+    for (int k = 0; k < PER; ++k) {
         const int q = lane + kWave * k;
         done[k] = q >= G;
         slot[k] = (uint32_t)(kRecPackets * ((epoch & 1u) * (uint32_t)G + (uint32_t)q) + first);
@@ -353,13 +427,13 @@ __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uin
     bool ok = true;
     for (;;) {
 #pragma unroll
-        for (int k = 0; k < kGatherPer; ++k)
+        for (int k = 0; k < PER; ++k)
             if (!done[k])
 #pragma unroll
                 for (int pk = 0; pk < NP; ++pk) r[k][pk] = packet_get(part, slot[k] + pk);
         bool all = true;
 #pragma unroll
-        for (int k = 0; k < kGatherPer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             if (!done[k]) {
                 bool fresh = true;
 #pragma unroll
@@ -377,56 +451,58 @@ __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uin
     return __builtin_amdgcn_ballot_w64(!ok) == 0;
 }
 
-__device__ __forceinline__ Partial broadcast_lane63(const Partial &x)
-{
-    Partial r;
-#pragma unroll
-    for (int k = 0; k < kPN; ++k) r.v[k] = lane63_f64(x.v[k]);
-    r.err = (uint32_t)__builtin_amdgcn_readlane((int)x.err, 63);
-    return r;
-}
-
-__device__ __forceinline__ bool gather_wave(const PacketArray &part, int G, uint32_t epoch, bool extra,
-                                            SyncCtl *ctl, Partial &total)
+template <int PER>
+__device__ __forceinline__ bool gather_records(const PacketArray &part, int G, uint32_t epoch, bool extra,
+                                               SyncCtl *ctl, Partial &total)
 {
     const int lane = threadIdx.x & (kWave - 1);
     Partial x = partial_identity();
     {
-        u32x4 r[kGatherPer][2];
-        if (!poll_records<2>(part, G, epoch, ctl, r)) return false;
+        u32x4 r[PER][2];
+        if (!poll_records<2, PER>(part, G, epoch, ctl, r)) return false;
 #pragma unroll
-        for (int k = 0; k < kGatherPer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             if (lane + kWave * k < G) {
-                Partial y;
-                y.v[kPC1] = packet_value(r[k][0]);
-                y.v[kPEtaMax] = (double)__uint_as_float(r[k][0].w);
-                y.v[kPC2] = packet_value(r[k][1]);
                 const float m2 = __uint_as_float(r[k][1].w);
-                y.err = (m2 == m2) ? 0u : 1u;
-                y.v[kPM2] = (double)m2;
-                y.v[kPObj] = 0.0;
-                partial_combine(x, y);
+                const Partial y = {packet_value(r[k][0]), packet_value(r[k][1]), (double)m2, 0.0,
+                                   r[k][0].w, (m2 == m2) ? 0u : 1u};
+                partial_combine<false>(x, y);
             }
         }
     }
     if (extra) {
         // the objective and the exact second moment (written with the two above): a second,
         // short poll on the first coordinate of a sweep and in evaluations only
-        u32x4 r[kGatherPer][2];
-        if (!poll_records<2>(part, G, epoch, ctl, r, 2)) return false;
+        u32x4 r[PER][2];
+        if (!poll_records<2, PER>(part, G, epoch, ctl, r, 2)) return false;
         double obj = 0.0, m2 = 0.0;
 #pragma unroll
-        for (int k = 0; k < kGatherPer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             if (lane + kWave * k < G) {
                 obj += packet_value(r[k][0]);
                 m2 += packet_value(r[k][1]);
             }
         }
-        x.v[kPObj] = obj;
-        x.v[kPM2] = m2;
+        x.obj = obj;
+        x.m2 = m2;
+        wave_reduce_partial<true>(x);
+    } else {
+        wave_reduce_partial<false>(x);
     }
-    total = broadcast_lane63(wave_reduce_partial(x));
+    total.c1 = lane63_f64(x.c1);
+    total.c2 = lane63_f64(x.c2);
+    total.m2 = lane63_f64(x.m2);
+    total.obj = extra ? lane63_f64(x.obj) : 0.0;
+    total.top = (uint32_t)__builtin_amdgcn_readlane((int)x.top, 63);
+    total.err = x.err;
     return true;
+}
+
+__device__ __forceinline__ bool gather_wave(const PacketArray &part, int G, uint32_t epoch, bool extra, SyncCtl *ctl,
+                                            Partial &total)
+{
+    if (G <= kWave) return gather_records<1>(part, G, epoch, extra, ctl, total);
+    return gather_records<kMaxGroups / kWave>(part, G, epoch, extra, ctl, total);
 }
 
 // Tie-group terms of one row, added to v (Sec. 2.4 derivatives).  S = (S0, S1, S2): the
@@ -435,94 +511,244 @@ __device__ __forceinline__ bool gather_wave(const PacketArray &part, int G, uint
 //   Breslow (the risk sets of Eq. strat_l taken literally): every tied event sees S,
 //     so the group adds d S1/S0, d (S2/S0 - (S1/S0)^2), d S2/S0, d (log S0 + c).  Evaluated
 //     on every row without branches (d = 0 adds zeros; S0 is replaced by 1 there so that
-//     no infinity enters).
+//     no infinity enters), in pass2 below.
 //   Efron (1977): E = (E0, E1, E2), the same sums over the group's own events; the l-th
 //     of its d events sees S - (l/d) E, l = 0..d-1 (d = 1 is Breslow's term exactly).
-template <bool EFRON, bool WANT_OBJ>
-__device__ __forceinline__ void group_terms(Partial &v, uint32_t d, const double (&S)[3], const double (&E)[3],
-                                            double c)
+template <bool WANT_OBJ>
+__device__ __forceinline__ void group_terms_efron(Partial &v, uint32_t d, const double (&S)[3], const double (&E)[3],
+                                                  double c)
 {
     const double s0 = S[0];
-    if constexpr (!EFRON) {
-        const bool end = d != 0u;
-        if (end && (!(s0 >= 1e-300) || !(s0 <= 1e300))) v.err = 1u;
-        const double sg = end ? s0 : 1.0;
-        const double inv = recip(sg);
-        const double r1 = S[1] * inv, r2 = S[2] * inv;
-        const double dd = (double)d;
-        v.v[kPC1] = fma(dd, r1, v.v[kPC1]);
-        v.v[kPC2] = fma(dd, fma(-r1, r1, r2), v.v[kPC2]);
-        v.v[kPM2] = fma(dd, r2, v.v[kPM2]);
-        if constexpr (WANT_OBJ) v.v[kPObj] = fma(dd, log(sg) + c, v.v[kPObj]);
-    } else {
-        if (d == 0u) return;
-        if (!(s0 >= 1e-300) || !(s0 <= 1e300)) v.err = 1u;
-        const double dd = (double)d;
-        for (uint32_t l = 0; l < d; ++l) {
-            const double a = (double)l / dd;
-            const double A = s0 - a * E[0];
-            const double inv = recip(A);
-            const double r1 = (S[1] - a * E[1]) * inv, r2 = (S[2] - a * E[2]) * inv;
-            v.v[kPC1] += r1;
-            v.v[kPC2] += r2 - r1 * r1;
-            v.v[kPM2] += r2;
-            if constexpr (WANT_OBJ) v.v[kPObj] += log(A) + c;
-        }
+    if (d == 0u) return;
+    if (!(s0 >= 1e-300) || !(s0 <= 1e300)) v.err = 1u;
+    const double dd = (double)d;
+    for (uint32_t l = 0; l < d; ++l) {
+        const double a = (double)l / dd;
+        const double A = s0 - a * E[0];
+        const double inv = recip(A);
+        const double r1 = (S[1] - a * E[1]) * inv, r2 = (S[2] - a * E[2]) * inv;
+        v.c1 += r1;
+        v.c2 += fma(-r1, r1, r2);   // one rounding whichever way r2 was formed (r2 = r1 on indicator X)
+        v.m2 += r2;
+        if constexpr (WANT_OBJ) v.obj += log(A) + c;
     }
 }
 
-// Scan element of one row.  Components 0..2: (D, N1, N2) restarting at stratum heads
-// (flag bit 0).  Efron adds components 3..5: the same values on event rows only, restarting
+// Scan element of one row.  Components 0..NC-1: (D, N1, N2) restarting at stratum heads
+// (flag bit 0).  On indicator X (XK = 1) x^2 = x, so N2 is N1 exactly and is left out (NC = 2).
+// Efron adds components NC..2 NC - 1: the same values on event rows only, restarting
 // after every row that ends a tie group with events (flag bit 1; such a row contributes 0
 // itself, so the running value before it plus its own values are its group's event sums).
 // An event-free stretch adds nothing, so these sums need no restart at stratum heads.
-template <bool EFRON>
-using RowVal = SegVal<EFRON ? 6 : 3, 3>;
+template <int XK>
+constexpr int kRowComp = XK == 1 ? 2 : 3;
+template <bool EFRON, int XK>
+using RowVal = SegVal<(EFRON ? 2 : 1) * kRowComp<XK>, kRowComp<XK>>;
 
-template <bool EFRON>
-__device__ __forceinline__ RowVal<EFRON> row_value(uint32_t m, double w, double x)
+template <bool EFRON, int XK>
+__device__ __forceinline__ RowVal<EFRON, XK> row_value(uint32_t m, double w, double x)
 {
-    RowVal<EFRON> r;
+    constexpr int NC = kRowComp<XK>;
+    RowVal<EFRON, XK> r;
     r.f = m >> 31;
     r.v[0] = w;
     r.v[1] = x * w;
-    r.v[2] = x * r.v[1];
+    if constexpr (NC == 3) r.v[2] = x * r.v[1];
     if constexpr (EFRON) {
         const bool end = (m & kCountMask) != 0u, ev = (m & kEventBit) != 0u;
         r.f |= end ? 2u : 0u;
         const bool keep = ev && !end;
-        r.v[3] = keep ? r.v[0] : 0.0;
-        r.v[4] = keep ? r.v[1] : 0.0;
-        r.v[5] = keep ? r.v[2] : 0.0;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) r.v[NC + k] = keep ? r.v[k] : 0.0;
     }
     return r;
 }
 
-// Pass 2 over a thread's rows: the inclusive prefixes from the thread's exclusive prefix
-// `run`, the group-end terms, the largest X beta over real rows, and (WANT_OBJ, the first
-// coordinate of a sweep) the objective's parts.
-template <int IPT, int XK, bool EFRON, bool WANT_OBJ>
-__device__ __forceinline__ Partial pass2(RowVal<EFRON> run, const uint32_t (&meta)[IPT], const double (&wv)[IPT],
-                                         const XCol<IPT, XK> &xc, const double (&eta)[IPT], double c)
+// 1.0 or 0.0 as the factor that keeps or drops what a scan carries in.
+__device__ __forceinline__ double keep_factor(bool keep)
 {
-    Partial v = partial_identity();
+    return __longlong_as_double(keep ? 0x3ff0000000000000ll : 0ll);
+}
+
+// The sums of several rows' values without flags: the flags of every step of the scans are the
+// same for every coordinate, so the factors that keep or drop the carried value are formed once
+// per fit (Breslow; Efron's six components take the general operator of segscan.hpp).
+template <int NC>
+struct Vals {
+    double v[NC];
+};
+
+template <int CTRL, int ROWS, int NC>
+__device__ __forceinline__ Vals<NC> dpp_vals(const Vals<NC> &x)
+{
+    Vals<NC> r;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) r.v[k] = dpp_f64<CTRL, ROWS>(x.v[k]);
+    return r;
+}
+
+template <int NC>
+__device__ __forceinline__ Vals<NC> add_kept(const Vals<NC> &a, double keep, const Vals<NC> &b)
+{
+    Vals<NC> r;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) r.v[k] = fma(a.v[k], keep, b.v[k]);
+    return r;
+}
+
+template <int NC>
+__device__ __forceinline__ Vals<NC> lane_vals(const Vals<NC> &x, int src)
+{
+    Vals<NC> r;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        const long long b = __double_as_longlong(x.v[k]);
+        const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), src);
+        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
+        r.v[k] = __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    }
+    return r;
+}
+
+// Factors of one thread's place in the scans.
+template <int NW>
+struct ScanKeep {
+    double wave[6];      // the six lane steps of the wave scan
+    double tot[3];       // the lane steps over the wave totals (lane k: wave k)
+    double exc, carry;   // what the earlier waves, and the earlier tiles, add to this thread
+    uint32_t tile_flag;  // the tile holds a head
+
+    // f: the thread's rows hold a head.  Called by every thread; two barriers.
+    __device__ __forceinline__ void init(uint32_t f, uint32_t *lds)
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+        wave[0] = keep_factor(f == 0u); f |= dpp_u32<0x111, 0xF>(f);
+        wave[1] = keep_factor(f == 0u); f |= dpp_u32<0x112, 0xF>(f);
+        wave[2] = keep_factor(f == 0u); f |= dpp_u32<0x114, 0xF>(f);
+        wave[3] = keep_factor(f == 0u); f |= dpp_u32<0x118, 0xF>(f);
+        wave[4] = keep_factor(f == 0u); f |= dpp_u32<0x142, 0xA>(f);
+        wave[5] = keep_factor(f == 0u); f |= dpp_u32<0x143, 0xC>(f);
+        const uint32_t before = dpp_u32<0x138, 0xF>(f);   // a head in the wave's rows before this thread's
+        if (lane == kWave - 1) lds[w] = f;
+        __syncthreads();
+        uint32_t g = lds[lane & (NW - 1)];
+        __syncthreads();
+        tot[0] = keep_factor(g == 0u); g |= dpp_u32<0x111, 0xF>(g);
+        tot[1] = keep_factor(g == 0u); g |= dpp_u32<0x112, 0xF>(g);
+        tot[2] = keep_factor(g == 0u);
+        if constexpr (NW == 8) g |= dpp_u32<0x114, 0xF>(g);
+        tile_flag = (uint32_t)__builtin_amdgcn_readlane((int)g, NW - 1);
+        const uint32_t earlier = w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)g, w > 0 ? w - 1 : 0) : 0u;
+        exc = keep_factor(w > 0 && before == 0u);
+        carry = keep_factor((before | earlier) == 0u);
+    }
+
+    template <int NC>
+    __device__ __forceinline__ Vals<NC> wave_scan(Vals<NC> x) const
+    {
+        x = add_kept(dpp_vals<0x111, 0xF>(x), wave[0], x);
+        x = add_kept(dpp_vals<0x112, 0xF>(x), wave[1], x);
+        x = add_kept(dpp_vals<0x114, 0xF>(x), wave[2], x);
+        x = add_kept(dpp_vals<0x118, 0xF>(x), wave[3], x);
+        x = add_kept(dpp_vals<0x142, 0xA>(x), wave[4], x);
+        x = add_kept(dpp_vals<0x143, 0xC>(x), wave[5], x);
+        return x;
+    }
+
+    // The workgroup's exclusive scan; `total` receives the tile's total.  One barrier.
+    template <int NC>
+    __device__ __forceinline__ Vals<NC> block_scan(const Vals<NC> &x, Vals<NC> *lds, Vals<NC> &total) const
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+        const Vals<NC> inc = wave_scan(x);
+        if (lane == kWave - 1) lds[w] = inc;
+        const Vals<NC> before = dpp_vals<0x138, 0xF>(inc);
+        __syncthreads();
+        Vals<NC> t = lds[lane & (NW - 1)];
+        t = add_kept(dpp_vals<0x111, 0xF>(t), tot[0], t);
+        t = add_kept(dpp_vals<0x112, 0xF>(t), tot[1], t);
+        if constexpr (NW == 8) t = add_kept(dpp_vals<0x114, 0xF>(t), tot[2], t);
+        total = lane_vals(t, NW - 1);
+        return add_kept(lane_vals(t, w > 0 ? w - 1 : 0), exc, before);
+    }
+};
+
+// Pass 2 over a thread's rows: the inclusive prefixes at group ends, the group-end terms, and
+// (WANT_OBJ, the first coordinate of a sweep) the objective's parts.
+//
+// Breslow: the terms go through each stage for kTermGroup rows together, so that the
+// reciprocals' dependent steps overlap.  A row that ends no group with events has d = 0; there
+// the high word of S0 is replaced by 1.0's, which keeps the reciprocal finite.  The range test
+// compares high words (S0 in [1e-300, 1e300] up to a relative 1e-6 at either end; a NaN or a
+// negative value is out).
+constexpr int kTermGroup = 4;
+constexpr uint32_t kHiLow = 0x01a56e1fu, kHiHigh = 0x7e37e43cu, kHiOne = 0x3ff00000u;
+
+// S(i, k): component k of the inclusive prefix at row i
+template <int IPT, int NC, bool WANT_OBJ, class Prefix>
+__device__ __forceinline__ void pass2_breslow(Partial &v, const uint32_t (&meta)[IPT], double c, Prefix S)
+{
+    constexpr int GR = IPT < kTermGroup ? IPT : kTermGroup;
+    uint32_t lo = kHiOne, hi = kHiOne;
+#pragma unroll
+    for (int g = 0; g < IPT; g += GR) {
+        double sg[GR], s1[GR], s2[GR], inv[GR];
+#pragma unroll
+        for (int i = 0; i < GR; ++i) {
+            double row[NC];
+            S(g + i, row);
+            const long long b = __double_as_longlong(row[0]);
+            const uint32_t h = (meta[g + i] & kCountMask) ? (uint32_t)(b >> 32) : kHiOne;
+            lo = h < lo ? h : lo;
+            hi = h > hi ? h : hi;
+            sg[i] = __longlong_as_double((long long)(((unsigned long long)h << 32) | (uint32_t)b));
+            s1[i] = row[1];
+            s2[i] = row[NC - 1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < GR; ++i) inv[i] = __builtin_amdgcn_rcp(sg[i]);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            double e[GR];
+#pragma unroll
+            for (int i = 0; i < GR; ++i) e[i] = fma(-sg[i], inv[i], 1.0);
+#pragma unroll
+            for (int i = 0; i < GR; ++i) inv[i] = fma(inv[i], e[i], inv[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < GR; ++i) {
+            const double dd = (double)(meta[g + i] & kCountMask);
+            const double r1 = s1[i] * inv[i], r2 = NC == 2 ? r1 : s2[i] * inv[i];
+            v.c1 = fma(dd, r1, v.c1);
+            v.c2 = fma(dd, fma(-r1, r1, r2), v.c2);
+            v.m2 = fma(dd, r2, v.m2);
+            if constexpr (WANT_OBJ) v.obj = fma(dd, log(sg[i]) + c, v.obj);
+        }
+    }
+    if (lo < kHiLow || hi > kHiHigh) v.err = 1u;
+}
+
+template <int IPT, int XK, bool WANT_OBJ>
+__device__ __forceinline__ void pass2_efron(Partial &v, RowVal<true, XK> run, const uint32_t (&meta)[IPT],
+                                            const double (&wv)[IPT], const XCol<IPT, XK> &xc, double c)
+{
+    constexpr int NC = kRowComp<XK>;
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
-        const RowVal<EFRON> r = row_value<EFRON>(meta[i], wv[i], xc[i]);
-        double E[3] = {0.0, 0.0, 0.0};
-        if constexpr (EFRON) {
-            // this row's group's event sums: the running value before it plus its own share
-            const bool ev = (meta[i] & kEventBit) != 0u;
+        const RowVal<true, XK> r = row_value<true, XK>(meta[i], wv[i], xc[i]);
+        double E[3];
+        // this row's group's event sums: the running value before it plus its own share
+        const bool ev = (meta[i] & kEventBit) != 0u;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) E[k] = run.v[3 + k] + (ev ? r.v[k] : 0.0);
-        }
+        for (int k = 0; k < NC; ++k) E[k] = run.v[NC + k] + (ev ? r.v[k] : 0.0);
+        E[2] = E[NC - 1];
         run = seg_combine(run, r);
-        v.v[kPEtaMax] = (meta[i] & kPadBit) ? v.v[kPEtaMax] : fmax(v.v[kPEtaMax], eta[i]);
-        const double S[3] = {run.v[0], run.v[1], run.v[2]};
-        group_terms<EFRON, WANT_OBJ>(v, meta[i] & kCountMask, S, E, c);
-        if constexpr (WANT_OBJ) v.v[kPObj] -= (meta[i] & kEventBit) ? eta[i] : 0.0;
+        const double S[3] = {run.v[0], run.v[1], run.v[NC - 1]};
+        group_terms_efron<WANT_OBJ>(v, meta[i] & kCountMask, S, E, c);
     }
-    return v;
 }
 
 // ------------------------------------------------------------------ the persistent kernel
@@ -533,20 +759,27 @@ template <int BLOCK, int IPT, int XK, bool EFRON, bool WAVE>
 __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
 {
     constexpr int NW = BLOCK / kWave;
-    constexpr int KV = EFRON ? 6 : 3;
-    using RV = RowVal<EFRON>;
-    static_assert(BLOCK % kWave == 0 && NW <= 16, "block shape");
+    using RV = RowVal<EFRON, XK>;
+    constexpr int NC = kRowComp<XK>, KV = (EFRON ? 2 : 1) * NC;
+    // Breslow with up to 8 rows per thread keeps the rows' prefixes within the thread from pass 1
+    // to pass 2 (one FMA per component adds the carry); 16 rows of them do not fit in registers
+    constexpr bool KEEP = IPT <= 8;
+    static_assert(BLOCK % kWave == 0 && (NW == 4 || NW == 8), "block shape");
     extern __shared__ double smem_dyn[];     // beta (the same in every workgroup)
-    __shared__ RV s_wtot[NW];
+    __shared__ RV s_wtot[EFRON ? NW : 1];
+    __shared__ Vals<NC> s_vtot[NW];
     __shared__ Partial s_red[NW];        // this workgroup's own reduction
+    __shared__ uint32_t s_flag[NW];
     __shared__ RV s_win[kMaxGroups / kWave];
     __shared__ int s_abort;
     __shared__ double s_exptab[64];
-    __shared__ double s_step, s_shift;   // wave 0's step and shift for the next coordinate
-    __shared__ uint32_t s_flags;
+    __shared__ StepWord s_word;          // wave 0's step and shift for the next coordinate
 
+    // One XCD: the launch has `spread` workgroups for each one that works, and workgroups go to
+    // the XCDs in turn, so those that work share an L2.
+    if (L.spread > 1 && blockIdx.x % L.spread != 0) return;
     const int p = L.p;
-    const int G = gridDim.x, b = blockIdx.x, t = threadIdx.x;
+    const int G = gridDim.x / L.spread, b = blockIdx.x / L.spread, t = threadIdx.x;
     const int lane = t & (kWave - 1), w = t / kWave;
     const bool writer = (b == 0 && t == 0);   // writes the outputs
     SyncCtl *ctl = static_cast<SyncCtl *>(L.ctl);
@@ -570,8 +803,20 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
     double eta[IPT];
     load_words<IPT>(meta, L.meta + row0);
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) eta[i] = 0.0;
+    for (int i = 0; i < IPT; ++i) eta[i] = (meta[i] & kPadBit) ? -INFINITY : 0.0;   // padding: weight 0, never the maximum
     const bool tile_head = (L.meta[tile0] & kHeadBit) != 0u;
+    ScanKeep<NW> keep;
+    double krow[IPT], kall[IPT];   // a row keeps the row before it; its prefix keeps what enters the thread
+    {
+        uint32_t f = 0u;
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            f |= meta[i] >> 31;
+            krow[i] = keep_factor(!(meta[i] & kHeadBit));
+            kall[i] = keep_factor(f == 0u);
+        }
+        if constexpr (!EFRON) keep.init(f, s_flag);
+    }
 
     // X beta0 (columns with beta0_j = 0 are skipped)
     for (int j = 0; j < p; ++j) {
@@ -585,27 +830,39 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
     }
     __syncthreads();
 
-    // epoch 1: the initial shift, the largest X beta over the real rows
+    // epoch 1: the initial shift, the largest X beta over the real rows, and with `spread` the
+    // XCDs the working workgroups run on (c1, c2: sums of the id and of its square, so that
+    // G c2 = c1^2 exactly when all are equal).  Packets of one XCD can stay in its L2; if the
+    // workgroups turn out to be spread after all, they go through to device memory as always.
     uint32_t epoch = 1;
     double c;
+    bool local = false;
     {
         Partial v = partial_identity();
 #pragma unroll
         for (int i = 0; i < IPT; ++i)
-            if (!(meta[i] & kPadBit)) v.v[kPEtaMax] = fmax(v.v[kPEtaMax], eta[i]);
-        v = block_reduce_partial<NW>(v, s_red);
-        if (t == 0) publish_partial(part, G, b, v, epoch, false);
+            if (!(meta[i] & kPadBit)) {
+                const uint32_t key = float_key((float)eta[i]);
+                v.top = key > v.top ? key : v.top;
+            }
+        v = block_reduce_partial<NW, false>(v, s_red);
         if (w == 0) {
+            const double xcc = (double)xcc_id();
+            v.c1 = xcc;
+            v.c2 = xcc * xcc;
+            if (lane == NW - 1) publish_partial(part, G, b, v, epoch, false, false);
             Partial tot;
-            if (gather_wave(part, G, epoch, false, ctl, tot)) {
-                if (lane == 0) s_shift = tot.v[kPEtaMax];
-            } else if (lane == 0) {
-                s_abort = 1;
+            const bool ok = gather_wave(part, G, epoch, false, ctl, tot);
+            if (lane == 0) {
+                const bool one = ok && (G == 1 || (L.spread > 1 && (double)G * tot.c2 == tot.c1 * tot.c1));
+                s_word = StepWord{one ? 1.0 : 0.0, ok ? tot.top : 0u, ok ? 0u : (uint32_t)kFlagAbort};
             }
         }
         __syncthreads();
-        if (s_abort) return;
-        c = s_shift;
+        const StepWord word = s_word;
+        if (word.flags & kFlagAbort) return;
+        c = (double)key_float(word.top);
+        local = word.step != 0.0;
     }
 
     const int jfirst = fit ? 0 : L.j0;
@@ -632,55 +889,97 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
             const double qj = L.q[j], gj = L.gamma[j];
             double trj = trust[j];
 
-            // pass 1: D, N1, N2 of the thread's rows and their fold
-            RV tagg = seg_identity<KV, 3>();
-            double wv[IPT];
-#pragma unroll
-            for (int i = 0; i < IPT; ++i) {
-                wv[i] = exp_table(eta[i] - c, s_exptab);
-                tagg = seg_combine(tagg, row_value<EFRON>(meta[i], wv[i], xc[i]));
-            }
-            RV exc;
-            if constexpr (WAVE) {
-                exc = wave_shift_right(wave_inclusive_scan(tagg));
-            } else {
-                RV btot;
-                exc = block_exclusive_scan<KV, NW, 3>(tagg, s_wtot, btot);
-                if (t == 0) publish_aggregate(agg, b, btot, epoch);
-                if (!tile_head) {
-                    RV carry;
-                    if (!look_back<KV, 3>(b, epoch, agg, ctl, s_win, &s_abort, carry)) return;
-                    exc = seg_combine(carry, exc);
-                }
-            }
-
+            // pass 1: D, N1, N2 of the thread's rows and their fold; the scans to what enters the thread;
             // pass 2: inclusive prefixes at group ends -> per-coordinate sums
-            Partial v = want_obj ? pass2<IPT, XK, EFRON, true>(exc, meta, wv, xc, eta, c)
-                                 : pass2<IPT, XK, EFRON, false>(exc, meta, wv, xc, eta, c);
-            v = block_reduce_partial<NW>(v, s_red);
+            double wv[IPT];
             const bool extra = want_obj || !fit;
-            if (t == 0) publish_partial(part, G, b, v, epoch, extra);
-
-            // wave 0 gathers every workgroup's record and takes the step; the others wait for it
-            if (w == 0) {
-                Partial tot;
-                if (!gather_wave(part, G, epoch, extra, ctl, tot)) {
-                    if (lane == 0) s_abort = 1;
+            Partial v = partial_identity();
+            v.top = (uint32_t)(exp_rows<IPT>(wv, eta, c, s_exptab) + kTopBias);
+            if constexpr (EFRON) {
+                RV tagg = seg_identity<KV, NC>();
+#pragma unroll
+                for (int i = 0; i < IPT; ++i) tagg = seg_combine(tagg, row_value<EFRON, XK>(meta[i], wv[i], xc[i]));
+                RV exc;
+                if constexpr (WAVE) {
+                    exc = wave_shift_right(wave_inclusive_scan(tagg));
                 } else {
+                    RV btot;
+                    exc = block_exclusive_scan<KV, NW, NC>(tagg, s_wtot, btot);
+                    if (t == 0) publish_aggregate(agg, b, btot, epoch, local);
+                    if (!tile_head) {
+                        RV carry;
+                        if (!look_back<KV, NC>(b, epoch, agg, ctl, s_win, &s_abort, carry)) return;
+                        exc = seg_combine(carry, exc);
+                    }
+                }
+                if (want_obj) pass2_efron<IPT, XK, true>(v, exc, meta, wv, xc, c);
+                else pass2_efron<IPT, XK, false>(v, exc, meta, wv, xc, c);
+            } else {
+                Vals<NC> loc[KEEP ? IPT : 1], tagg;
+                auto row = [&](int i) {
+                    Vals<NC> r;
+                    r.v[0] = wv[i];
+                    r.v[1] = xc[i] * wv[i];
+                    if constexpr (NC == 3) r.v[2] = xc[i] * r.v[1];
+                    return r;
+                };
+#pragma unroll
+                for (int i = 0; i < IPT; ++i) {
+                    tagg = i == 0 ? row(0) : add_kept(tagg, krow[i], row(i));
+                    if constexpr (KEEP) loc[i] = tagg;
+                }
+                Vals<NC> exc;
+                if constexpr (WAVE) {
+                    exc = dpp_vals<0x138, 0xF>(keep.template wave_scan<NC>(tagg));
+                } else {
+                    Vals<NC> btot;
+                    exc = keep.template block_scan<NC>(tagg, s_vtot, btot);
+                    if (t == 0) {
+                        RV a;
+                        a.f = keep.tile_flag;
+#pragma unroll
+                        for (int k = 0; k < NC; ++k) a.v[k] = btot.v[k];
+                        publish_aggregate(agg, b, a, epoch, local);
+                    }
+                    if (!tile_head) {
+                        RV carry;
+                        if (!look_back<KV, NC>(b, epoch, agg, ctl, s_win, &s_abort, carry)) return;
+#pragma unroll
+                        for (int k = 0; k < NC; ++k) exc.v[k] = fma(carry.v[k], keep.carry, exc.v[k]);
+                    }
+                }
+                Vals<NC> run = exc;
+                auto prefix = [&](int i, double (&out)[NC]) {
+                    if constexpr (KEEP) {
+#pragma unroll
+                        for (int k = 0; k < NC; ++k) out[k] = fma(exc.v[k], kall[i], loc[KEEP ? i : 0].v[k]);
+                    } else {
+                        run = add_kept(run, krow[i], row(i));   // called in row order
+#pragma unroll
+                        for (int k = 0; k < NC; ++k) out[k] = run.v[k];
+                    }
+                };
+                if (want_obj) pass2_breslow<IPT, NC, true>(v, meta, c, prefix);
+                else pass2_breslow<IPT, NC, false>(v, meta, c, prefix);
+            }
+            if (want_obj) {
+#pragma unroll
+                for (int i = 0; i < IPT; ++i) v.obj -= (meta[i] & kEventBit) ? eta[i] : 0.0;
+                v = block_reduce_partial<NW, true>(v, s_red);
+            } else {
+                v = block_reduce_partial<NW, false>(v, s_red);
+            }
+
+            // wave 0 publishes, gathers every workgroup's record and takes the step; the others wait for it
+            if (w == 0) {
+                if (lane == NW - 1) publish_partial(part, G, b, v, epoch, extra, local);
+                Partial tot;
+                StepWord word = {0.0, 0u, kFlagAbort};
+                if (gather_wave(part, G, epoch, extra, ctl, tot)) {
                     uint32_t flags = tot.err ? kFlagNumeric : 0u;
-                    const double g1 = -qj + tot.v[kPC1], g2 = tot.v[kPC2], m2 = tot.v[kPM2];
-                    if (writer) {
-                        L.g1[j] = g1;
-                        L.g2[j] = g2;
-                        L.m2[j] = m2;
-                    }
-                    if (want_obj) {
-                        objective = tot.v[kPObj];
-                        if (fit)
-                            for (int k = 0; k < p; ++k) objective += L.gamma[k] * fabs(sbeta[k]);
-                    }
+                    const double g1 = -qj + tot.c1, g2 = tot.c2, m2 = tot.m2;
                     double step = 0.0;
-                    if (fit && !(flags & kFlagNumeric)) {
+                    if (fit && !tot.err) {
                         int pin = 0;
                         step = ccd_step(bj, g1, g2, m2, gj, &trj, &pin);
                         maxstep = fmax(maxstep, fabs(step));
@@ -688,7 +987,9 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
                         if (j == jend - 1) {
                             ++sweeps;
                             double bmax = 1.0;
-                            for (int k = 0; k < p; ++k) bmax = fmax(bmax, fabs(k == j ? bj + step : sbeta[k]));
+                            for (int k = lane; k < p; k += kWave) bmax = fmax(bmax, fabs(k == j ? bj + step : sbeta[k]));
+#pragma unroll
+                            for (int o = kWave / 2; o >= 1; o >>= 1) bmax = fmax(bmax, __shfl_xor(bmax, o, kWave));
                             if (maxstep <= L.tol * bmax) flags |= kFlagConverged;
                             else if (sweeps >= L.max_sweeps) flags |= kFlagSweepLimit;
                             last_maxstep = maxstep;
@@ -696,34 +997,49 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
                             maxstep = 0.0;
                             pinned = 0;
                         }
-                    }
-                    if (lane == 0) {
-                        if (fit && !(flags & kFlagNumeric)) {
+                        if (lane == 0) {
                             trust[j] = trj;
                             sbeta[j] = bj + step;
                         }
-                        s_step = step;
-                        s_shift = tot.v[kPEtaMax];
-                        s_flags = flags;
                     }
+                    word = StepWord{step, tot.top, flags};
+                    if (lane == 0) s_word = word;
+                    if (writer) {
+                        L.g1[j] = g1;
+                        L.g2[j] = g2;
+                        L.m2[j] = m2;
+                    }
+                    if (want_obj) {
+                        objective = tot.obj;
+                        if (fit) {
+                            // the penalty at the sweep's start (beta_j is already replaced)
+                            double pen = 0.0;
+                            for (int k = lane; k < p; k += kWave) pen = fma(L.gamma[k], fabs(k == j ? bj : sbeta[k]), pen);
+#pragma unroll
+                            for (int o = kWave / 2; o >= 1; o >>= 1) pen += __shfl_xor(pen, o, kWave);
+                            objective += pen;
+                        }
+                    }
+                } else if (lane == 0) {
+                    s_word = word;
                 }
             }
             __syncthreads();
-            if (s_abort) return;
-            const uint32_t flags = s_flags;
-            if (flags & kFlagNumeric) {
+            const StepWord word = s_word;
+            if (word.flags & (kFlagAbort | kFlagNumeric)) {
+                if (word.flags & kFlagAbort) return;
                 stop = kFlagNumeric;
                 break;
             }
-            const double step = s_step;
-            c = s_shift;
+            const double step = word.step;
+            c = fma((double)((int)word.top - kTopBias), kTopStep, c);
             if (step != 0.0) {
 #pragma unroll
                 for (int i = 0; i < IPT; ++i) eta[i] = fma(xc[i], step, eta[i]);
             }
             xc = xn;
-            if (flags & (kFlagConverged | kFlagSweepLimit)) {
-                stop = flags;
+            if (word.flags & (kFlagConverged | kFlagSweepLimit)) {
+                stop = word.flags;
                 break;
             }
         }
@@ -782,7 +1098,7 @@ __global__ __launch_bounds__(kScanBlock) void segscan_kernel(const double *a, co
     const uint32_t epoch = 1;
     SegVal<1> btot;
     SegVal<1> exc = block_exclusive_scan<1, NW>(tagg, s_wtot, btot);
-    if (t == 0) publish_aggregate<1>(agg, b, btot, epoch);
+    if (t == 0) publish_aggregate<1>(agg, b, btot, epoch, false);
     const bool tile_head = tile0 >= n || tile0 == 0 || head[tile0] != 0;
     if (!tile_head) {
         SegVal<1> carry;
@@ -801,57 +1117,52 @@ __global__ __launch_bounds__(kScanBlock) void segscan_kernel(const double *a, co
 
 namespace {
 
-constexpr int kCcdBlock = kThreads;
-
 // Dynamic LDS of one persistent workgroup: beta.
 size_t ccd_smem_bytes(int, int p)
 {
     return sizeof(double) * (size_t)p;
 }
 
-template <int IPT, int XK, bool EFRON, bool WAVE>
-const void *ccd_fn()
-{
-    return reinterpret_cast<const void *>(&ccd_kernel<kCcdBlock, IPT, XK, EFRON, WAVE>);
-}
-
+// One instantiation per workgroup shape (kShapes).
 template <int XK, bool EFRON, bool WAVE>
-const void *ccd_fn_ipt(int ipt)
+const void *ccd_fn(int threads, int ipt)
 {
-    switch (ipt) {
-    case 1: return ccd_fn<1, XK, EFRON, WAVE>();
-    case 2: return ccd_fn<2, XK, EFRON, WAVE>();
-    case 4: return ccd_fn<4, XK, EFRON, WAVE>();
-    case 8: return ccd_fn<8, XK, EFRON, WAVE>();
-    case 16: return ccd_fn<16, XK, EFRON, WAVE>();
-    default: return nullptr;
+    if (threads == 512) {
+        if (ipt == 8) return reinterpret_cast<const void *>(&ccd_kernel<512, 8, XK, EFRON, WAVE>);
+        if (ipt == 16) return reinterpret_cast<const void *>(&ccd_kernel<512, 16, XK, EFRON, WAVE>);
+    } else if (threads == 256) {
+        if (ipt == 1) return reinterpret_cast<const void *>(&ccd_kernel<256, 1, XK, EFRON, WAVE>);
+        if (ipt == 2) return reinterpret_cast<const void *>(&ccd_kernel<256, 2, XK, EFRON, WAVE>);
+        if (ipt == 4) return reinterpret_cast<const void *>(&ccd_kernel<256, 4, XK, EFRON, WAVE>);
+        if (ipt == 8) return reinterpret_cast<const void *>(&ccd_kernel<256, 8, XK, EFRON, WAVE>);
     }
+    return nullptr;
 }
 
 template <bool WAVE>
-const void *ccd_function_w(int ipt, int xk, bool efron)
+const void *ccd_function_w(int threads, int ipt, int xk, bool efron)
 {
-    if (xk == 2) return efron ? ccd_fn_ipt<2, true, WAVE>(ipt) : ccd_fn_ipt<2, false, WAVE>(ipt);
-    if (xk == 1) return efron ? ccd_fn_ipt<1, true, WAVE>(ipt) : ccd_fn_ipt<1, false, WAVE>(ipt);
-    return efron ? ccd_fn_ipt<0, true, WAVE>(ipt) : ccd_fn_ipt<0, false, WAVE>(ipt);
+    if (xk == 2) return efron ? ccd_fn<2, true, WAVE>(threads, ipt) : ccd_fn<2, false, WAVE>(threads, ipt);
+    if (xk == 1) return efron ? ccd_fn<1, true, WAVE>(threads, ipt) : ccd_fn<1, false, WAVE>(threads, ipt);
+    return efron ? ccd_fn<0, true, WAVE>(threads, ipt) : ccd_fn<0, false, WAVE>(threads, ipt);
 }
 
 // xk: 0 dense X, 1 indicator X, 2 sparse values (see XCol)
-const void *ccd_function(int ipt, int xk, bool efron, bool wave)
+const void *ccd_function(int threads, int ipt, int xk, bool efron, bool wave)
 {
-    return wave ? ccd_function_w<true>(ipt, xk, efron) : ccd_function_w<false>(ipt, xk, efron);
+    return wave ? ccd_function_w<true>(threads, ipt, xk, efron) : ccd_function_w<false>(threads, ipt, xk, efron);
 }
 
 // Workgroups of the persistent kernel that fit on one compute unit; every variant
 // (indicator or sparse X, Efron, wave-aligned layout) must fit, since a handle may run any of them.
-int occupancy_for(int ipt, int p, int *blocks)
+int occupancy_for(int threads, int ipt, int p, int *blocks)
 {
     *blocks = 1 << 30;
     for (int v = 0; v < 12; ++v) {
-        const void *fn = ccd_function(ipt, v % 3, ((v / 3) & 1) != 0, ((v / 3) & 2) != 0);
+        const void *fn = ccd_function(threads, ipt, v % 3, ((v / 3) & 1) != 0, ((v / 3) & 2) != 0);
         if (!fn) return (int)hipErrorInvalidValue;
         int nb = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kCcdBlock, ccd_smem_bytes(ipt, p));
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, ccd_smem_bytes(ipt, p));
         if (e != hipSuccess) return (int)e;
         *blocks = nb < *blocks ? nb : *blocks;
     }
@@ -868,7 +1179,7 @@ int device_cus(int *cus)
 
 }  // namespace
 
-int max_resident_groups(int ipt, int p, int *groups, std::string &err)
+int max_resident_groups(int threads, int ipt, int p, int *groups, std::string &err)
 {
     *groups = 0;
     int cus = 0;
@@ -876,8 +1187,27 @@ int max_resident_groups(int ipt, int p, int *groups, std::string &err)
         err = "cannot query the device's compute-unit count";
         return -3;
     }
-    int blocks = 0;
-    if (occupancy_for(ipt, p, &blocks) != (int)hipSuccess) {
+    // Twelve occupancy queries take tens of microseconds, as long as a small refit's kernels: asked
+    // once per device and shape at the most columns (the most LDS); a smaller p then fits too.
+    static std::mutex mu;
+    static std::map<std::array<int, 3>, int> at_most_columns;
+    int dev = -1, blocks = 0;
+    (void)hipGetDevice(&dev);
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        const auto key = std::array<int, 3>{dev, threads, ipt};
+        const auto it = at_most_columns.find(key);
+        if (it != at_most_columns.end()) {
+            blocks = it->second;
+        } else {
+            if (occupancy_for(threads, ipt, (int)kMaxCcdP, &blocks) != (int)hipSuccess) {
+                err = "occupancy query failed";
+                return -3;
+            }
+            at_most_columns[key] = blocks;
+        }
+    }
+    if (blocks < 1 && occupancy_for(threads, ipt, p, &blocks) != (int)hipSuccess) {
         err = "occupancy query failed";
         return -3;
     }
@@ -892,11 +1222,12 @@ int launch_ccd(const LaunchShape &shape, const CcdLaunch &L, hipStream_t stream,
     if (e != hipSuccess) return (int)e;
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return (int)e;
     CcdLaunch arg = L;
+    arg.spread = shape.spread;
     void *args[] = {&arg};
     const size_t smem = ccd_smem_bytes(shape.ipt, L.p);
-    const void *fn = ccd_function(shape.ipt, L.xvals ? 2 : (L.xbits ? 1 : 0), L.efron != 0, shape.wave);
+    const void *fn = ccd_function(shape.threads, shape.ipt, L.xvals ? 2 : (L.xbits ? 1 : 0), L.efron != 0, shape.wave);
     if (!fn) return (int)hipErrorInvalidValue;
-    e = hipLaunchCooperativeKernel(fn, dim3(shape.grid), dim3(kCcdBlock), args, (unsigned)smem, stream);
+    e = hipLaunchCooperativeKernel(fn, dim3(shape.grid * shape.spread), dim3(shape.threads), args, (unsigned)smem, stream);
     if (e != hipSuccess) return (int)e;
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return (int)e;
     return (int)hipSuccess;

@@ -104,59 +104,95 @@ static int64_t aligned_positions(const std::vector<uint32_t> &meta, int64_t R, s
     return cur;
 }
 
-// Rows per thread, workgroups and device row positions for the persistent
-// kernel: the fewest rows per thread whose workgroup count fits one per
-// compute unit, preferring a layout in which no stratum crosses a wave's rows
-// (then every wave's scan is its own, with no carry between waves), then one in
-// which no stratum that fits a workgroup tile crosses a tile boundary.
-static int choose_layout(const std::vector<uint32_t> &meta, int p, LaunchShape &shape,
+// Workgroup shapes of the persistent kernel, by rows per tile (threads x ipt).  Few waves with
+// several rows each beat many waves with one: a SIMD issues a wave's lane steps (scan, sums) once
+// per wave, whatever the rows, so 256 threads are used until a compute unit needs 4096 rows.
+static const struct { int threads, ipt; } kShapes[] = {{256, 1}, {256, 2}, {256, 4}, {256, 8}, {512, 8}, {512, 16}};
+
+// Length of the layout whose tiles hold R rows and in which no stratum that fits a tile crosses
+// a tile boundary (what aligned_positions returns), from the strata's lengths.
+static int64_t aligned_length(const std::vector<int64_t> &strata, int64_t R)
+{
+    int64_t cur = 0;
+    for (const int64_t m : strata) {
+        const int64_t room = R - (cur % R);
+        if (m <= R && m > room) cur += room;
+        cur += m;
+    }
+    return cur;
+}
+
+// Microseconds per coordinate of the persistent kernel, fitted to measurements on one MI355X
+// (N = 2e3 ... 1e6, K = 1 ... N/20, every shape): the passes are issued once per wave and once
+// per row; the exchange of records goes through one XCD's L2 (spread) or through device memory,
+// where it grows with the workgroups that poll; a carry between tiles is a second exchange.
+// Measured against the model: 256 x 4 on one XCD, 10 and 32 tiles: 2.44, 2.48 us (2.54); across
+// the chip, 10, 32, 105, 250 tiles: 2.89, 3.17, 3.82, 4.36 us (3.02, 3.32, 3.87, 4.54).
+// 16 rows per thread read 128 bytes per lane and miss the L1 (6 us more).
+static double coordinate_us(int threads, int ipt, int grid, int spread, bool wave, bool carries)
+{
+    const double waves = threads / 256.0;
+    const double passes = waves * (0.15 + 0.085 * ipt) + (ipt > 8 ? 6.0 : 0.0) + (wave ? 0.0 : 0.25);
+    const double hop = grid == 1 ? 1.0 : (spread > 1 ? 1.3 : 1.4 + 0.12 * std::sqrt((double)grid));
+    return 0.75 + passes + hop + (carries ? hop : 0.0);
+}
+
+// Workgroup shape, workgroups and device row positions for the persistent kernel.  For each
+// shape the layout is, in order of preference, one in which no stratum crosses a wave's rows
+// (every wave's scan is its own), one in which no stratum that fits a tile crosses a tile
+// boundary, or the rows as they are, whichever fits one workgroup per compute unit.  CCD handles
+// take the shape with the least time per coordinate, on one XCD's compute units where that is
+// faster; Newton handles (whose column pass wants many tiles) the fewest rows per thread.
+static int choose_layout(const std::vector<uint32_t> &meta, int p, bool latency, LaunchShape &shape,
                          std::vector<int64_t> &pos, std::string &err)
 {
     const int64_t n = (int64_t)meta.size();
     pos.assign(n, 0);
-    shape.wave = false;
+    std::vector<int64_t> strata;
     int64_t longest = 0;   // the longest stratum
     for (int64_t i = 0; i < n;) {
         int64_t e = i + 1;
         while (e < n && !(meta[e] & kHeadBit)) ++e;
         longest = std::max(longest, e - i);
+        strata.push_back(e - i);
         i = e;
     }
-    const int ipts[] = {1, 2, 4, 8, 16};
-    for (int ipt : ipts) {
+    int kind = 0;             // of the best shape: 1 wave-aligned, 2 tile-aligned, 3 as they are
+    double best = INFINITY;
+    for (const auto &sh : kShapes) {
+        if (!latency && sh.threads * sh.ipt < 512) continue;
         int groups = 0;
-        if (max_resident_groups(ipt, p, &groups, err) != 0) return COX_EDEVICE;
+        if (max_resident_groups(sh.threads, sh.ipt, p, &groups, err) != 0) return COX_EDEVICE;
         if (groups < 1) continue;
-        const int64_t R = (int64_t)kThreads * ipt, Rw = (int64_t)kWaveRows * ipt;
-        if (longest <= Rw) {
-            const int64_t lw = aligned_positions(meta, Rw, nullptr);
-            if ((lw + R - 1) / R <= groups) {
-                aligned_positions(meta, Rw, &pos);
-                shape.ipt = ipt;
-                shape.grid = (int)((lw + R - 1) / R);
-                shape.ld = (int64_t)shape.grid * R;
-                shape.wave = true;
-                return 0;
+        const int64_t R = (int64_t)sh.threads * sh.ipt, Rw = (int64_t)kWaveRows * sh.ipt;
+        const int64_t lens[] = {longest <= Rw ? aligned_length(strata, Rw) : INT64_MAX, aligned_length(strata, R), n};
+        for (int k = 0; k < 3; ++k) {
+            if (lens[k] == INT64_MAX || (lens[k] + R - 1) / R > groups) continue;
+            const int grid = (int)((lens[k] + R - 1) / R);
+            for (int spread = 1; spread <= kXcds; spread *= kXcds) {
+                if (spread > 1 && (!latency || (int64_t)grid * spread > groups || grid < 2)) continue;
+                const double us = coordinate_us(sh.threads, sh.ipt, grid, spread, k == 0, grid > 1 && (k == 2 || longest > R));
+                if (us >= best) continue;
+                best = us;
+                kind = k + 1;
+                shape.threads = sh.threads;
+                shape.ipt = sh.ipt;
+                shape.grid = grid;
+                shape.spread = spread;
+                shape.ld = (int64_t)grid * R;
+                shape.wave = k == 0;
             }
+            break;
         }
-        const int64_t la = aligned_positions(meta, R, nullptr);
-        if ((la + R - 1) / R <= groups) {
-            aligned_positions(meta, R, &pos);
-            shape.ipt = ipt;
-            shape.grid = (int)((la + R - 1) / R);
-            shape.ld = (int64_t)shape.grid * R;
-            return 0;
-        }
-        if ((n + R - 1) / R <= groups) {
-            std::iota(pos.begin(), pos.end(), int64_t(0));
-            shape.ipt = ipt;
-            shape.grid = (int)((n + R - 1) / R);
-            shape.ld = (int64_t)shape.grid * R;
-            return 0;
-        }
+        if (!latency && kind) break;
     }
-    err = "n exceeds the register-resident capacity of the persistent kernel (CUs x 512 x 16 rows)";
-    return COX_EUNSUPPORTED;
+    if (!kind) {
+        err = "n exceeds the register-resident capacity of the persistent kernel (CUs x 512 x 16 rows)";
+        return COX_EUNSUPPORTED;
+    }
+    if (kind == 3) std::iota(pos.begin(), pos.end(), int64_t(0));
+    else aligned_positions(meta, kind == 1 ? (int64_t)kWaveRows * shape.ipt : (int64_t)shape.threads * shape.ipt, &pos);
+    return 0;
 }
 
 // Layout for data sets beyond the persistent kernel (Newton fits only): tiles
@@ -176,6 +212,8 @@ static void tile_layout(const std::vector<uint32_t> &meta, LaunchShape &shape, s
     }
     const int64_t rows = la <= n + n / 8 ? la : n;
     shape.ipt = 0;
+    shape.threads = 0;
+    shape.spread = 1;
     shape.wave = false;
     shape.grid = (int)((rows + kNewtonTile - 1) / kNewtonTile);
     shape.ld = (int64_t)shape.grid * kNewtonTile;
@@ -247,7 +285,7 @@ static int check_options(const cox_options &opt, std::string &msg)
 // handle too long for the persistent kernel (p <= kMaxNewtonP).
 static int layout_for(cox_handle *h, std::string &err, bool dense)
 {
-    int rc = choose_layout(h->meta, (int)h->p, h->shape, h->pos, err);
+    int rc = choose_layout(h->meta, (int)h->p, h->opt.mode == COX_CCD, h->shape, h->pos, err);
     if (rc == COX_EUNSUPPORTED &&
         (h->opt.mode == COX_NEWTON_REFINE || (dense && h->p <= kMaxNewtonP))) {
         tile_layout(h->meta, h->shape, h->pos);

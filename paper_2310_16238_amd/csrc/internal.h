@@ -14,26 +14,28 @@ constexpr uint32_t kEventBit = 0x40000000u;
 constexpr uint32_t kPadBit = 0x20000000u;     // device layout only: a padding row
 constexpr uint32_t kCountMask = 0x1fffffffu;
 
-constexpr int kThreads = 512;           // threads per workgroup of the CCD kernel
 constexpr int kWaveRows = 64;           // threads per wave: a wave owns kWaveRows * ipt consecutive rows
 constexpr int kMaxGroups = 256;         // workgroups of one persistent launch (one per compute unit)
+constexpr int kXcds = 8;                // accelerator dies, each with its own L2; workgroups are dealt to them in turn
 constexpr int64_t kMaxCcdP = 12288;     // columns of the persistent kernel (beta in LDS: 96 KB)
 constexpr int64_t kMaxNewtonP = 4096;   // columns of the Newton / full-evaluation path
 
 enum KernelMode { kModeFit = 0, kModeEval = 1 };
 
-// Resident launch shape of a data set: `grid` workgroups of kThreads threads,
-// each thread owning `ipt` consecutive rows; ld = grid * kThreads * ipt rows.
+// Resident launch shape of a data set: `grid` workgroups of `threads` threads,
+// each thread owning `ipt` consecutive rows; ld = grid * threads * ipt rows.
 struct LaunchShape {
+    int threads = 0;
     int ipt = 0;
     int grid = 0;
     int64_t ld = 0;
+    int spread = 1;      // workgroups launched per working one (8: the working ones share one XCD)
     bool wave = false;   // every stratum lies within one wave's rows (kWaveRows(ipt)): wave-local scans
 };
 
-// Workgroups that fit on the device at once for the persistent kernel with
-// `ipt` rows per thread (0 if it does not fit); at most one per compute unit.
-int max_resident_groups(int ipt, int p, int *groups, std::string &err);
+// Workgroups that fit on the device at once for the persistent kernel with `threads` threads
+// of `ipt` rows each (0 if it does not fit); at most one per compute unit.
+int max_resident_groups(int threads, int ipt, int p, int *groups, std::string &err);
 
 // Arguments of one persistent launch (device pointers unless noted).
 struct CcdLaunch {
@@ -54,6 +56,7 @@ struct CcdLaunch {
     int mode = kModeFit;
     int efron = 0;                   // 1: Efron's tie correction instead of the plain risk sets
     int wave = 0;                    // 1: the layout is wave-aligned (LaunchShape::wave)
+    int spread = 1;                  // LaunchShape::spread
     int j0 = 0, j1 = 0;              // evaluation: columns [j0, j1)
     int max_sweeps = 0;
     double tol = 0.0;

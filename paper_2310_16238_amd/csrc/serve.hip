@@ -1258,7 +1258,7 @@ __device__ int round_barrier(const RoundWork &w, RoundCtl *ctl, uint32_t epoch, 
             __hip_atomic_store(&ctl->hold[round & 1], h != 0u ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __threadfence();
-        packet_put(arrive, blockIdx.x, 0.0, epoch, 0u);
+        packet_put(arrive, blockIdx.x, 0.0, epoch, 0u, false);
     }
     if (t < kWave) {
         bool ok = true;
