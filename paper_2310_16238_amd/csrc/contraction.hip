@@ -1451,102 +1451,168 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
 // Proximal Newton's model solve: cyclic coordinate descent with soft thresholding (the l1
 // rule of Sec. 2.4, applied to the quadratic model of the objective)
 //   min_D  g'D + D'HD/2 + sum_j gamma_j |beta_j + D_j|
-// in one wave.  Every lane takes the same scalar decision for coordinate j from inputs
-// broadcast out of LDS; lane l keeps HD[k] (k = l mod 64) up to date from row j of the
-// symmetric H when D_j moves.  Row j+1's first kProxPre * 64 entries are loaded into
-// registers while coordinate j is decided.  Coordinates not free, or with H_jj <= 0 or not
-// finite, stay at 0.  Stops after the first sweep whose largest |change| is <= tol, or after
-// max_sweeps sweeps.
-constexpr int kProxChunk = 1024;   // coordinates whose inputs are staged in LDS at a time
-constexpr int kProxPre = 16;       // prefetched entries of a row per lane (1024 columns)
+// in one workgroup.  With z_j = beta_j + D_j and a_j = H_jj, coordinate j moves to
+// soft(u_j, gamma_j) / a_j where u_j = a_j z_j - g_j - (HD)_j, and a move of another coordinate i by
+// delta changes u_j by -H_ij delta (its own move leaves u_j as it is).  Coordinates not free, or
+// with H_jj <= 0 or not finite, stay.  Stops after the first sweep whose largest |change| is
+// <= tol, or after max_sweeps sweeps.
+//
+// The chain is what bounds it: each coordinate needs the one before.  Coordinates go in blocks
+// of 64: wave 0 holds a block's u in its lanes and takes its 64 decisions in turn from the
+// 64 x 64 diagonal block in LDS (7 dependent FP64 operations and a lane broadcast each), while the
+// other waves stage the next diagonal block; then all 16 waves apply the block's moves to the
+// rest of u, a row of H per moved coordinate, 32 rows in flight.  One wave that
+// fetched a row of H per coordinate (a memory round trip each) took 9.9 ms per solve in a
+// p = 1000 fit; this takes 2.0 ms.
+constexpr int kProxB = 64;         // coordinates of a block
+constexpr int kProxThreads = 1024;
+constexpr int kProxRows = 32;      // rows of H in flight per thread
 
-__global__ __launch_bounds__(64) void prox_cd_kernel(const double *H, int p, const double *g, const double *beta,
-                                                     const double *gam, const uint8_t *free_col, double tol,
-                                                     int max_sweeps, double *D, int *sweeps_out)
+__global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, int p, const double *g,
+                                                               const double *beta, const double *gam,
+                                                               const uint8_t *free_col, double tol, int max_sweeps,
+                                                               double *D, int *sweeps_out)
 {
-    extern __shared__ double sm[];   // HD[p], Dv[p]
-    double *HD = sm, *Dv = sm + p;
-    __shared__ double cg[kProxChunk], cb[kProxChunk], cgam[kProxChunk], ca[kProxChunk];
-    const int lane = threadIdx.x;
-    for (int k = lane; k < p; k += 64) {
-        HD[k] = 0.0;
-        Dv[k] = 0.0;
-    }
-    double nxt[kProxPre];
-    auto load_row = [&](int j) {
-        const double *row = H + (size_t)j * p;
-#pragma unroll
-        for (int m = 0; m < kProxPre; ++m) {
-            const int k = lane + 64 * m;
-            nxt[m] = k < p ? row[k] : 0.0;
+    extern __shared__ double sm[];   // u[p], z[p], two diagonal blocks (row-major, zero diagonal)
+    double *u = sm, *z = sm + p, *blk = sm + 2 * (size_t)p;
+    __shared__ double s_delta[kProxB];
+    __shared__ int s_row[kProxB], s_moved;
+    __shared__ double s_change;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
+    const int nblk = (p + kProxB - 1) / kProxB;
+    auto stage = [&](int block, int first, int threads) {
+        double *dst = blk + (block & 1) * (kProxB * kProxB);
+        const int j0 = block * kProxB;
+        for (int e = t - first; e < kProxB * kProxB; e += threads) {
+            const int r = e / kProxB, c = e % kProxB;
+            dst[e] = (r != c && j0 + r < p && j0 + c < p) ? H[(size_t)(j0 + r) * p + j0 + c] : 0.0;
         }
     };
+    for (int k = t; k < p; k += kProxThreads) {
+        const double bk = beta[k];
+        u[k] = fma(H[(size_t)k * p + k], bk, -g[k]);
+        z[k] = bk;
+    }
+    stage(0, 0, kProxThreads);
+    // wave 0's inputs of its lane's coordinate, one block ahead; inverse 0: the coordinate stays
+    double ga = 0.0, inv = 0.0;
+    auto inputs = [&](int block, double &gm, double &iv) {
+        const int j = block * kProxB + lane;
+        gm = 0.0;
+        iv = 0.0;
+        if (j < p) {
+            const double a = H[(size_t)j * p + j];
+            gm = gam[j];
+            iv = (free_col[j] && a > 0.0 && a < INFINITY) ? 1.0 / a : 0.0;
+        }
+    };
+    if (w == 0) inputs(0, ga, inv);
     int sweep = 0;
     while (sweep < max_sweeps) {
         ++sweep;
-        double change = 0.0;
-        for (int j0 = 0; j0 < p; j0 += kProxChunk) {
-            const int jn = p - j0 < kProxChunk ? p - j0 : kProxChunk;
-            __syncthreads();
-            for (int i = lane; i < jn; i += 64) {
-                const int j = j0 + i;
-                const double a = H[(size_t)j * p + j];
-                cg[i] = g[j];
-                cb[i] = beta[j];
-                cgam[i] = gam[j];
-                ca[i] = (free_col[j] && a > 0.0 && a < INFINITY) ? a : 0.0;
-            }
-            load_row(j0);
-            __syncthreads();
-            for (int i = 0; i < jn; ++i) {
-                const int j = j0 + i;
-                double cur[kProxPre];
+        double change = 0.0;   // wave 0's lanes
+        for (int b = 0; b < nblk; ++b) {
+            const int nextb = b + 1 < nblk ? b + 1 : 0;
+            const int j0 = b * kProxB, nb = p - j0 < kProxB ? p - j0 : kProxB;
+            // one block stays where it is; with an odd number the first one's buffer is the last one's too
+            const bool restage = nblk > 1, clash = restage && nextb == 0 && (b & 1) == 0;
+            __syncthreads();   // u holds every earlier move, the diagonal block is staged
+            if (w == 0) {
+                double gn, invn;
+                inputs(nextb, gn, invn);   // in flight during the decisions
+                const bool live = lane < nb && inv != 0.0;
+                double ul = lane < nb ? u[j0 + lane] : 0.0, zl = lane < nb ? z[j0 + lane] : 0.0;
+                double moved = 0.0;
+                const double *row = blk + (b & 1) * (kProxB * kProxB) + lane;
+                double hc[8], hn[8];
 #pragma unroll
-                for (int m = 0; m < kProxPre; ++m) cur[m] = nxt[m];
-                if (i + 1 < jn) load_row(j + 1);
-                const double a = ca[i];
-                if (a == 0.0) continue;
-                const double bj = cb[i], gm = cgam[i], dj = Dv[j];
-                const double b = cg[i] + HD[j] - a * dj;   // the model's slope at D with D_j removed
-                const double u = a * bj - b;
-                const double z = u > gm ? (u - gm) / a : (u < -gm ? (u + gm) / a : 0.0);
-                const double dn = z - bj;
-                const double delta = dn - dj;
-                if (delta != 0.0) {
-                    __syncthreads();   // every lane has read Dv[j] and HD[j]
-                    if (lane == 0) Dv[j] = dn;
+                for (int q = 0; q < 8; ++q) hc[q] = row[q * kProxB];
+                for (int i0 = 0; i0 < nb; i0 += 8) {
+                    const int in = i0 + 8 < kProxB ? i0 + 8 : 0;
 #pragma unroll
-                    for (int m = 0; m < kProxPre; ++m) {
-                        const int k = lane + 64 * m;
-                        if (k < p) HD[k] += cur[m] * delta;
+                    for (int q = 0; q < 8; ++q) hn[q] = row[(in + q) * kProxB];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        // every lane's move as of now; lane i0 + q takes its own
+                        const double soft = ul > ga ? ul - ga : (ul < -ga ? ul + ga : 0.0);
+                        const double znew = live ? soft * inv : zl;
+                        const double delta = lane_value(znew - zl, i0 + q);
+                        if (lane == i0 + q) {
+                            moved = znew - zl;
+                            zl = znew;
+                        }
+                        ul = fma(-hc[q], delta, ul);
                     }
-                    for (int k = lane + 64 * kProxPre; k < p; k += 64) HD[k] += H[(size_t)j * p + k] * delta;
-                    change = fmax(change, fabs(delta));
-                    __syncthreads();   // HD and Dv written before the next coordinate reads them
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) hc[q] = hn[q];
                 }
+                if (lane < nb) {
+                    u[j0 + lane] = ul;
+                    z[j0 + lane] = zl;
+                }
+                change = fmax(change, fabs(moved));
+                // the moved coordinates, in order
+                const unsigned long long mask = __builtin_amdgcn_ballot_w64(moved != 0.0);
+                if (moved != 0.0) {
+                    const int at = __popcll(mask & ((1ull << lane) - 1ull));
+                    s_delta[at] = moved;
+                    s_row[at] = j0 + lane;
+                }
+                if (lane == 0) s_moved = __popcll(mask);
+                ga = gn;
+                inv = invn;
+            } else if (restage && !clash) {
+                stage(nextb, 64, kProxThreads - 64);
             }
+            __syncthreads();
+            const int m = s_moved;
+            for (int k = t; k < p; k += kProxThreads) {
+                if (k >= j0 && k < j0 + nb) continue;
+                double acc = u[k];
+                for (int q0 = 0; q0 < m; q0 += kProxRows) {
+                    double h[kProxRows];
+#pragma unroll
+                    for (int q = 0; q < kProxRows; ++q) {
+                        const int r = s_row[q0 + q < m ? q0 + q : q0];
+                        h[q] = H[(size_t)r * p + k];
+                    }
+#pragma unroll
+                    for (int q = 0; q < kProxRows; ++q)
+                        if (q0 + q < m) acc = fma(-h[q], s_delta[q0 + q], acc);
+                }
+                u[k] = acc;
+            }
+            if (clash) stage(nextb, 0, kProxThreads);   // nobody reads the buffer before the next barrier
         }
-        if (change <= tol) break;
+        if (w == 0) {
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) change = fmax(change, __shfl_xor(change, o, 64));
+            if (lane == 0) s_change = change;
+        }
+        __syncthreads();
+        const double most = s_change;
+        if (most <= tol) break;
     }
     __syncthreads();
-    for (int k = lane; k < p; k += 64) D[k] = Dv[k];
-    if (lane == 0) *sweeps_out = sweep;
+    for (int k = t; k < p; k += kProxThreads) D[k] = z[k] - beta[k];
+    if (t == 0) *sweeps_out = sweep;
 }
 
 int prox_model_solve(const double *H, int p, const double *g, const double *beta, const double *gam,
                      const uint8_t *free_col, double tol, int max_sweeps, double *D, int *sweeps, hipStream_t stream)
 {
     if (p < 1 || p > 4096) return -1;
-    const size_t lds = sizeof(double) * 2 * (size_t)p;
+    const size_t lds = sizeof(double) * (2 * (size_t)p + 2 * kProxB * kProxB);
     static bool attr = false;
     if (!attr) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(&prox_cd_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(double) * 2 * 4096)) !=
-            hipSuccess)
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(sizeof(double) * (2 * 4096 + 2 * kProxB * kProxB))) != hipSuccess)
             return -3;
         attr = true;
     }
-    prox_cd_kernel<<<1, 64, lds, stream>>>(H, p, g, beta, gam, free_col, tol, max_sweeps, D, sweeps);
+    prox_cd_kernel<<<1, kProxThreads, lds, stream>>>(H, p, g, beta, gam, free_col, tol, max_sweeps, D, sweeps);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
