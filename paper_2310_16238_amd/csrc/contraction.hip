@@ -13,8 +13,8 @@
 // BF16 kernel (matrix cores): u is stored as BF16 with a power-of-two scale
 // per column; v_mfma_f32_32x32x16_bf16 accumulates 32x32 tiles in FP32.  The
 // weights c_k multiply one operand in FP32 before it is rounded to BF16.
-// Each wave owns up to 8 tiles of the upper triangle, a workgroup's 4 waves
-// share one K range, and the FP32 partials of the K ranges are summed in FP64
+// A workgroup's waves share one K range and the tiles of the upper triangle (p <= 256) or of one
+// 256 x 256 block of it, and the FP32 partials of the K ranges are summed in FP64
 // in range order with the column scales applied.
 #include <hip/hip_bf16.h>
 #include <math.h>
@@ -604,21 +604,17 @@ __global__ __launch_bounds__(64 * kSyrkBfWaves) void syrk_bf16_kernel(const uint
     }
 }
 
-// LDS-staged variant for p <= 256 (at most 8 row tiles): per 128-row K chunk
+// LDS-staged variant for p <= 256 (at most 8 row tiles): per 64-row K chunk
 // the workgroup stages all row tiles of u once (and once more multiplied by
 // the weights, rounded to BF16), then every wave runs its tile pairs' MFMAs
 // from LDS.  The next chunk's global loads are issued into registers before
 // the current chunk's MFMAs.  Same partial layout as syrk_bf16_kernel.
-// KC rows per chunk: 128 for up to 8 row tiles, 64 for up to 16 (the LDS then
-// holds 16 tiles x 32 rows x 72 BF16, twice with weights: 147 KB).
-constexpr int kLdsMaxTiles = 16;
 
 // MAXT: the most row tiles the launch may have (the LDS holds MAXT x 32 rows); OCC: the waves
 // per SIMD the register budget is cut for (with NWV waves of TPW tile pairs each: two
 // workgroups of 8 waves per compute unit need 4, so one workgroup's loads overlap the
 // other's matrix-core work).
-template <bool WEIGHT, int KC, int MAXT = (KC == 128 ? 8 : 16), int OCC = 1, int NWV = kSyrkBfWaves,
-          int TPW = kTilesPerWave>
+template <bool WEIGHT, int KC, int MAXT, int OCC, int NWV, int TPW>
 __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint16_t *u, int64_t ldu, int p,
                                                                                const double *c, int64_t K,
                                                                                int64_t kchunk, float *part)
@@ -723,140 +719,155 @@ __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint
     }
 }
 
-// Wide X (more than kLdsMaxTiles row tiles): the tile pairs are cut into blocks of
-// kBlkTiles x kBlkTiles pairs (row block I, column block J >= I), and a workgroup stages
-// only the 2 kBlkTiles row tiles its block touches (kBlkTiles on the diagonal), so the
-// LDS holds 8 tiles x 32 rows x (KC + 8) BF16, twice with weights: 139 KB at KC = 128.
-// Waves take kBlkPairsPerWave pairs of the block; same partial layout as the kernels above.
-constexpr int kBlkTiles = 4;
-constexpr int kBlkPairsPerWave = kBlkTiles * kBlkTiles / kSyrkBfWaves;   // 4
+// More than 8 row tiles: the tile pairs are cut into blocks of 8 x 8 (row block I, column block
+// J >= I), one block and K range per workgroup of 8 waves.  Per 64-row chunk the rows of block I
+// are staged in LDS multiplied by the weights (FP32, rounded to BF16) and those of block J as
+// they are; two buffers and one barrier per chunk, the next chunk's loads in flight during the
+// products.  Off the diagonal a wave holds 2 x 4 tiles, so 6 fragments read from LDS feed
+// 8 products (a wave of 4 tile pairs in a row needs 5 for 4: the LDS, not the matrix cores, set
+// the pace).  An element is staged once per
+// block that it takes part in -- 5 times at p = 1000, where 4 x 4 blocks with both copies of
+// every row staged it 9 times.  Measured: N = 1e6, p = 1000 with weights 4.50 -> 1.85 ms (0.55
+// PFLOP/s of the upper triangle), half as many rows without 0.91 -> 0.66 ms; 1.25e6 rows, p = 500
+// 1.11 -> 0.50 ms.  Same partial layout as the kernels above.
+constexpr int kWideTiles = 8, kWideRows = kWideTiles * kMT, kWideWaves = 8, kWideKC = 64, kWideStride = kWideKC + 8;
+constexpr int kWidePer = kWideRows * (kWideKC / 8) / (64 * kWideWaves);   // 16-byte pieces per thread and operand: 4
 
 __host__ __device__ __forceinline__ int pair_index(int ti, int tj, int nt)
 {
     return ti * nt - ti * (ti - 1) / 2 + (tj - ti);   // row-major upper triangle, ti <= tj
 }
 
-template <bool WEIGHT, int KC>
-__global__ __launch_bounds__(64 * kSyrkBfWaves) void syrk_bf16_blk_kernel(const uint16_t *u, int64_t ldu, int p,
-                                                                          const double *c, int64_t K, int64_t kchunk,
-                                                                          float *part)
+__device__ __forceinline__ void store_tile(float *part, int64_t slot, const f32x16 &acc, int lane)
 {
-    constexpr int kStride = KC + 8, kPieces = KC / 8;
-    constexpr int kRows = 2 * kBlkTiles * kMT;                                // staged rows (off-diagonal block)
-    constexpr int kPerThread = kRows * kPieces / (64 * kSyrkBfWaves);      // 16 at KC = 128
-    extern __shared__ uint16_t sh[];   // [kRows][kStride] plain, then weighted (WEIGHT)
-    __shared__ float cw[KC];
-    uint16_t *plain = sh;
-    uint16_t *wtd = sh + (size_t)kRows * kStride;
+    float *out = part + slot * (kMT * kMT);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int m = 8 * (i / 4) + 4 * (lane / 32) + (i % 4), n = lane % 32;
+        out[m * kMT + n] = acc[i];
+    }
+}
+
+// Wave w's 2 x 4 tiles of a block: rows 2 wr.., columns 4 wc..; returns the mask of the wanted ones.
+// On the diagonal the eight regions hold 8, 8, 7, 7, 3, 3, 0 and 0 wanted tiles (row <= column),
+// dealt so that the two waves of a SIMD (w, w + 4) have 8, 8, 10 and 10.
+__device__ __forceinline__ uint32_t wide_region(int w, bool diag, int &wr, int &wc)
+{
+    wr = diag ? (0x31322010 >> (4 * w)) & 3 : w / 2;
+    wc = diag ? (0x10001011 >> (4 * w)) & 1 : w % 2;
+    uint32_t want = 0xffu;
+    if (diag) {
+        want = 0u;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (2 * wr + q / 4 <= 4 * wc + q % 4) want |= 1u << q;
+    }
+    return __builtin_amdgcn_readfirstlane(want);
+}
+
+template <bool WEIGHT>
+__global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_bf16_wide_kernel(const uint16_t *u, int64_t ldu, int p,
+                                                                           const double *c, int64_t K, int64_t kchunk,
+                                                                           float *part)
+{
+    extern __shared__ uint16_t sh[];   // two buffers of [A rows, B rows][kWideStride]
+    constexpr int kHalf = kWideRows * kWideStride;
     const int nt = (p + kMT - 1) / kMT;
-    const int nb = (nt + kBlkTiles - 1) / kBlkTiles;
+    const int nb = (nt + kWideTiles - 1) / kWideTiles;
     const int npairs = nt * (nt + 1) / 2;
-    int I, J;
-    int s, grp;
+    int I, J, s, grp;
     split_group(s, grp);
     tile_pair(grp, nb, I, J);
     const bool diag = I == J;
-    const int nst = diag ? kBlkTiles : 2 * kBlkTiles;     // staged tiles
-    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    const bool both = !diag || WEIGHT;   // a diagonal block without weights reads one copy twice
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
     const int64_t k0 = (int64_t)s * kchunk;
     const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
-    // this wave's pairs: local tiles (la, lb) of the staged rows, global pair index, valid flag
-    int la[kBlkPairsPerWave], lb[kBlkPairsPerWave], gp[kBlkPairsPerWave];
-    bool ok[kBlkPairsPerWave];
-    f32x16 acc[kBlkPairsPerWave];
+    const int piece = t % 8, row = t / 8;   // this thread's rows: row + 64 m
+    u32x4v ra[kWidePer], rb[kWidePer];
+    float wt[8];
+    auto load = [&](int64_t kc) {
 #pragma unroll
-    for (int q = 0; q < kBlkPairsPerWave; ++q) {
-        const int idx = w * kBlkPairsPerWave + q;
-        int a, b;
-        if (diag) {
-            tile_pair(idx < kBlkTiles * (kBlkTiles + 1) / 2 ? idx : 0, kBlkTiles, a, b);
-            ok[q] = idx < kBlkTiles * (kBlkTiles + 1) / 2;
-            la[q] = a;
-            lb[q] = b;
-        } else {
-            a = idx / kBlkTiles;
-            b = idx % kBlkTiles;
-            ok[q] = true;
-            la[q] = a;
-            lb[q] = kBlkTiles + b;
+        for (int m = 0; m < kWidePer; ++m) {
+            const int i = I * kWideRows + row + 64 * m, j = J * kWideRows + row + 64 * m;
+            u32x4v va = {0u, 0u, 0u, 0u}, vb = {0u, 0u, 0u, 0u};
+            if (i < p) va = *reinterpret_cast<const u32x4v *>(u + (int64_t)i * ldu + kc + 8 * piece);
+            if (!diag && j < p) vb = *reinterpret_cast<const u32x4v *>(u + (int64_t)j * ldu + kc + 8 * piece);
+            ra[m] = va;
+            rb[m] = vb;
         }
-        const int ti = I * kBlkTiles + a, tj = J * kBlkTiles + b;
-        ok[q] = ok[q] && ti < nt && tj < nt;
-        gp[q] = ok[q] ? pair_index(ti, tj, nt) : 0;
+        if constexpr (WEIGHT) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) wt[i] = (float)c[kc + 8 * piece + i];
+        }
+    };
+    auto stage = [&](int buf) {
+        uint16_t *pa = sh + buf * 2 * kHalf + row * kWideStride + 8 * piece, *pb = pa + kHalf;
+#pragma unroll
+        for (int m = 0; m < kWidePer; ++m) {
+            u32x4v va = ra[m];
+            if constexpr (WEIGHT) {
+                const bf16x8 x = __builtin_bit_cast(bf16x8, va);
+                bf16x8 y;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) y[i] = (__bf16)((float)x[i] * wt[i]);
+                va = __builtin_bit_cast(u32x4v, y);
+            }
+            *reinterpret_cast<u32x4v *>(pa + 64 * m * kWideStride) = va;
+            if (both) *reinterpret_cast<u32x4v *>(pb + 64 * m * kWideStride) = diag ? ra[m] : rb[m];
+        }
+    };
+    f32x16 acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
-    }
-    const int rsub = lane & 31, ksub = 8 * (lane >> 5);
-    const int npieces = nst * kMT * kPieces;
-    u32x4v reg[kPerThread];
-    float creg = 0.0f;
-    auto global_row = [&](int lr) {
-        const int lt = lr / kMT;
-        const int gt = lt < kBlkTiles ? I * kBlkTiles + lt : J * kBlkTiles + (lt - kBlkTiles);
-        return gt * kMT + lr % kMT;
-    };
-    auto load_chunk = [&](int64_t kc) {
+    // a fragment: row tile's row lane % 32, 8 K values from 8 (lane / 32)
+    const int frag = (lane & 31) * kWideStride + 8 * (lane >> 5);
+    int wr, wc;
+    const uint32_t want = wide_region(w, diag, wr, wc);
+    const uint16_t *fa = sh + 2 * wr * kMT * kWideStride + frag;
+    const uint16_t *fb = sh + (both ? kHalf : 0) + 4 * wc * kMT * kWideStride + frag;
+    auto products = [&](int buf) {
+        const uint16_t *A = fa + buf * 2 * kHalf, *B = fb + buf * 2 * kHalf;
+        auto get = [](const uint16_t *src) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4v *>(src)); };
+        if (want == 0u) return;
 #pragma unroll
-        for (int m = 0; m < kPerThread; ++m) {
-            const int e = threadIdx.x + 64 * kSyrkBfWaves * m;
-            const int lr = e / kPieces, piece = e % kPieces;
-            u32x4v v = {0u, 0u, 0u, 0u};
-            if (e < npieces) {
-                const int r = global_row(lr);
-                if (r < p) v = *reinterpret_cast<const u32x4v *>(u + (int64_t)r * ldu + kc + 8 * piece);
-            }
-            reg[m] = v;
+        for (int k = 0; k < kWideKC; k += 16) {
+            bf16x8 a[2], b[4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = get(A + i * kMT * kWideStride + k);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[j] = get(B + j * kMT * kWideStride + k);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (want & (1u << (4 * i + j)))
+                        acc[4 * i + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[4 * i + j], 0, 0, 0);
         }
-        if (WEIGHT && threadIdx.x < KC) creg = (float)c[kc + threadIdx.x];
     };
-    if (k0 < k1) load_chunk(k0);
-    for (int64_t kc = k0; kc < k1; kc += KC) {
-        if (WEIGHT && threadIdx.x < KC) cw[threadIdx.x] = creg;
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < kPerThread; ++m) {
-            const int e = threadIdx.x + 64 * kSyrkBfWaves * m;
-            if (e < npieces) {
-                const int lr = e / kPieces, piece = e % kPieces;
-                *reinterpret_cast<u32x4v *>(plain + lr * kStride + 8 * piece) = reg[m];
-                if (WEIGHT) {
-                    const bf16x8 x = __builtin_bit_cast(bf16x8, reg[m]);
-                    bf16x8 y;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) y[i] = (__bf16)((float)x[i] * cw[8 * piece + i]);
-                    *reinterpret_cast<u32x4v *>(wtd + lr * kStride + 8 * piece) = __builtin_bit_cast(u32x4v, y);
-                }
-            }
+    if (k0 < k1) {
+        load(k0);
+        stage(0);
+        if (k0 + kWideKC < k1) load(k0 + kWideKC);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int64_t kc = k0; kc < k1; kc += kWideKC, buf ^= 1) {
+        products(buf);
+        if (kc + kWideKC < k1) {
+            stage(buf ^ 1);   // last read before the previous barrier
+            if (kc + 2 * kWideKC < k1) load(kc + 2 * kWideKC);
         }
         __syncthreads();
-        if (kc + KC < k1) load_chunk(kc + KC);   // in flight during the MFMAs below
-        const uint16_t *asrc = WEIGHT ? wtd : plain;
-#pragma unroll
-        for (int sub = 0; sub < KC / 16; ++sub) {
-            const int kk = 16 * sub + ksub;
-#pragma unroll
-            for (int q = 0; q < kBlkPairsPerWave; ++q) {
-                if (ok[q]) {
-                    const bf16x8 a = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4v *>(asrc + (la[q] * kMT + rsub) * kStride + kk));
-                    const bf16x8 b = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4v *>(plain + (lb[q] * kMT + rsub) * kStride + kk));
-                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[q], 0, 0, 0);
-                }
-            }
-        }
-        __syncthreads();   // the next chunk rewrites the LDS tiles
     }
+    const int64_t base = (int64_t)s * npairs;
 #pragma unroll
-    for (int q = 0; q < kBlkPairsPerWave; ++q) {
-        if (ok[q]) {
-            float *out = part + ((int64_t)s * npairs + gp[q]) * (kMT * kMT);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 8 * (i / 4) + 4 * (lane / 32) + (i % 4), n = lane % 32;
-                out[m * kMT + n] = acc[q][i];
-            }
-        }
+    for (int q = 0; q < 8; ++q) {
+        const int ti = I * kWideTiles + 2 * wr + q / 4, tj = J * kWideTiles + 4 * wc + q % 4;
+        if ((want & (1u << q)) && ti < nt && tj < nt) store_tile(part, base + pair_index(ti, tj, nt), acc[q], lane);
     }
 }
 
@@ -872,7 +883,7 @@ __global__ __launch_bounds__(64 * kSyrkBfWaves) void syrk_bf16_blk_kernel(const 
 
 constexpr float kFp8Max = 224.0f;   // below the e4m3 maximum of either encoding
 constexpr int kF8KC = 64, kF8Stride = 80;   // bytes per LDS row (64 + 16 pad)
-constexpr int kF8MaxRows = 800;                // p <= 800 (rows = p rounded up to 32)
+constexpr int kF8Rows = 256;                   // most staged rows of the one-pass kernel (p rounded up to 32)
 typedef int i32x8v __attribute__((ext_vector_type(8)));
 
 // The e4m3 copy is stored in blocks of kF8KC rows of X: block k holds, for each
@@ -923,9 +934,8 @@ __global__ __launch_bounds__(256) void wscale_kernel(const double *blockmax, int
 
 // Two waves per SIMD (registers capped at 256, accumulators included): the
 // products of one chunk overlap the other wave's staging.
-// MAXR: the most staged rows (p rounded up to 32) the launch may have; it sizes the prefetch
-// registers.  NWV waves of TPW tile pairs each, registers cut for two workgroups per compute unit.
-template <int MAXR, int NWV = kSyrkBfWaves, int TPW = kTilesPerWave>
+// NWV waves of TPW tile pairs each, registers cut for two workgroups per compute unit.
+template <int NWV = kSyrkBfWaves, int TPW = kTilesPerWave>
 __global__ __launch_bounds__(64 * NWV, NWV / 2) void syrk_fp8_lds_kernel(const uint8_t *u, int p,
                                                                         const double *c, const double *wsc,
                                                                         int64_t K, int64_t kchunk, float *part)
@@ -945,7 +955,7 @@ __global__ __launch_bounds__(64 * NWV, NWV / 2) void syrk_fp8_lds_kernel(const u
     const double invS = 1.0 / wsc[0];
     const int rsub = lane & 31, kofs = 32 * (lane >> 5);
     // LDS byte offsets of this lane's A and B rows for each tile pair, packed 16 bits each
-    // (at most kF8MaxRows rows of kF8Stride bytes: < 2^16)
+    // (at most kF8Rows rows of kF8Stride bytes: < 2^16)
     uint32_t offs[TPW];
     f32x16 acc[TPW];
 #pragma unroll
@@ -960,7 +970,7 @@ __global__ __launch_bounds__(64 * NWV, NWV / 2) void syrk_fp8_lds_kernel(const u
     // the chunk is one contiguous block of rows x 64 bytes (padding rows are zero), read
     // as 16-byte pieces e = tid + 256 m into registers one chunk ahead
     static_assert(NWV * TPW == kPairsPerGroup, "a group holds kPairsPerGroup tile pairs");
-    constexpr int kPieces = (MAXR * 4 + 64 * NWV - 1) / (64 * NWV);
+    constexpr int kPieces = (kF8Rows * 4 + 64 * NWV - 1) / (64 * NWV);
     const int npieces = rows * 4;
     u32x4v reg[kPieces];
     double creg = 0.0;
@@ -1039,131 +1049,139 @@ __global__ __launch_bounds__(64 * NWV, NWV / 2) void syrk_fp8_lds_kernel(const u
     }
 }
 
-// Wide X in FP8 (more than kF8MaxRows rows): blocks of kBlkTiles x kBlkTiles tile pairs as in
-// syrk_bf16_blk_kernel; a workgroup stages only the row tiles of its block (8 tiles x 32 rows
-// x 80 bytes of LDS) with the same decode / weight / re-encode as syrk_fp8_lds_kernel.
-__global__ __launch_bounds__(64 * kSyrkBfWaves) void syrk_fp8_blk_kernel(const uint8_t *u, int p, const double *c,
-                                                                         const double *wsc, int64_t K, int64_t kchunk,
-                                                                         float *part)
+// More than 8 row tiles in FP8: blocks of 8 x 8 tile pairs as in syrk_bf16_wide_kernel.  Per
+// 128-row chunk (two of the copy's 64-row blocks) the rows of block I, and off the diagonal
+// those of block J, are decoded, weighted and re-encoded into LDS -- both operands are the same
+// matrix, so a diagonal block stages 256 rows only.  What bounds it is that conversion
+// (8 vector instructions per 4 bytes, 2560 cycles per chunk and SIMD against 2050 of products):
+// an element is converted once per block that it takes part in, 2 times at p = 500, where
+// groups of 32 tile pairs that staged all rows converted it 5 times (N = 2.5e6: 1.22 -> 0.71 ms).
+constexpr int kF8WideKC = 128, kF8WideStride = kF8WideKC + 16;
+
+__global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_fp8_wide_kernel(const uint8_t *u, int p, const double *c,
+                                                                          const double *wsc, int64_t K,
+                                                                          int64_t kchunk, float *part)
 {
-    constexpr int kRows = 2 * kBlkTiles * kMT;                                   // staged rows
-    constexpr int kPieces = kRows * 4 / (64 * kSyrkBfWaves);                    // 4 per thread
-    __shared__ uint8_t sh8[kRows * kF8Stride];
-    __shared__ float cw[kF8KC];
+    extern __shared__ uint8_t sh8[];   // two buffers of [I rows, J rows][kF8WideStride]
+    __shared__ float cw[2][kF8WideKC];
+    constexpr int kHalf = kWideRows * kF8WideStride;
     const int nt = (p + kMT - 1) / kMT;
     const int rows = nt * kMT;
-    const int nb = (nt + kBlkTiles - 1) / kBlkTiles;
+    const int nb = (nt + kWideTiles - 1) / kWideTiles;
     const int npairs = nt * (nt + 1) / 2;
-    int I, J;
-    int s, grp;
+    int I, J, s, grp;
     split_group(s, grp);
     tile_pair(grp, nb, I, J);
     const bool diag = I == J;
-    const int nst = diag ? kBlkTiles : 2 * kBlkTiles;
-    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t / 64);
     const int64_t k0 = (int64_t)s * kchunk;
     const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
     const double invS = 1.0 / wsc[0];
-    int la[kBlkPairsPerWave], lb[kBlkPairsPerWave], gp[kBlkPairsPerWave];
-    bool ok[kBlkPairsPerWave];
-    f32x16 acc[kBlkPairsPerWave];
+    const int piece = t % 8, row = t / 8;   // this thread's rows: row + 64 m; K values 16 piece ..
+    u32x4v ra[kWidePer], rb[kWidePer];
+    auto load = [&](int64_t kc) {
+        const uint8_t *blk = u + (kc / kF8KC + piece / 4) * (int64_t)rows * kF8KC + 16 * (piece % 4);
+        const bool in = kc + 16 * piece < k1;   // K is a multiple of 64
 #pragma unroll
-    for (int q = 0; q < kBlkPairsPerWave; ++q) {
-        const int idx = w * kBlkPairsPerWave + q;
-        int a, b;
-        if (diag) {
-            ok[q] = idx < kBlkTiles * (kBlkTiles + 1) / 2;
-            tile_pair(ok[q] ? idx : 0, kBlkTiles, a, b);
-            la[q] = a;
-            lb[q] = b;
-        } else {
-            a = idx / kBlkTiles;
-            b = idx % kBlkTiles;
-            ok[q] = true;
-            la[q] = a;
-            lb[q] = kBlkTiles + b;
+        for (int m = 0; m < kWidePer; ++m) {
+            const int i = I * kWideRows + row + 64 * m, j = J * kWideRows + row + 64 * m;
+            u32x4v va = {0u, 0u, 0u, 0u}, vb = {0u, 0u, 0u, 0u};
+            if (in && i < rows) va = *reinterpret_cast<const u32x4v *>(blk + (int64_t)i * kF8KC);
+            if (in && !diag && j < rows) vb = *reinterpret_cast<const u32x4v *>(blk + (int64_t)j * kF8KC);
+            ra[m] = va;
+            rb[m] = vb;
         }
-        const int ti = I * kBlkTiles + a, tj = J * kBlkTiles + b;
-        ok[q] = ok[q] && ti < nt && tj < nt;
-        gp[q] = ok[q] ? pair_index(ti, tj, nt) : 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
-    }
-    const int rsub = lane & 31, kofs = 32 * (lane >> 5);
-    const int npieces = nst * kMT * 4;
-    u32x4v reg[kPieces];
-    double creg = 0.0;
-    auto load_chunk = [&](int64_t kc) {
-        const uint8_t *blk = u + (kc / kF8KC) * (int64_t)rows * kF8KC;
-#pragma unroll
-        for (int m = 0; m < kPieces; ++m) {
-            const int e = threadIdx.x + 64 * kSyrkBfWaves * m;
-            u32x4v v = {0u, 0u, 0u, 0u};
-            if (e < npieces) {
-                const int lr = e >> 2, lt = lr / kMT;
-                const int gt = lt < kBlkTiles ? I * kBlkTiles + lt : J * kBlkTiles + (lt - kBlkTiles);
-                if (gt < nt)
-                    v = *reinterpret_cast<const u32x4v *>(blk + (int64_t)(gt * kMT + lr % kMT) * kF8KC + 16 * (e & 3));
-            }
-            reg[m] = v;
-        }
-        if (threadIdx.x < kF8KC) creg = c[kc + threadIdx.x];
     };
-    if (k0 < k1) load_chunk(k0);
-    for (int64_t kc = k0; kc < k1; kc += kF8KC) {
-        if (threadIdx.x < kF8KC) cw[threadIdx.x] = (float)(sqrt(creg) * invS);
-        __syncthreads();
-        const int piece = threadIdx.x & 3;
+    auto weight = [&](int64_t k) { return k < k1 ? (float)(sqrt(c[k]) * invS) : 0.0f; };
+    auto stage = [&](int buf, const float *cwk) {
+        uint8_t *pa = sh8 + buf * 2 * kHalf + row * kF8WideStride + 16 * piece, *pb = pa + kHalf;
         float wk[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) wk[i] = cw[16 * piece + i];
+        for (int i = 0; i < 16; ++i) wk[i] = cwk[16 * piece + i];
+        auto convert = [&](const u32x4v &raw) {
+            u32x4v v;
 #pragma unroll
-        for (int m = 0; m < kPieces; ++m) {
-            const int e = threadIdx.x + 64 * kSyrkBfWaves * m;
-            if (e < npieces) {
-                const u32x4v raw = reg[m];
-                u32x4v v;
+            for (int d = 0; d < 4; ++d) {
+                const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[d], false);
+                const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[d], true);
+                int o = __builtin_amdgcn_cvt_pk_fp8_f32(lo[0] * wk[4 * d], lo[1] * wk[4 * d + 1], 0, false);
+                o = __builtin_amdgcn_cvt_pk_fp8_f32(hi[0] * wk[4 * d + 2], hi[1] * wk[4 * d + 3], o, true);
+                v[d] = (unsigned)o;
+            }
+            return v;
+        };
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const int word = (int)raw[d];
-                    int o = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_cvt_f32_fp8(word, 0) * wk[4 * d],
-                                                            __builtin_amdgcn_cvt_f32_fp8(word, 1) * wk[4 * d + 1], 0,
-                                                            false);
-                    o = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_cvt_f32_fp8(word, 2) * wk[4 * d + 2],
-                                                        __builtin_amdgcn_cvt_f32_fp8(word, 3) * wk[4 * d + 3], o, true);
-                    v[d] = (unsigned)o;
-                }
-                *reinterpret_cast<u32x4v *>(sh8 + (e >> 2) * kF8Stride + 16 * piece) = v;
+        for (int m = 0; m < kWidePer; ++m) {
+            *reinterpret_cast<u32x4v *>(pa + 64 * m * kF8WideStride) = convert(ra[m]);
+            if (!diag) *reinterpret_cast<u32x4v *>(pb + 64 * m * kF8WideStride) = convert(rb[m]);
+        }
+    };
+    f32x16 acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
+    int wr, wc;
+    const uint32_t want = wide_region(w, diag, wr, wc);
+    const int frag = (lane & 31) * kF8WideStride + 32 * (lane >> 5);
+    const uint8_t *fa = sh8 + 2 * wr * kMT * kF8WideStride + frag;
+    const uint8_t *fb = sh8 + (diag ? 0 : kHalf) + 4 * wc * kMT * kF8WideStride + frag;
+    auto products = [&](int buf) {
+        const uint8_t *A = fa + buf * 2 * kHalf, *B = fb + buf * 2 * kHalf;
+        auto get = [](const uint8_t *src) {
+            const u32x4v x = *reinterpret_cast<const u32x4v *>(src), y = *reinterpret_cast<const u32x4v *>(src + 16);
+            return i32x8v{(int)x[0], (int)x[1], (int)x[2], (int)x[3], (int)y[0], (int)y[1], (int)y[2], (int)y[3]};
+        };
+        if (want == 0u) return;
+#pragma unroll
+        for (int k = 0; k < kF8WideKC; k += kF8KC) {
+            i32x8v a[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = get(A + i * kMT * kF8WideStride + k);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const i32x8v b = get(B + j * kMT * kF8WideStride + k);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (want & (1u << (4 * i + j)))
+                        acc[4 * i + j] =
+                            __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i], b, acc[4 * i + j], 0, 0, 0, 127, 0, 127);
+            }
+        }
+    };
+    // the weights of chunk i + 2 replace those of chunk i once chunk i is staged
+    double cnext = 0.0;
+    if (t < kF8WideKC) {
+        cw[0][t] = weight(k0 + t);
+        cw[1][t] = weight(k0 + kF8WideKC + t);
+        if (k0 + 2 * kF8WideKC + t < k1) cnext = c[k0 + 2 * kF8WideKC + t];
+    }
+    if (k0 < k1) load(k0);
+    __syncthreads();
+    if (k0 < k1) {
+        stage(0, cw[0]);
+        if (k0 + kF8WideKC < k1) load(k0 + kF8WideKC);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int64_t kc = k0; kc < k1; kc += kF8WideKC, buf ^= 1) {
+        products(buf);
+        if (kc + kF8WideKC < k1) {
+            stage(buf ^ 1, cw[buf ^ 1]);   // last read before the previous barrier
+            if (kc + 2 * kF8WideKC < k1) load(kc + 2 * kF8WideKC);
+            if (t < kF8WideKC) {
+                cw[buf][t] = (float)(sqrt(cnext) * invS);
+                cnext = kc + 3 * kF8WideKC + t < k1 ? c[kc + 3 * kF8WideKC + t] : 0.0;
             }
         }
         __syncthreads();
-        if (kc + kF8KC < k1) load_chunk(kc + kF8KC);   // in flight during the products below
-#pragma unroll
-        for (int q = 0; q < kBlkPairsPerWave; ++q) {
-            if (ok[q]) {
-                const uint8_t *pa = sh8 + (la[q] * kMT + rsub) * kF8Stride + kofs;
-                const uint8_t *pb = sh8 + (lb[q] * kMT + rsub) * kF8Stride + kofs;
-                const u32x4v a0 = *reinterpret_cast<const u32x4v *>(pa), a1 = *reinterpret_cast<const u32x4v *>(pa + 16);
-                const u32x4v b0 = *reinterpret_cast<const u32x4v *>(pb), b1 = *reinterpret_cast<const u32x4v *>(pb + 16);
-                const i32x8v av = {(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3],
-                                   (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
-                const i32x8v bv = {(int)b0[0], (int)b0[1], (int)b0[2], (int)b0[3],
-                                   (int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3]};
-                acc[q] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[q], 0, 0, 0, 127, 0, 127);
-            }
-        }
-        __syncthreads();   // the next chunk rewrites the LDS tiles
     }
+    const int64_t base = (int64_t)s * npairs;
 #pragma unroll
-    for (int q = 0; q < kBlkPairsPerWave; ++q) {
-        if (ok[q]) {
-            float *out = part + ((int64_t)s * npairs + gp[q]) * (kMT * kMT);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 8 * (i / 4) + 4 * (lane / 32) + (i % 4), n = lane % 32;
-                out[m * kMT + n] = acc[q][i];
-            }
-        }
+    for (int q = 0; q < 8; ++q) {
+        const int ti = I * kWideTiles + 2 * wr + q / 4, tj = J * kWideTiles + 4 * wc + q % 4;
+        if ((want & (1u << q)) && ti < nt && tj < nt) store_tile(part, base + pair_index(ti, tj, nt), acc[q], lane);
     }
 }
 
@@ -1296,11 +1314,10 @@ int syrk_bf16(const uint16_t *u, int64_t ldu, int p, const float *scale, const d
     if (K16 > ldu) return -1;
     float *fpart = reinterpret_cast<float *>(part);
     const int nt = (p + kMT - 1) / kMT;
-    const int KC = nt <= 8 ? 128 : 64;
-    const int64_t K64 = (K + KC - 1) / KC * KC;
-    if (nt <= 8 && (K + 63) / 64 * 64 <= ldu && ldu % 8 == 0) {
+    const int64_t K64 = (K + 63) / 64 * 64;
+    if (nt <= 8 && K64 <= ldu && ldu % 8 == 0) {
         // two workgroups per compute unit, 64-row chunks (64.5 KB of LDS each with the weighted copy)
-        const int64_t KB = (K + 63) / 64 * 64;
+        const int64_t KB = K64;
         const int s2 = 2 * splits;
         int64_t kchunk = (KB + s2 - 1) / s2;
         kchunk = (kchunk + 63) / 64 * 64;
@@ -1319,62 +1336,26 @@ int syrk_bf16(const uint16_t *u, int64_t ldu, int p, const float *scale, const d
         const dim3 grid(s2, ngroups);
         if (c) syrk_bf16_lds_kernel<true, 64, 8, 4, 8, 4><<<grid, 64 * 8, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
         else syrk_bf16_lds_kernel<false, 64, 8, 4, 8, 4><<<grid, 64 * 8, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-    } else if (nt <= kLdsMaxTiles && K64 <= ldu && ldu % 8 == 0) {
-        int64_t kchunk = (K64 + splits - 1) / splits;
-        kchunk = (kchunk + KC - 1) / KC * KC;
-        const size_t lds = sizeof(uint16_t) * (size_t)nt * kMT * (KC + 8) * (c ? 2 : 1);
-        static bool attr = false;
-        if (!attr) {
-            const size_t most = sizeof(uint16_t) * (size_t)16 * kMT * (64 + 8) * 2;   // the largest of both shapes
-            const void *fns[] = {reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<true, 128>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<false, 128>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<true, 64>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<false, 64>)};
-            for (const void *fn : fns)
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                    return -3;
-            attr = true;
-        }
-        const dim3 grid(splits, ngroups);
-        if (KC == 128) {
-            if (c) syrk_bf16_lds_kernel<true, 128><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-            else syrk_bf16_lds_kernel<false, 128><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-        } else {
-            if (c) syrk_bf16_lds_kernel<true, 64><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-            else syrk_bf16_lds_kernel<false, 64><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-        }
-    } else if (nt > kLdsMaxTiles && ldu % 8 == 0 && (K + 63) / 64 * 64 <= ldu) {
-        // wide X: blocks of tile pairs, each staging only its row blocks
-        const int BKC = (K + 127) / 128 * 128 <= ldu ? 128 : 64;
-        const int64_t KB = (K + BKC - 1) / BKC * BKC;
-        const int nb = (nt + kBlkTiles - 1) / kBlkTiles;
+    } else if (nt > 8 && ldu % 8 == 0 && K64 <= ldu) {
+        const int nb = (nt + kWideTiles - 1) / kWideTiles;
         const int nblocks = nb * (nb + 1) / 2;
         int bsplits = splits;
         if (bsplits * (int64_t)nblocks > 16384) bsplits = 16384 / nblocks > 1 ? 16384 / nblocks : 1;
-        int64_t kchunk = (KB + bsplits - 1) / bsplits;
-        kchunk = (kchunk + BKC - 1) / BKC * BKC;
-        const size_t lds = sizeof(uint16_t) * (size_t)2 * kBlkTiles * kMT * (BKC + 8) * (c ? 2 : 1);
-        static bool battr = false;
-        if (!battr) {
-            const size_t most = sizeof(uint16_t) * (size_t)2 * kBlkTiles * kMT * (128 + 8) * 2;
-            const void *fns[] = {reinterpret_cast<const void *>(&syrk_bf16_blk_kernel<true, 128>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_blk_kernel<false, 128>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_blk_kernel<true, 64>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_blk_kernel<false, 64>)};
+        int64_t kchunk = (K64 + bsplits - 1) / bsplits;
+        kchunk = (kchunk + kWideKC - 1) / kWideKC * kWideKC;
+        const size_t lds = sizeof(uint16_t) * (size_t)4 * kWideRows * kWideStride;
+        static bool wattr = false;
+        if (!wattr) {
+            const void *fns[] = {reinterpret_cast<const void *>(&syrk_bf16_wide_kernel<true>),
+                                 reinterpret_cast<const void *>(&syrk_bf16_wide_kernel<false>)};
             for (const void *fn : fns)
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                    return -3;
-            battr = true;
+                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return -3;
+            wattr = true;
         }
         splits = bsplits;   // the reduce below sums the slices this launch writes
         const dim3 grid(bsplits, nblocks);
-        if (BKC == 128) {
-            if (c) syrk_bf16_blk_kernel<true, 128><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-            else syrk_bf16_blk_kernel<false, 128><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-        } else {
-            if (c) syrk_bf16_blk_kernel<true, 64><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-            else syrk_bf16_blk_kernel<false, 64><<<grid, 64 * kSyrkBfWaves, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-        }
+        if (c) syrk_bf16_wide_kernel<true><<<grid, 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
+        else syrk_bf16_wide_kernel<false><<<grid, 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
     } else {
         int64_t kchunk = (K16 + splits - 1) / splits;
         kchunk = (kchunk + 15) / 16 * 16;
@@ -1409,16 +1390,23 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
     if (K64 > ldu || ldu % kF8KC != 0) return -1;
     bmax_kernel<<<256, 256, 0, stream>>>(c, K, blockmax);
     wscale_kernel<<<1, 256, 0, stream>>>(blockmax, 256, wsc);
-    if (nt * kMT > kF8MaxRows) {
-        // wide X: blocks of tile pairs, each staging only its row blocks
-        const int nb = (nt + kBlkTiles - 1) / kBlkTiles;
+    if (nt * kMT > kF8Rows) {
+        const int nb = (nt + kWideTiles - 1) / kWideTiles;
         const int nblocks = nb * (nb + 1) / 2;
         int bsplits = splits;
         if (bsplits * (int64_t)nblocks > 16384) bsplits = 16384 / nblocks > 1 ? 16384 / nblocks : 1;
         int64_t kchunk = (K64 + bsplits - 1) / bsplits;
-        kchunk = (kchunk + kF8KC - 1) / kF8KC * kF8KC;
+        kchunk = (kchunk + kF8WideKC - 1) / kF8WideKC * kF8WideKC;
+        const size_t lds = (size_t)4 * kWideRows * kF8WideStride;
+        static bool wattr = false;
+        if (!wattr) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(&syrk_fp8_wide_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                return -3;
+            wattr = true;
+        }
         float *fpart = reinterpret_cast<float *>(part);
-        syrk_fp8_blk_kernel<<<dim3(bsplits, nblocks), 64 * kSyrkBfWaves, 0, stream>>>(u, p, c, wsc, K64, kchunk, fpart);
+        syrk_fp8_wide_kernel<<<dim3(bsplits, nblocks), 64 * kWideWaves, lds, stream>>>(u, p, c, wsc, K64, kchunk, fpart);
         syrk_bf16_reduce_kernel<<<dim3(npairs, 16), 64 * kRedWaves, 0, stream>>>(fpart, p, bsplits, scale, sign, accumulate, C,
                                                                      wsc);
         return hipGetLastError() == hipSuccess ? 0 : -3;
@@ -1438,12 +1426,7 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
     kchunk = (kchunk + kF8KC - 1) / kF8KC * kF8KC;
     const size_t lds = (size_t)nt * kMT * kF8Stride;
     float *fpart = reinterpret_cast<float *>(part);
-    if (nt * kMT <= 512)
-        syrk_fp8_lds_kernel<512><<<dim3(splits, ngroups), 64 * kSyrkBfWaves, lds, stream>>>(u, p, c, wsc, K64, kchunk,
-                                                                                          fpart);
-    else
-        syrk_fp8_lds_kernel<kF8MaxRows><<<dim3(splits, ngroups), 64 * kSyrkBfWaves, lds, stream>>>(u, p, c, wsc, K64,
-                                                                                                 kchunk, fpart);
+    syrk_fp8_lds_kernel<><<<dim3(splits, ngroups), 64 * kSyrkBfWaves, lds, stream>>>(u, p, c, wsc, K64, kchunk, fpart);
     syrk_bf16_reduce_kernel<<<dim3(npairs, 16), 64 * kRedWaves, 0, stream>>>(fpart, p, splits, scale, sign, accumulate, C, wsc);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
