@@ -534,93 +534,26 @@ __host__ __device__ __forceinline__ int npairs32(int p)
     return nt * (nt + 1) / 2;
 }
 
-// Fragment of 8 consecutive K values of row `row` (0 beyond p).
-__device__ __forceinline__ bf16x8 load_frag(const uint16_t *u, int64_t ldu, int p, int row, int64_t k)
-{
-    if (row >= p) {
-        bf16x8 z;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
-        return z;
-    }
-    const u32x4v v = *reinterpret_cast<const u32x4v *>(u + (int64_t)row * ldu + k);
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-__device__ __forceinline__ bf16x8 weight_frag(bf16x8 a, const double *c, int64_t k)
-{
-    bf16x8 r;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = (__bf16)((float)a[i] * (float)c[k + i]);
-    return r;
-}
-
-// part[(s * npairs + pair) * 1024 + m * 32 + n] = sum over K range s of
-// c_k u[ti*32+m][k] u[tj*32+n][k] (scaled units).  Grid (S, pair groups).
-__global__ __launch_bounds__(64 * kSyrkBfWaves) void syrk_bf16_kernel(const uint16_t *u, int64_t ldu, int p,
-                                                                      const double *c, int64_t K,
-                                                                      int64_t kchunk, float *part)
-{
-    const int nt = (p + kMT - 1) / kMT;
-    const int npairs = nt * (nt + 1) / 2;
-    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
-    int s, grp;
-    split_group(s, grp);
-    const int pair0 = grp * kPairsPerGroup + w * kTilesPerWave;
-    const int64_t k0 = (int64_t)s * kchunk;
-    const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
-    int ti[kTilesPerWave], tj[kTilesPerWave];
-    f32x16 acc[kTilesPerWave];
-#pragma unroll
-    for (int q = 0; q < kTilesPerWave; ++q) {
-        tile_pair(pair0 + q < npairs ? pair0 + q : 0, nt, ti[q], tj[q]);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
-    }
-    const int nq = npairs - pair0 < kTilesPerWave ? (npairs - pair0 > 0 ? npairs - pair0 : 0) : kTilesPerWave;
-    const int rsub = lane % 32, ksub = 8 * (lane / 32);
-    for (int64_t k = k0; k < k1; k += 16) {
-        const int64_t kk = k + ksub;
-#pragma unroll
-        for (int q = 0; q < kTilesPerWave; ++q) {
-            if (q < nq) {
-                bf16x8 a = load_frag(u, ldu, p, ti[q] * kMT + rsub, kk);
-                if (c) a = weight_frag(a, c, kk);
-                const bf16x8 bv = load_frag(u, ldu, p, tj[q] * kMT + rsub, kk);
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, acc[q], 0, 0, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kTilesPerWave; ++q) {
-        if (q < nq) {
-            float *out = part + ((int64_t)s * npairs + pair0 + q) * (kMT * kMT);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 8 * (i / 4) + 4 * (lane / 32) + (i % 4), n = lane % 32;
-                out[m * kMT + n] = acc[q][i];
-            }
-        }
-    }
-}
-
 // LDS-staged variant for p <= 256 (at most 8 row tiles): per 64-row K chunk
 // the workgroup stages all row tiles of u once (and once more multiplied by
 // the weights, rounded to BF16), then every wave runs its tile pairs' MFMAs
 // from LDS.  The next chunk's global loads are issued into registers before
-// the current chunk's MFMAs.  Same partial layout as syrk_bf16_kernel.
+// the current chunk's MFMAs.  part[(s * npairs + pair) * 1024 + m * 32 + n] = sum over K range s of
+// c_k u[ti*32+m][k] u[tj*32+n][k] (scaled units).  Grid (S, pair groups).
+// BLK: u is [ldu / 8][p][8], a thread's pieces are one K unit of rows 64 apart, not K units of a row.
 
 // MAXT: the most row tiles the launch may have (the LDS holds MAXT x 32 rows); OCC: the waves
 // per SIMD the register budget is cut for (with NWV waves of TPW tile pairs each: two
 // workgroups of 8 waves per compute unit need 4, so one workgroup's loads overlap the
 // other's matrix-core work).
-template <bool WEIGHT, int KC, int MAXT, int OCC, int NWV, int TPW>
+template <bool WEIGHT, bool BLK, int KC, int MAXT, int OCC, int NWV, int TPW>
 __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint16_t *u, int64_t ldu, int p,
                                                                                const double *c, int64_t K,
                                                                                int64_t kchunk, float *part)
 {
     constexpr int kLdsKC = KC, kLdsStride = KC + 8, kLdsPieces = KC / 8;
     static_assert(NWV * TPW == kPairsPerGroup, "a group holds kPairsPerGroup tile pairs");
+    static_assert(!BLK || NWV == kLdsPieces, "a wave stages one K unit of the chunk");
     constexpr int kLdsPerThread = (MAXT * kMT * kLdsPieces + 64 * NWV - 1) / (64 * NWV);
     extern __shared__ uint16_t sh[];   // [nt*32][kLdsStride] plain, then weighted (WEIGHT)
     __shared__ float cw[kLdsKC];
@@ -649,17 +582,18 @@ __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][i] = 0.0f;
     }
-    const int npieces = rows * kLdsPieces;
-    // prefetch registers: this thread's pieces e = tid + 256 m, one chunk ahead
+    // prefetch registers: this thread's pieces, one chunk ahead
     u32x4v reg[kLdsPerThread];
     float creg = 0.0f;
     auto load_chunk = [&](int64_t kc) {
 #pragma unroll
         for (int m = 0; m < kLdsPerThread; ++m) {
             const int e = threadIdx.x + 64 * NWV * m;
-            const int r = e / kLdsPieces, piece = e % kLdsPieces;
+            const int r = BLK ? lane + 64 * m : e / kLdsPieces, piece = BLK ? w : e % kLdsPieces;
             u32x4v v = {0u, 0u, 0u, 0u};
-            if (e < npieces && r < p) v = *reinterpret_cast<const u32x4v *>(u + (int64_t)r * ldu + kc + 8 * piece);
+            if (r < p)
+                v = *reinterpret_cast<const u32x4v *>(BLK ? u + ((kc / 8 + piece) * p + r) * 8
+                                                          : u + (int64_t)r * ldu + kc + 8 * piece);
             reg[m] = v;
         }
         if (WEIGHT && threadIdx.x < kLdsKC) creg = (float)c[kc + threadIdx.x];
@@ -671,8 +605,8 @@ __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint
 #pragma unroll
         for (int m = 0; m < kLdsPerThread; ++m) {
             const int e = threadIdx.x + 64 * NWV * m;
-            if (e < npieces) {
-                const int r = e / kLdsPieces, piece = e % kLdsPieces;
+            const int r = BLK ? lane + 64 * m : e / kLdsPieces, piece = BLK ? w : e % kLdsPieces;
+            if (r < rows) {
                 *reinterpret_cast<u32x4v *>(plain + r * kLdsStride + 8 * piece) = reg[m];
                 if (WEIGHT) {
                     const bf16x8 x = __builtin_bit_cast(bf16x8, reg[m]);
@@ -765,7 +699,7 @@ __device__ __forceinline__ uint32_t wide_region(int w, bool diag, int &wr, int &
     return __builtin_amdgcn_readfirstlane(want);
 }
 
-template <bool WEIGHT>
+template <bool WEIGHT, bool BLK>
 __global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_bf16_wide_kernel(const uint16_t *u, int64_t ldu, int p,
                                                                            const double *c, int64_t K, int64_t kchunk,
                                                                            float *part)
@@ -784,7 +718,8 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_bf16_wide_kernel(cons
     const int w = __builtin_amdgcn_readfirstlane(t / 64);
     const int64_t k0 = (int64_t)s * kchunk;
     const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
-    const int piece = t % 8, row = t / 8;   // this thread's rows: row + 64 m
+    // this thread's rows: row + 64 m (BLK: u is [ldu / 8][p][8], consecutive rows of a K unit lie together)
+    const int piece = BLK ? w : t % 8, row = BLK ? lane : t / 8;
     u32x4v ra[kWidePer], rb[kWidePer];
     float wt[8];
     auto load = [&](int64_t kc) {
@@ -792,8 +727,12 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_bf16_wide_kernel(cons
         for (int m = 0; m < kWidePer; ++m) {
             const int i = I * kWideRows + row + 64 * m, j = J * kWideRows + row + 64 * m;
             u32x4v va = {0u, 0u, 0u, 0u}, vb = {0u, 0u, 0u, 0u};
-            if (i < p) va = *reinterpret_cast<const u32x4v *>(u + (int64_t)i * ldu + kc + 8 * piece);
-            if (!diag && j < p) vb = *reinterpret_cast<const u32x4v *>(u + (int64_t)j * ldu + kc + 8 * piece);
+            auto at = [&](int r) {
+                return reinterpret_cast<const u32x4v *>(BLK ? u + ((kc / 8 + piece) * p + r) * 8
+                                                            : u + (int64_t)r * ldu + kc + 8 * piece);
+            };
+            if (i < p) va = *at(i);
+            if (!diag && j < p) vb = *at(j);
             ra[m] = va;
             rb[m] = vb;
         }
@@ -1304,65 +1243,57 @@ int make_bf16_copy(const double *x, int64_t ld, int p, void *xlp, float *xscale,
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
-int syrk_bf16(const uint16_t *u, int64_t ldu, int p, const float *scale, const double *c, int64_t K, int splits,
-              double *part, double sign, int accumulate, double *C, hipStream_t stream)
+namespace {
+
+template <bool WEIGHT, bool BLK>
+int launch_syrk_bf16(const uint16_t *u, int64_t ldu, int p, const double *c, int64_t K64, int *splits, float *part,
+                     hipStream_t stream)
 {
-    if (ldu % 16 != 0) return -1;
-    const int npairs = npairs32(p);
-    const int ngroups = (npairs + kPairsPerGroup - 1) / kPairsPerGroup;
-    const int64_t K16 = (K + 15) / 16 * 16;          // entries K..K16-1 are zero (padding)
-    if (K16 > ldu) return -1;
-    float *fpart = reinterpret_cast<float *>(part);
     const int nt = (p + kMT - 1) / kMT;
-    const int64_t K64 = (K + 63) / 64 * 64;
-    if (nt <= 8 && K64 <= ldu && ldu % 8 == 0) {
+    if (nt <= 8) {
         // two workgroups per compute unit, 64-row chunks (64.5 KB of LDS each with the weighted copy)
-        const int64_t KB = K64;
-        const int s2 = 2 * splits;
-        int64_t kchunk = (KB + s2 - 1) / s2;
+        const int ngroups = (npairs32(p) + kPairsPerGroup - 1) / kPairsPerGroup;
+        *splits *= 2;
+        int64_t kchunk = (K64 + *splits - 1) / *splits;
         kchunk = (kchunk + 63) / 64 * 64;
-        const size_t lds = sizeof(uint16_t) * (size_t)nt * kMT * (64 + 8) * (c ? 2 : 1);
-        static bool attr2 = false;
-        if (!attr2) {
-            const size_t most = sizeof(uint16_t) * (size_t)8 * kMT * (64 + 8) * 2;
-            const void *fns[] = {reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<true, 64, 8, 4, 8, 4>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_lds_kernel<false, 64, 8, 4, 8, 4>)};
-            for (const void *fn : fns)
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                    return -3;
-            attr2 = true;
-        }
-        splits = s2;   // the reduce below sums the slices this launch writes
-        const dim3 grid(s2, ngroups);
-        if (c) syrk_bf16_lds_kernel<true, 64, 8, 4, 8, 4><<<grid, 64 * 8, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-        else syrk_bf16_lds_kernel<false, 64, 8, 4, 8, 4><<<grid, 64 * 8, lds, stream>>>(u, ldu, p, c, KB, kchunk, fpart);
-    } else if (nt > 8 && ldu % 8 == 0 && K64 <= ldu) {
+        constexpr size_t per_tile = sizeof(uint16_t) * kMT * (64 + 8) * (WEIGHT ? 2 : 1);
+        auto *fn = &syrk_bf16_lds_kernel<WEIGHT, BLK, 64, 8, 4, 8, 4>;
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)(8 * per_tile));
+        if (attr != hipSuccess) return -3;
+        fn<<<dim3(*splits, ngroups), 64 * 8, nt * per_tile, stream>>>(u, ldu, p, c, K64, kchunk, part);
+    } else {
         const int nb = (nt + kWideTiles - 1) / kWideTiles;
         const int nblocks = nb * (nb + 1) / 2;
-        int bsplits = splits;
-        if (bsplits * (int64_t)nblocks > 16384) bsplits = 16384 / nblocks > 1 ? 16384 / nblocks : 1;
-        int64_t kchunk = (K64 + bsplits - 1) / bsplits;
+        if (*splits * (int64_t)nblocks > 16384) *splits = 16384 / nblocks > 1 ? 16384 / nblocks : 1;
+        int64_t kchunk = (K64 + *splits - 1) / *splits;
         kchunk = (kchunk + kWideKC - 1) / kWideKC * kWideKC;
-        const size_t lds = sizeof(uint16_t) * (size_t)4 * kWideRows * kWideStride;
-        static bool wattr = false;
-        if (!wattr) {
-            const void *fns[] = {reinterpret_cast<const void *>(&syrk_bf16_wide_kernel<true>),
-                                 reinterpret_cast<const void *>(&syrk_bf16_wide_kernel<false>)};
-            for (const void *fn : fns)
-                if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return -3;
-            wattr = true;
-        }
-        splits = bsplits;   // the reduce below sums the slices this launch writes
-        const dim3 grid(bsplits, nblocks);
-        if (c) syrk_bf16_wide_kernel<true><<<grid, 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-        else syrk_bf16_wide_kernel<false><<<grid, 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, fpart);
-    } else {
-        int64_t kchunk = (K16 + splits - 1) / splits;
-        kchunk = (kchunk + 15) / 16 * 16;
-        syrk_bf16_kernel<<<dim3(splits, ngroups), 64 * kSyrkBfWaves, 0, stream>>>(u, ldu, p, c, K16, kchunk, fpart);
+        constexpr size_t lds = sizeof(uint16_t) * (size_t)4 * kWideRows * kWideStride;
+        auto *fn = &syrk_bf16_wide_kernel<WEIGHT, BLK>;
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (attr != hipSuccess) return -3;
+        fn<<<dim3(*splits, nblocks), 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, part);
     }
-    syrk_bf16_reduce_kernel<<<dim3(npairs, 16), 64 * kRedWaves, 0, stream>>>(fpart, p, splits, scale, sign, accumulate, C,
-                                                                 nullptr);
+    return 0;
+}
+
+}  // namespace
+
+int syrk_bf16(const uint16_t *u, int64_t ldu, int p, bool blocked, const float *scale, const double *c, int64_t K,
+              int splits, double *part, double sign, int accumulate, double *C, hipStream_t stream)
+{
+    const int64_t K64 = (K + 63) / 64 * 64;   // entries K..K64-1 are zero (padding)
+    if (ldu % 64 != 0 || K64 > ldu || (blocked && c)) return -1;
+    float *fpart = reinterpret_cast<float *>(part);
+    int rc;
+    if (c) rc = launch_syrk_bf16<true, false>(u, ldu, p, c, K64, &splits, fpart, stream);
+    else if (blocked) rc = launch_syrk_bf16<false, true>(u, ldu, p, c, K64, &splits, fpart, stream);
+    else rc = launch_syrk_bf16<false, false>(u, ldu, p, c, K64, &splits, fpart, stream);
+    if (rc != 0) return rc;
+    // sums the slices that the launch wrote
+    syrk_bf16_reduce_kernel<<<dim3(npairs32(p), 16), 64 * kRedWaves, 0, stream>>>(fpart, p, splits, scale, sign,
+                                                                                 accumulate, C, nullptr);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

@@ -8,6 +8,7 @@
 
 #include "coxmi.h"
 #include "internal.h"
+#include "newton.h"
 
 // Device buffers of the full-evaluation / Newton path, allocated on first use.
 struct NewtonState {
@@ -17,6 +18,8 @@ struct NewtonState {
     int ntiles = 0, n_agg = 0;
     int64_t n_groups = 0, ldz = 0;
     int32_t *gidx = nullptr;       // [ld]
+    coxmi::EvalSeg *seg = nullptr; // [nseg] runs of whole strata (0: some stratum is too long, or Efron)
+    int nseg = 0, seg_rows = 0;
     double *rows = nullptr;        // 9 x [ld]: eta, u, s0', h', R, alpha, b, zq, m
     double *blockbuf = nullptr;    // [max_blocks]
     uint8_t *tile_carry = nullptr; // [ntiles]

@@ -9,13 +9,25 @@
 
 namespace coxmi {
 
-// Columns of the FP8 contraction (up to 800 every workgroup stages all p rows, beyond that
+// Columns of the FP8 contraction (up to 256 every workgroup stages all p rows, beyond that
 // blocks of tile pairs stage only their own rows): the Newton path's limit.
 constexpr int64_t kMaxFp8P = 4096;
 
 // ------------------------------------------------------------------ full evaluation (newton.hip)
 
 enum ZType { kZF64 = 0, kZF32 = 1, kZBF16 = 2 };
+
+// A run of whole strata for one workgroup: device rows row0 .. row0 + n - 1; g0: index of its first
+// event group (the groups of a run are consecutive).
+struct EvalSeg {
+    int32_t row0, n, g0;
+};
+// True when segments can serve p columns, strata of up to `longest` rows, X of ld and Z of ldz rows.
+bool segments_fit(int p, int64_t longest, int64_t ld, int64_t ldz);
+// Most rows of a segment for n rows and p columns (at least `longest`).
+int segment_rows(int64_t n, int p, int64_t longest);
+// Partial records per column that nseg segments write to colpart.
+int seg_part_slots(int p, int nseg);
 
 // Buffers and sizes of one full evaluation (device pointers).
 struct FullEvalArgs {
@@ -46,9 +58,14 @@ struct FullEvalArgs {
     double *scal = nullptr;           // [0] shift c, [1] objective
     unsigned *flags = nullptr;        // bit 0: a risk-set sum left the FP64 normal range
     int ztype = kZF64;
-    void *z = nullptr;                // [p][ldz] sqrt(d_g) xbar_g / zscale_j, event groups in order
+    // sqrt(d_g) xbar_g / zscale_j, event groups in order: [p][ldz], or with segments and BF16
+    // [ldz / 8][p][8] (8 consecutive groups of a column, the contraction's 16-byte unit)
+    void *z = nullptr;
     int64_t ldz = 0;
     const float *zscale = nullptr;    // [p] power-of-two column scales (NULL for FP64)
+    const EvalSeg *seg = nullptr;     // [nseg] segments; then only b (and m, lam with want_rows) of the row vectors is written
+    int nseg = 0, seg_rows = 0;       // segments, their most rows; 0: tiles as below
+    bool want_rows = false;           // m and lam are read afterwards
     bool want_xbar = true;            // form xbar, Z and the second diagonal part
     void *scan_scratch = nullptr;     // sync scratch of the row scans
     size_t scan_scratch_bytes = 0;
@@ -92,9 +109,10 @@ int syrk_f64(const double *u, int64_t ldu, int p, const double *c, int64_t K, in
 int make_bf16_copy(const double *x, int64_t ld, int p, void *xlp, float *xscale, float *zscale, hipStream_t stream);
 // C (+)= sign * scale_i scale_j sum_k c_k u_ik u_jk with BF16 u on the matrix cores (FP32 accumulate).
 // `part` must hold syrk_bf16_partial_bytes(p, 2 * splits): up to 256 columns the K range is cut
-// into 2 * splits slices (two workgroups per compute unit).
-int syrk_bf16(const uint16_t *u, int64_t ldu, int p, const float *scale, const double *c, int64_t K, int splits,
-              double *part, double sign, int accumulate, double *C, hipStream_t stream);
+// into 2 * splits slices (two workgroups per compute unit).  blocked (c must be NULL): u is
+// [ldu / 8][p][8] instead of [p][ldu].  ldu: a multiple of 64.
+int syrk_bf16(const uint16_t *u, int64_t ldu, int p, bool blocked, const float *scale, const double *c, int64_t K,
+              int splits, double *part, double sign, int accumulate, double *C, hipStream_t stream);
 // Bytes of the blocked e4m3 copy of an ld x p matrix (make_fp8_copy, syrk_fp8).
 size_t fp8_copy_bytes(int64_t ld, int p);
 // e4m3 copy of X with power-of-two column scales (|x / s| <= 224), in blocks of 64 rows

@@ -28,6 +28,7 @@
 #include <hip/hip_bf16.h>
 #include <math.h>
 
+#include <mutex>
 #include <type_traits>
 
 #include "internal.h"
@@ -741,9 +742,398 @@ int tile_scan(Ld ldr, Wr wr, int64_t n, int64_t tile, void *scratch, size_t scra
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+// ------------------------------------------------------------------ strata that fit a workgroup
+//
+// When every stratum has at most kSegRows rows, one workgroup evaluates whole strata at a time
+// (a segment: consecutive strata of up to R rows) and nothing crosses workgroups: X beta of the
+// segment's rows, the row scans, and the column sums, in one launch instead of about twenty.
+//
+//   1. X beta: a thread per row and column part, 8 columns in flight; the columns with beta_j != 0.
+//   2. Row scans over the segment in registers and LDS (as the row-scan kernels below, one row
+//      per thread).
+//   3. Column sums: a wave takes 64 columns, a column per lane, and walks down the rows, so S1' is
+//      a plain recurrence in a register and the three sums need no lane reductions (a wave of 64
+//      rows per column spends four times the instructions on scan steps and reductions).  X comes in
+//      8 rows at a time, two chunks ahead, coalesced along the rows, and turns through a wave-private LDS tile; the
+//      row's factors are LDS broadcasts; xbar of the chunk's group ends goes back through the
+//      tile and out along the groups.  With up to 512 columns spare waves take the segment's
+//      strata in parts.
+// X is read twice, at 5.3 TB/s (score only, N = 1e6, P = 200: 0.62 ms; X beta, three tiled row scans and the
+// column pass took 0.71; with xbar in BF16 0.83 against 0.90; P = 500, N = 2.5e6: 4.4 against 5.1).
+// Small data sets gain most, by the launches: N = 2e4, P = 20: 28 us against 53; N = 5e4, P = 300:
+// 58 us against 156.
+constexpr int kSegRows = 512, kSegThreads = 512, kSegWaves = kSegThreads / kWave;
+constexpr int kSegChunk = 8, kSegTile = kSegChunk + 1;    // rows per chunk; padded LDS stride
+constexpr int kSegGrid = 2 * kMaxGroups;                 // two workgroups per compute unit
+
+__host__ __device__ __forceinline__ int seg_groups(int p) { return (p + kWave - 1) / kWave; }
+__host__ __device__ __forceinline__ int seg_parts(int p)
+{
+    const int g = seg_groups(p);
+    return g >= kSegWaves ? 1 : kSegWaves / g;
+}
+
+// Orders a wave's own LDS accesses across its lanes (they execute in order; this is for the compiler).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+size_t seg_lds_bytes(int p, int rows)
+{
+    return sizeof(double) * ((size_t)kSegWaves * kWave * kSegTile + 4 * ((size_t)rows + kSegChunk) +
+                             3 * (size_t)seg_groups(p) * kWave * seg_parts(p) + (size_t)p) +
+           sizeof(int) * (size_t)p;
+}
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <typename ZT, bool XBAR>
+__global__ __launch_bounds__(kSegThreads, 4) void strata_eval_kernel(const double *x, int64_t ld, int p,
+                                                                  const double *beta, const uint32_t *meta,
+                                                                  const EvalSeg *seg, int nseg, int wpp, double *bout,
+                                                                  double *mout, double *rout, ZT *z, int64_t ldz,
+                                                                  const float *zscale, double *part, double *blockobj,
+                                                                  unsigned *flags)
+{
+    extern __shared__ double sm[];
+    const int groups = seg_groups(p), parts = seg_parts(p);
+    double *tiles = sm;                                                  // [waves][64][kSegTile]; scratch of phases 1, 2
+    double2 *reca = reinterpret_cast<double2 *>(tiles + kSegWaves * kWave * kSegTile);   // alpha (0 at a head), u
+    const int nrec = wpp * kWave + kSegChunk;
+    double2 *recb = reca + nrec;                                         // b, zq
+    double *acc = reinterpret_cast<double *>(recb + nrec);               // [groups * parts][3][64]
+    double *bval = acc + 3 * groups * kWave * parts;                     // the nonzero beta_j
+    int *bcol = reinterpret_cast<int *>(bval + p);
+    __shared__ MaxE wm[kSegWaves];
+    __shared__ AffE wf[kSegWaves], wb[kSegWaves];
+    __shared__ unsigned long long headm[kSegWaves + 1], endm[kSegWaves + 1], evm[kSegWaves + 1];
+    __shared__ double red[kSegWaves];
+    __shared__ int s_nz;
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+
+    for (int i = t; i < 3 * groups * kWave * parts; i += kSegThreads) acc[i] = 0.0;
+    if (t < kSegChunk) {
+        reca[wpp * kWave + t] = double2{0.0, 0.0};
+        recb[wpp * kWave + t] = double2{0.0, 0.0};
+    }
+    if (t == 0) headm[kSegWaves] = endm[kSegWaves] = evm[kSegWaves] = 0ull;
+    if (w == 0) {
+        // the columns with beta_j != 0, in order
+        int n = 0;
+        for (int j0 = 0; j0 < p; j0 += kWave) {
+            const double bj = j0 + lane < p ? beta[j0 + lane] : 0.0;
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(bj != 0.0);
+            if (bj != 0.0) {
+                const int at = n + __popcll(mask & ((1ull << lane) - 1ull));
+                bval[at] = bj;
+                bcol[at] = j0 + lane;
+            }
+            n += __popcll(mask);
+        }
+        if (lane == 0) s_nz = n;
+    }
+    __syncthreads();
+    const int nz = __builtin_amdgcn_readfirstlane(s_nz);
+    const int np = kSegWaves / wpp;   // column parts of phase 1
+    double obj = 0.0;
+
+    for (int si = blockIdx.x; si < nseg; si += gridDim.x) {
+        const int64_t row0 = __builtin_amdgcn_readfirstlane(seg[si].row0);
+        const int n = __builtin_amdgcn_readfirstlane(seg[si].n), g0 = __builtin_amdgcn_readfirstlane(seg[si].g0);
+        // ---- 1. X beta
+        {
+            const int q = w / wpp, r = (w % wpp) * kWave + lane;
+            double e = 0.0;
+            if (q < np && r < n) {
+                const double *xr = x + row0 + r;
+                const int k0 = (int)((int64_t)nz * q / np), k1 = (int)((int64_t)nz * (q + 1) / np);
+                int k = k0;
+                for (; k + 8 <= k1; k += 8) {
+                    double v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = xr[(int64_t)__builtin_amdgcn_readfirstlane(bcol[k + i]) * ld];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) e = fma(v[i], bval[k + i], e);
+                }
+                for (; k < k1; ++k) e = fma(xr[(int64_t)__builtin_amdgcn_readfirstlane(bcol[k]) * ld], bval[k], e);
+            }
+            if (q < np) tiles[q * wpp * kWave + r] = e;
+        }
+        const bool in = t < n;
+        const uint32_t mw = in ? meta[row0 + t] : kHeadBit;
+        __syncthreads();
+        // ---- 2. row scans
+        {
+            double e = 0.0;
+            if (in)
+                for (int q = 0; q < np; ++q) e += tiles[q * wpp * kWave + t];
+            const uint32_t head = mw >> 31;
+            const unsigned long long hm = __builtin_amdgcn_ballot_w64(in && head), em = __builtin_amdgcn_ballot_w64(in && (mw & kCountMask)),
+                                     vm = __builtin_amdgcn_ballot_w64(in && (mw & kEventBit));
+            if (lane == 0) {
+                headm[w] = hm;
+                endm[w] = em;
+                evm[w] = vm;
+            }
+            MaxE mt;
+            const MaxE me = {head, e};
+            const MaxE mx = block_exclusive_e<MaxOp, kSegWaves>(me, wm, mt);
+            const double m = MaxOp::combine(mx, me).m;
+            const double alpha = head ? 1.0 : exp(mx.m - m), u = exp(e - m);
+            AffE at;
+            const AffE ae = {head, alpha, u};
+            const double s0 = AffOp::combine(block_exclusive_e<AffOp, kSegWaves>(ae, wf, at), ae).b;
+            const uint32_t d = mw & kCountMask;
+            double hv = 0.0, zq = 0.0;
+            if (d != 0u) {
+                if (!(s0 >= 0.5) || !(s0 <= 1e300)) atomicOr(flags, 1u);
+                hv = (double)d / s0;
+                zq = hv / sqrt((double)d);
+                obj += (double)d * (log(s0) + m);
+            }
+            if (mw & kEventBit) obj -= e;
+            // reverse: thread t takes row n - 1 - t (every thread has passed the two scans' barriers, so
+            // the sums of phase 1 are read)
+            double *sh = tiles + kSegRows, *sa = tiles + 2 * kSegRows, *sr = tiles + 3 * kSegRows;
+            if (in) {
+                sh[t] = hv;
+                sa[t] = alpha;
+            }
+            __syncthreads();
+            const int r = n - 1 - t;
+            AffE re = AffOp::id();
+            if (r >= 0) {
+                const bool start = r == n - 1 || ((headm[(r + 1) / kWave] >> ((r + 1) % kWave)) & 1ull);
+                re = AffE{start ? 1u : 0u, start ? 1.0 : sa[r + 1], sh[r]};
+            }
+            AffE rt;
+            const double R = AffOp::combine(block_exclusive_e<AffOp, kSegWaves>(re, wb, rt), re).b;
+            if (r >= 0) sr[r] = R;
+            __syncthreads();
+            double b = 0.0;
+            if (in) {
+                b = u * sr[t];
+                bout[row0 + t] = b;
+                if (mout) {
+                    mout[row0 + t] = m;
+                    rout[row0 + t] = sr[t];
+                }
+            }
+            if (t < wpp * kWave) {
+                reca[t] = in ? double2{head ? 0.0 : alpha, u} : double2{0.0, 0.0};
+                recb[t] = double2{b, zq};
+            }
+        }
+        __syncthreads();
+        // ---- 3. column sums
+        auto bits = [&](const unsigned long long *mask, int r) {   // the 64 rows from r
+            const int word = r / kWave, sft = r % kWave;
+            const unsigned long long lo = mask[word] >> sft;
+            return sft ? lo | (mask[word + 1 <= kSegWaves ? word + 1 : kSegWaves] << (kWave - sft)) : lo;
+        };
+        auto head_at = [&](int r) {   // the first head at or after row r, or n
+            while (r < n) {
+                const unsigned long long hm = bits(headm, r);
+                if (hm) {
+                    r += __builtin_ctzll(hm);
+                    break;
+                }
+                r += kWave;
+            }
+            return r < n ? r : n;
+        };
+        for (int item = w; item < groups * parts; item += kSegWaves) {
+            const int gi = item % groups, pi = item / groups;
+            const int rs = __builtin_amdgcn_readfirstlane(pi == 0 ? 0 : head_at(n * pi / parts));
+            const int re = __builtin_amdgcn_readfirstlane(pi == parts - 1 ? n : head_at(n * (pi + 1) / parts));
+            if (rs >= re) continue;
+            const int j0 = gi * kWave;
+            int g = g0;   // the next group's index
+            if (XBAR && rs > 0) {
+                for (int k = 0; k < rs / kWave; ++k) g += __popcll(endm[k]);
+                if (rs % kWave) g += __popcll(endm[rs / kWave] & ((1ull << (rs % kWave)) - 1ull));
+                g = __builtin_amdgcn_readfirstlane(g);
+            }
+            double *tile = tiles + w * kWave * kSegTile;
+            // loads: lane covers row lane % 8 of columns j0 + lane / 8 + 8 i (columns and rows beyond the
+            // end are clamped, so that no load is conditional); sums: column j0 + lane
+            const int lr = lane % kSegChunk, lc = lane / kSegChunk;
+            uint32_t cl[kSegChunk];   // bytes from column j0 + 8 i (uniform) to this lane's
+#pragma unroll
+            for (int i = 0; i < kSegChunk; ++i) {
+                const int most = p - 1 - (j0 + 8 * i);
+                cl[i] = (uint32_t)(most <= 0 ? 0 : (lc < most ? lc : most)) * (uint32_t)ld * 8u;
+            }
+            const char *xg = reinterpret_cast<const char *>(x + (int64_t)j0 * ld + row0);
+            auto load = [&](double (&v)[kSegChunk], int r) {
+                const uint32_t at = (uint32_t)(r + lr < re ? r + lr : re - 1) * 8u;
+#pragma unroll
+                for (int i = 0; i < kSegChunk; ++i) {
+                    const int ji = j0 + 8 * i < p ? 8 * i : p - 1 - j0;   // uniform
+                    v[i] = *reinterpret_cast<const double *>(xg + (int64_t)ji * ld * 8 + (cl[i] + at));
+                }
+            };
+            const float inv = (XBAR && zscale && j0 + lane < p) ? 1.0f / zscale[j0 + lane] : 1.0f;
+            // Z as a buffer: stores beyond it are dropped, so none is conditional either (a conditional
+            // store makes the next wait for X a wait for all stores).  FP64: these columns' [64][ldz].
+            // BF16: blocks of 8 groups, [block][p][8] from the part's first block (see newton.h), so a
+            // lane's 8 values are one 16-byte store and the wave's are contiguous; [p][ldz] here
+            // meant runs of 16 bytes per column and line, written again and again (1.1 ms
+            // instead of 0.6 at N = 1e6, P = 200).
+            constexpr bool kBlocked = !std::is_same<ZT, double>::value;
+            const int cols = p - j0 < kWave ? p - j0 : kWave;
+            const int gfirst = g;
+            __amdgpu_buffer_rsrc_t zbuf;
+            if constexpr (kBlocked)
+                zbuf = __builtin_amdgcn_make_buffer_rsrc(z + (int64_t)(gfirst / 8) * p * 8, (short)0,
+                                                         (kSegRows / 8 + 1) * p * 16, kBufferWord3);
+            else
+                zbuf = __builtin_amdgcn_make_buffer_rsrc(XBAR ? z + (int64_t)j0 * ldz : z, (short)0,
+                                                         XBAR ? (int)((uint32_t)cols * (uint32_t)ldz * 8u) : 0, kBufferWord3);
+            const uint32_t zlane = lane < cols ? (uint32_t)(j0 + lane) * 16u : 0xfffffff0u;   // BF16: this lane's column
+            u32x4 zreg = {0u, 0u, 0u, 0u}, zfull = {0u, 0u, 0u, 0u};   // the last 8 values; a completed block
+            auto push = [&](uint32_t h) {
+                zreg.x = __builtin_amdgcn_alignbit(zreg.y, zreg.x, 16);
+                zreg.y = __builtin_amdgcn_alignbit(zreg.z, zreg.y, 16);
+                zreg.z = __builtin_amdgcn_alignbit(zreg.w, zreg.z, 16);
+                zreg.w = __builtin_amdgcn_alignbit(h, zreg.w, 16);
+            };
+            auto store_slots = [&](const u32x4 &v, int block, int q0, int q1) {   // an incomplete block
+                for (int q = q0; q < q1; ++q) {
+                    const uint32_t word = q < 4 ? (q < 2 ? v.x : v.y) : (q < 6 ? v.z : v.w);
+                    const uint32_t off = zlane == 0xfffffff0u ? zlane : (uint32_t)block * (uint32_t)p * 16u + zlane + 2u * q;
+                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(q & 1 ? word >> 16 : word), zbuf, (int)off, 0, 0);
+                }
+            };
+            double sg = 0.0, s1 = 0.0, s2 = 0.0, run = 0.0;
+            double xa[kSegChunk], xb[kSegChunk];
+            auto chunk = [&](double (&xr)[kSegChunk], int r) {
+                const int left = re - r < kSegChunk ? re - r : kSegChunk;
+                if (left < kSegChunk) {
+#pragma unroll
+                    for (int i = 0; i < kSegChunk; ++i) xr[i] = lr < left ? xr[i] : 0.0;
+                }
+#pragma unroll
+                for (int i = 0; i < kSegChunk; ++i) tile[(lc + 8 * i) * kSegTile + lr] = xr[i];
+                if (r + 2 * kSegChunk < re) load(xr, r + 2 * kSegChunk);
+                wave_sync();
+                const uint32_t live = (1u << left) - 1u;
+                const uint32_t ends = __builtin_amdgcn_readfirstlane((uint32_t)bits(endm, r) & live);
+                const uint32_t evs = __builtin_amdgcn_readfirstlane((uint32_t)bits(evm, r) & live);
+                int k = 0;
+                double *col = tile + lane * kSegTile;
+#pragma unroll
+                for (int i = 0; i < kSegChunk; ++i) {
+                    const double xv = col[i];
+                    const double2 cb = recb[r + i];
+                    const double aw = cb.x - ((evs >> i) & 1u ? 1.0 : 0.0);   // w Lambda - delta
+                    sg = fma(xv, aw, sg);
+                    s1 = fma(xv * xv, cb.x, s1);
+                    if constexpr (XBAR) {
+                        const double2 ca = reca[r + i];
+                        run = fma(ca.x, run, ca.y * xv);
+                        if ((ends >> i) & 1u) {
+                            const double zv = run * cb.y;   // sqrt(d) xbar
+                            s2 = fma(zv, zv, s2);
+                            if constexpr (kBlocked) {
+                                const ZT h = __float2bfloat16((float)zv * inv);
+                                push(__builtin_bit_cast(uint16_t, h));
+                                ++g;
+                                if ((g & 7) == 0) {   // at most once in 8 rows
+                                    zfull = zreg;
+                                    k = g / 8 - gfirst / 8;   // 1 + its block
+                                }
+                            } else {
+                                col[k] = zv;   // slot k <= i of this lane's own row of the tile is already read
+                                ++k;
+                            }
+                        }
+                    }
+                }
+                if constexpr (XBAR && kBlocked) {
+                    if (k == 1 && (gfirst & 7)) {   // the part's first block began in another part
+                        store_slots(zfull, 0, gfirst & 7, 8);
+                        k = 0;
+                    }
+                    const uint32_t off = k == 0 ? 0xfffffff0u : (uint32_t)(k - 1) * (uint32_t)p * 16u + zlane;
+                    __builtin_amdgcn_raw_buffer_store_b128(zfull, zbuf, (int)(zlane == 0xfffffff0u ? zlane : off), 0, 0);
+                } else if constexpr (XBAR) {
+                    wave_sync();
+#pragma unroll
+                    for (int i = 0; i < kSegChunk; ++i) {
+                        const long long slot = __double_as_longlong(tile[(lc + 8 * i) * kSegTile + lr]);
+                        const uint32_t at = ((uint32_t)(lc + 8 * i) * (uint32_t)ldz + (uint32_t)(g + lr)) * 8u;
+                        const u32x2 v = {(uint32_t)slot, (uint32_t)(slot >> 32)};
+                        __builtin_amdgcn_raw_buffer_store_b64(v, zbuf, (int)(lr < k ? at : 0xfffffff0u), 0, 0);
+                    }
+                    g += k;
+                }
+                wave_sync();   // the tile is rewritten by the next chunk
+            };
+            load(xa, rs);
+            if (rs + kSegChunk < re) load(xb, rs + kSegChunk);
+            for (int r = rs; r < re; r += 2 * kSegChunk) {
+                chunk(xa, r);
+                if (r + kSegChunk < re) chunk(xb, r + kSegChunk);
+            }
+            if constexpr (XBAR && kBlocked) {
+                if (g & 7) {
+                    for (int q = g & 7; q < 8; ++q) push(0u);   // the block's values to their slots
+                    store_slots(zreg, g / 8 - gfirst / 8, g / 8 == gfirst / 8 ? gfirst & 7 : 0, g & 7);
+                }
+            }
+            double *o = acc + (size_t)item * 3 * kWave + lane;
+            o[0] += sg;
+            o[kWave] += s1;
+            o[2 * kWave] += s2;
+        }
+        __syncthreads();   // the tiles are the next segment's scratch
+    }
+    for (int i = t; i < groups * parts * kWave; i += kSegThreads) {
+        const int item = i / kWave, c = i % kWave, gi = item % groups, pi = item / groups, j = gi * kWave + c;
+        if (j < p) {
+            double *o = part + (((int64_t)blockIdx.x * parts + pi) * p + j) * 3;
+            const double *v = acc + (size_t)item * 3 * kWave + c;
+            o[0] = v[0];
+            o[1] = v[kWave];
+            o[2] = v[2 * kWave];
+        }
+    }
+    obj = block_sum(obj, red);
+    if (t == 0) blockobj[blockIdx.x] = obj;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ host launchers
+
+constexpr size_t kSegMaxLds = 160 * 1024 - 2048;
+
+// (64 columns of Z, ldz entries of at most 8 bytes each, are addressed by 32-bit offsets)
+// (so are 8 columns of X, ld rows each)
+bool segments_fit(int p, int64_t longest, int64_t ld, int64_t ldz)
+{
+    return ld < (int64_t)1 << 26 && longest <= kSegRows && seg_lds_bytes(p, kSegRows) <= kSegMaxLds && ldz < (int64_t)1 << 23;
+}
+
+// Rows of a segment: a power of two, at least the longest stratum.  Up to 512 rows while that is at
+// most 64K entries of X, else 128 (measured, score only: P = 50, N = 1e6: 402, 261, 186, 180 us at
+// 64 ... 512 rows; P = 200: 643, 602, 610, 684; P = 500, N = 2.5e6: 4.0, 3.3, 3.4, 3.6 ms; P = 1000:
+// 3.1, 2.8, 3.2, 3.0); fewer where the data set would leave compute units idle.
+int segment_rows(int64_t n, int p, int64_t longest)
+{
+    int R = kSegRows;
+    while (R > 2 * kWave && (int64_t)R * p > 65536) R /= 2;
+    while (R > kWave && (int64_t)R * kSegGrid > 2 * n) R /= 2;
+    while (R < longest) R *= 2;
+    return R;
+}
+
+int seg_part_slots(int p, int nseg) { return (nseg < kSegGrid ? nseg : kSegGrid) * seg_parts(p); }
 
 size_t rowscan_scratch_bytes(int ntiles) { return sizeof(AffE) * 2 * (size_t)ntiles + 256; }
 
@@ -754,6 +1144,33 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
     if (nb > A.max_blocks) return -5;
     hipError_t e = hipMemsetAsync(A.flags, 0, sizeof(unsigned), stream);
     if (e != hipSuccess) return -3;
+    if (A.nseg > 0) {
+        const int grid = A.nseg < kSegGrid ? A.nseg : kSegGrid;
+        const int wpp = (A.seg_rows + kWave - 1) / kWave;
+        const size_t lds = seg_lds_bytes(A.p, wpp * kWave);
+        static std::once_flag once;
+        static hipError_t attr = hipSuccess;
+        std::call_once(once, [] {
+            const void *fns[] = {reinterpret_cast<const void *>(&strata_eval_kernel<double, true>),
+                                 reinterpret_cast<const void *>(&strata_eval_kernel<__hip_bfloat16, true>),
+                                 reinterpret_cast<const void *>(&strata_eval_kernel<double, false>)};
+            for (const void *fn : fns)
+                if (attr == hipSuccess)
+                    attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSegMaxLds);
+        });
+        if (attr != hipSuccess) return -3;
+#define COXMI_SEGEVAL(ZT, XB)                                                                                     \
+    strata_eval_kernel<ZT, XB><<<grid, kSegThreads, lds, stream>>>(                                               \
+        A.x, ld, A.p, A.beta, A.meta, A.seg, A.nseg, wpp, A.b, A.want_rows ? A.m : nullptr,                       \
+        A.want_rows ? A.lam : nullptr, static_cast<ZT *>(A.z), A.ldz, A.zscale, A.colpart, A.blockbuf, A.flags)
+        if (!A.want_xbar) COXMI_SEGEVAL(double, false);
+        else if (A.ztype == kZF64) COXMI_SEGEVAL(double, true);
+        else COXMI_SEGEVAL(__hip_bfloat16, true);
+#undef COXMI_SEGEVAL
+        colreduce_kernel<<<A.p + 1, kRowBlock, 0, stream>>>(A.colpart, A.p, grid * seg_parts(A.p), A.grad, A.diag1,
+                                                            A.diag2, A.blockbuf, grid, A.scal);
+        return hipGetLastError() == hipSuccess ? 0 : -3;
+    }
     eta_kernel<<<nb, kRowBlock, 0, stream>>>(A.x, ld, A.p, A.beta, A.eta);
     int rc = tile_scan<MaxOp>(MaxLoad{A.eta, A.meta}, MaxWrite{A.m}, ld, A.tile, A.scan_scratch,
                               A.scan_scratch_bytes, stream);

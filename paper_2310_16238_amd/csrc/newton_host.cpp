@@ -88,7 +88,29 @@ int newton_setup(cox_handle *h)
     s.n_zrows = G + s.n_multi;
     s.eblocks = (int)std::max<int64_t>(1, (s.n_multi + 255) / 256);
     s.ldz = std::max<int64_t>(128, (s.n_zrows + 127) / 128 * 128);   // K chunks of the contraction are 128 rows
-    s.max_blocks = (int)((ld + 255) / 256) + 1;
+    s.max_blocks = std::max((int)((ld + 255) / 256) + 1, 2 * kMaxGroups);
+    // runs of whole strata, when every stratum fits one
+    std::vector<EvalSeg> segs;
+    if (!s.efron) {
+        int64_t longest = 0, len = 0;
+        for (int64_t i = 0; i < n; ++i) {
+            len = (h->meta[i] & kHeadBit) ? 1 : len + 1;
+            longest = std::max(longest, len);
+        }
+        if (segments_fit(p, longest, ld, s.ldz)) {
+            s.seg_rows = segment_rows(n, p, longest);
+            int32_t g = 0;
+            for (int64_t i = 0; i < n;) {
+                int64_t e = i + 1;
+                while (e < n && !(h->meta[e] & kHeadBit)) ++e;
+                const int32_t row0 = (int32_t)h->pos[i], m = (int32_t)(e - i);
+                if (segs.empty() || row0 + m - segs.back().row0 > s.seg_rows) segs.push_back(EvalSeg{row0, 0, g});
+                segs.back().n = row0 + m - segs.back().row0;
+                for (; i < e; ++i) g += (h->meta[i] & kCountMask) ? 1 : 0;
+            }
+        }
+    }
+    s.nseg = (int)segs.size();
     // column-pass tiles: the persistent kernel's tiles (ld = grid * tile)
     s.tile = ld / h->shape.grid;
     s.ntiles = h->shape.grid;
@@ -121,7 +143,9 @@ int newton_setup(cox_handle *h)
         (e = dalloc(&s.agg_tiles, sizeof(int32_t) * std::max(1, s.n_agg))) != hipSuccess ||
         (e = dalloc(&s.agg, sizeof(double) * 2 * (size_t)s.ntiles * p)) != hipSuccess ||
         (e = dalloc(&s.carry, sizeof(double) * (size_t)s.ntiles * p)) != hipSuccess ||
-        (e = dalloc(&s.colpart, sizeof(double) * 3 * (size_t)s.ntiles * p)) != hipSuccess ||
+        (e = dalloc(&s.colpart, sizeof(double) * 3 *
+                                    (size_t)std::max(s.ntiles, s.nseg ? seg_part_slots(p, s.nseg) : 0) * p)) != hipSuccess ||
+        (e = dalloc(&s.seg, sizeof(EvalSeg) * std::max<size_t>(1, segs.size()))) != hipSuccess ||
         (e = dalloc(&s.vec, sizeof(double) * (5 * (size_t)p + kScalSlots))) != hipSuccess ||
         (e = dalloc(&s.flags, sizeof(unsigned))) != hipSuccess ||
         (e = dalloc(&s.status, sizeof(int))) != hipSuccess ||
@@ -148,6 +172,11 @@ int newton_setup(cox_handle *h)
     if (e == hipSuccess && s.n_agg)
         e = hipMemcpy(s.agg_tiles, agg_tiles.data(), sizeof(int32_t) * s.n_agg, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(s.z, 0, zb * (size_t)p * s.ldz);
+    if (e == hipSuccess && s.nseg) {
+        // the segments write the weights of their rows only: padding rows keep 0
+        e = hipMemcpy(s.seg, segs.data(), sizeof(EvalSeg) * segs.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemset(nrow(s, ld, 6), 0, sizeof(double) * ld);
+    }
     if (e == hipSuccess && s.efron) {
         const size_t nme = std::max<size_t>(1, me_row.size()), nm = (size_t)std::max<int64_t>(1, s.n_multi);
         if (e == hipSuccess) e = dalloc(&s.gidx2, sizeof(int32_t) * ld);
@@ -213,7 +242,7 @@ struct EvalOut {
 };
 
 // Full evaluation at beta (host); xbar (and diag2) only when want_xbar.
-int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out)
+int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out, bool want_rows = false)
 {
     NewtonState &s = h->nt;
     const int64_t ld = h->shape.ld;
@@ -262,6 +291,13 @@ int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out)
     A.ldz = s.ldz;
     A.zscale = lowp(h->opt.x_precision) ? s.zscale : nullptr;
     A.want_xbar = want_xbar;
+    A.seg = s.seg;
+    // FP64 Z keeps [p][ldz], whose 64-byte runs per column the segments' waves write at once: beyond
+    // half a gigabyte of X the tiles' longer runs win (N = 1e6, P = 200: 1.02 ms against 1.40; P = 50:
+    // 0.37 against 0.35; without Z, or in BF16, the segments are faster throughout)
+    A.nseg = want_xbar && !lowp(h->opt.x_precision) && (double)h->n * p > 6.4e7 ? 0 : s.nseg;
+    A.seg_rows = s.seg_rows;
+    A.want_rows = want_rows;
     A.scan_scratch = s.scan_scratch;
     A.scan_scratch_bytes = s.scan_scratch_bytes;
     if (s.efron) {
@@ -322,10 +358,10 @@ int newton_info(cox_handle *h)
             rc = syrk_fp8(static_cast<const uint8_t *>(s.xlp), ld, p, s.xscale, b, ld, kSplitsXFP8, s.syrk_part,
                           s.wscratch, s.wscratch + 256, 1.0, 0, s.info, h->stream);
         else
-            rc = syrk_bf16(static_cast<const uint16_t *>(s.xlp), ld, p, s.xscale, b, ld, kSplitsXBF16, s.syrk_part,
+            rc = syrk_bf16(static_cast<const uint16_t *>(s.xlp), ld, p, false, s.xscale, b, ld, kSplitsXBF16, s.syrk_part,
                            1.0, 0, s.info, h->stream);
         if (rc == 0 && s.n_zrows > 0)
-            rc = syrk_bf16(static_cast<const uint16_t *>(s.z), s.ldz, p, s.zscale, nullptr, s.n_zrows, kSplitsZBF16,
+            rc = syrk_bf16(static_cast<const uint16_t *>(s.z), s.ldz, p, s.nseg > 0, s.zscale, nullptr, s.n_zrows, kSplitsZBF16,
                            s.syrk_part, -1.0, 1, s.info, h->stream);
     } else {
         rc = syrk_f64(h->d_x, ld, p, b, ld, kSplitsXF64, s.syrk_part, 1.0, 0, s.info, h->stream);
@@ -343,7 +379,7 @@ int newton_info(cox_handle *h)
 void newton_free(cox_handle *h)
 {
     NewtonState &s = h->nt;
-    void *ptrs[] = {s.gidx, s.rows, s.blockbuf, s.tile_carry, s.lasthead, s.agg_tiles, s.agg, s.carry,
+    void *ptrs[] = {s.gidx, s.seg, s.rows, s.blockbuf, s.tile_carry, s.lasthead, s.agg_tiles, s.agg, s.carry,
                     s.colpart, s.vec, s.flags, s.status, s.free_col, s.z,
                     s.zscale, s.xlp, s.xscale, s.syrk_part, s.info, s.scan_scratch, s.wscratch,
                     s.gidx2, s.gend, s.me_ptr, s.me_row, s.me_end, s.me_w, s.s1me, s.erows, s.epart, s.prox};
@@ -399,7 +435,7 @@ extern "C" int cox_baseline_hazard(cox_handle *h, const double *beta, double *cu
     int rc = newton_setup(h);
     if (rc != COX_OK) return rc;
     EvalOut ev;
-    rc = newton_eval(h, beta, false, ev);
+    rc = newton_eval(h, beta, false, ev, true);
     if (rc != COX_OK) return rc;
     // R_r = Lambda_r exp(m_r) (the reverse scan of the evaluation), m_r the running maximum of X beta
     const int64_t ld = h->shape.ld;
