@@ -1047,19 +1047,39 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
     }
 
     if (b == 0) {
-        // wave 0 holds the bookkeeping; beta is in LDS (written before the last barrier)
-        if (fit)
-            for (int j = t; j < p; j += BLOCK) L.beta[j] = sbeta[j];
+        // wave 0 holds the bookkeeping; beta is in LDS (written before the last barrier), the
+        // derivatives were written by this workgroup's thread 0
+        auto seen = [](const double *v) { return __hip_atomic_load(v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        __threadfence();
+        __syncthreads();
+        for (int j = t; j < p; j += BLOCK) {
+            L.hout[j] = sbeta[j];
+            L.hout[p + j] = seen(L.g1 + j);
+            L.hout[2 * p + j] = seen(L.g2 + j);
+            L.hout[3 * p + j] = seen(L.m2 + j);
+        }
         if (t == 0) {
-            L.result[kResSweeps] = sweeps;
-            L.result[kResLastStep] = last_maxstep;
-            L.result[kResObjective] = objective;
-            L.result[kResPinned] = pinned_last;
-            L.result[kResConverged] = (stop & kFlagConverged) ? 1.0 : 0.0;
-            L.result[kResNumeric] = (stop & kFlagNumeric) ? 1.0 : 0.0;
-            L.result[kResCompleted] = 1.0;
+            double *result = L.hout + 4 * (int64_t)p;
+            result[kResSweeps] = sweeps;
+            result[kResLastStep] = last_maxstep;
+            result[kResObjective] = objective;
+            result[kResPinned] = pinned_last;
+            result[kResConverged] = (stop & kFlagConverged) ? 1.0 : 0.0;
+            result[kResNumeric] = (stop & kFlagNumeric) ? 1.0 : 0.0;
+            result[kResAborted] = abort_raised(ctl) ? 1.0 : 0.0;
+            result[kResCompleted] = 1.0;
         }
     }
+}
+
+// Before the persistent kernel: the synchronisation words cleared, the start point read from
+// host memory once (not by every workgroup).
+__global__ __launch_bounds__(256) void ccd_prepare_kernel(uint32_t *words, int64_t nwords, const double *beta0,
+                                                          double *beta, int p)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < nwords) words[i] = 0u;
+    if (i < p) beta[i] = beta0 ? beta0[i] : 0.0;
 }
 
 // ------------------------------------------------------------------ raw segmented scan
@@ -1218,7 +1238,11 @@ int max_resident_groups(int threads, int ipt, int p, int *groups, std::string &e
 int launch_ccd(const LaunchShape &shape, const CcdLaunch &L, hipStream_t stream, hipEvent_t ev0,
                hipEvent_t ev1)
 {
-    hipError_t e = hipMemsetAsync(L.ctl, 0, sync_scratch_bytes(shape.grid), stream);
+    const int64_t words = (int64_t)(sync_scratch_bytes(shape.grid) / sizeof(uint32_t));
+    const int64_t most = words > L.p ? words : L.p;
+    ccd_prepare_kernel<<<(unsigned)((most + 255) / 256), 256, 0, stream>>>(static_cast<uint32_t *>(L.ctl), words, L.beta0,
+                                                                          L.beta, L.p);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return (int)e;
     CcdLaunch arg = L;

@@ -12,6 +12,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -57,23 +58,133 @@ extern "C" void cox_default_options(cox_options *o)
     o->stream = nullptr;
 }
 
+namespace {
+
+struct PoolBlock {
+    void *p;
+    size_t bytes;
+    int device;     // -1: pinned host memory
+};
+
+struct Pool {
+    std::mutex mu;
+    std::vector<PoolBlock> idle, used;
+    size_t idle_bytes = 0;
+    int handles = 0;
+};
+
+Pool &pool()
+{
+    static Pool *p = new Pool;   // never destroyed: handles may be released at exit
+    return *p;
+}
+
+void pool_release(const PoolBlock &b)
+{
+    if (b.device < 0) (void)hipHostFree(b.p);
+    else (void)hipFree(b.p);
+}
+
+}  // namespace
+
+hipError_t pool_get(void **out, size_t bytes, bool pinned)
+{
+    *out = nullptr;
+    int device = -1;
+    if (!pinned) {
+        const hipError_t e = hipGetDevice(&device);
+        if (e != hipSuccess) return e;
+    }
+    bytes = (std::max<size_t>(bytes, 1) + 4095) & ~size_t(4095);
+    Pool &P = pool();
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        size_t best = P.idle.size();
+        for (size_t i = 0; i < P.idle.size(); ++i)
+            if (P.idle[i].device == device && P.idle[i].bytes >= bytes && P.idle[i].bytes <= 2 * bytes &&
+                (best == P.idle.size() || P.idle[i].bytes < P.idle[best].bytes))
+                best = i;
+        if (best < P.idle.size()) {
+            const PoolBlock b = P.idle[best];
+            P.idle.erase(P.idle.begin() + (std::ptrdiff_t)best);
+            P.idle_bytes -= b.bytes;
+            P.used.push_back(b);
+            *out = b.p;
+            return hipSuccess;
+        }
+    }
+    void *p = nullptr;
+    const hipError_t e = pinned ? hipHostMalloc(&p, bytes, hipHostMallocPortable) : hipMalloc(&p, bytes);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(P.mu);
+    P.used.push_back(PoolBlock{p, bytes, device});
+    *out = p;
+    return hipSuccess;
+}
+
+void pool_put(void *p)
+{
+    if (!p) return;
+    Pool &P = pool();
+    PoolBlock b{nullptr, 0, 0};
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        for (size_t i = 0; i < P.used.size(); ++i)
+            if (P.used[i].p == p) {
+                b = P.used[i];
+                P.used.erase(P.used.begin() + (std::ptrdiff_t)i);
+                break;
+            }
+        if (b.p && P.handles > 0 && b.bytes <= kPoolBlock && P.idle_bytes + b.bytes <= kPoolBytes) {
+            P.idle.push_back(b);
+            P.idle_bytes += b.bytes;
+            return;
+        }
+    }
+    if (b.p) pool_release(b);
+}
+
+void pool_handle_born()
+{
+    std::lock_guard<std::mutex> lock(pool().mu);
+    ++pool().handles;
+}
+
+void pool_handle_gone()
+{
+    Pool &P = pool();
+    std::vector<PoolBlock> all;
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        if (--P.handles > 0) return;
+        all.swap(P.idle);
+        P.idle_bytes = 0;
+    }
+    for (const PoolBlock &b : all) pool_release(b);
+}
+
+cox_handle::cox_handle() { pool_handle_born(); }
+cox_handle::~cox_handle() { pool_handle_gone(); }
+
 static void free_device(cox_handle *h)
 {
+    // a call that failed may have left work queued: no block goes back to the pool under it
+    (void)hipDeviceSynchronize();
     newton_free(h);
-    if (h->d_x) (void)hipFree(h->d_x);
+    pool_put(h->d_x);
     if (h->d_xbits) (void)hipFree(h->d_xbits);
     if (h->d_xvals) (void)hipFree(h->d_xvals);
     if (h->d_xvoff) (void)hipFree(h->d_xvoff);
     if (h->d_woff) (void)hipFree(h->d_woff);
-    if (h->d_trust) (void)hipFree(h->d_trust);
     h->d_xbits = nullptr;
     h->d_xvals = nullptr;
     h->d_xvoff = nullptr;
     h->d_woff = nullptr;
     h->d_trust = nullptr;
-    if (h->d_meta) (void)hipFree(h->d_meta);
-    if (h->d_vec) (void)hipFree(h->d_vec);
-    if (h->d_sync) (void)hipFree(h->d_sync);
+    pool_put(h->d_small);
+    pool_put(h->hpin);
+    h->d_small = nullptr;
+    h->hpin = nullptr;
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);
     h->d_x = nullptr;
@@ -226,36 +337,47 @@ static size_t indicator_unit(int ipt) { return ipt > 8 ? 2 : 1; }
 static hipError_t alloc_device(cox_handle *h)
 {
     const int64_t ld = h->shape.ld, p = h->p;
+    auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
+    // the small arrays share one allocation (an allocation and its release cost more than a small
+    // data set's kernels)
+    const size_t meta = up(sizeof(uint32_t) * (size_t)ld), vec = up(sizeof(double) * (size_t)(6 * p + kResultSlots + 64));
+    const size_t sync = up(sync_scratch_bytes(h->shape.ipt ? h->shape.grid : 1));
+    const size_t trust = h->shape.ipt ? sizeof(double) * (size_t)h->shape.grid * p : 0;
     hipError_t e;
-    if ((h->ldb == 0 && (e = hipMalloc(&h->d_x, sizeof(double) * (size_t)ld * p)) != hipSuccess) ||
+    void *x = nullptr, *pin = nullptr;
+    if ((h->ldb == 0 && (e = pool_get(&x, sizeof(double) * (size_t)ld * p, false)) != hipSuccess) ||
         (h->ldb != 0 && (e = hipMalloc(&h->d_xbits, indicator_unit(h->shape.ipt) * (size_t)h->ldb * p)) != hipSuccess) ||
-        (e = hipMalloc(&h->d_meta, sizeof(uint32_t) * (size_t)ld)) != hipSuccess ||
-        (e = hipMalloc(&h->d_vec, sizeof(double) * (size_t)(6 * p + kResultSlots + 64))) != hipSuccess ||
-        (e = hipMalloc(&h->d_sync, sync_scratch_bytes(h->shape.ipt ? h->shape.grid : 1))) != hipSuccess ||
-        (h->shape.ipt && (e = hipMalloc(&h->d_trust, sizeof(double) * (size_t)h->shape.grid * p)) != hipSuccess))
+        (e = pool_get(&h->d_small, meta + vec + sync + trust, false)) != hipSuccess ||
+        (e = pool_get(&pin, sizeof(double) * cox_handle::hpin_doubles(p), true)) != hipSuccess) {
+        pool_put(x);
         return e;
+    }
+    h->d_x = static_cast<double *>(x);
+    h->hpin = static_cast<double *>(pin);
+    char *at = static_cast<char *>(h->d_small);
+    h->d_meta = reinterpret_cast<uint32_t *>(at);
+    h->d_vec = reinterpret_cast<double *>(at + meta);
+    h->d_sync = at + meta + vec;
+    h->d_trust = trust ? reinterpret_cast<double *>(at + meta + vec + sync) : nullptr;
     return hipSuccess;
 }
 
-// Row words at the layout positions; padding rows are single-row strata without events.
-static hipError_t upload_meta(cox_handle *h)
+// Row words at the layout positions (padding rows are single-row strata without events), the l1
+// weights and the exponential's table, in one copy; and the timing events.  The sums q follow.
+static hipError_t upload_host_state(cox_handle *h)
 {
-    const int64_t ld = h->shape.ld;
-    std::vector<uint32_t> mpad(ld, kHeadBit | kPadBit);
+    const int64_t ld = h->shape.ld, p = h->p;
+    const size_t vec_at = (size_t)(reinterpret_cast<char *>(h->d_vec) - reinterpret_cast<char *>(h->d_meta));
+    std::vector<char> image(vec_at + sizeof(double) * (size_t)(6 * p + kResultSlots + 64), 0);
+    uint32_t *mpad = reinterpret_cast<uint32_t *>(image.data());
+    std::fill(mpad, mpad + ld, kHeadBit | kPadBit);
     for (int64_t i = 0; i < h->n; ++i) mpad[h->pos[i]] = h->meta[i];
-    return hipMemcpy(h->d_meta, mpad.data(), sizeof(uint32_t) * ld, hipMemcpyHostToDevice);
-}
-
-// l1 weights, the exponential's table and the timing events.
-static hipError_t upload_tables(cox_handle *h)
-{
-    hipError_t e = hipMemcpy(h->gam(), h->gamma.data(), sizeof(double) * h->p, hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-        // 2^(j/64), j = 0..63, rounded to nearest from extended precision (table of the device exp)
-        double tab[64];
-        for (int j = 0; j < 64; ++j) tab[j] = (double)std::exp2l((long double)j / 64.0L);
-        e = hipMemcpy(h->exp_tab(), tab, sizeof(tab), hipMemcpyHostToDevice);
-    }
+    double *vec = reinterpret_cast<double *>(image.data() + vec_at);
+    std::copy(h->gamma.begin(), h->gamma.end(), vec + (h->gam() - h->d_vec));
+    // 2^(j/64), j = 0..63, rounded to nearest from extended precision (table of the device exp)
+    double *tab = vec + (h->exp_tab() - h->d_vec);
+    for (int j = 0; j < 64; ++j) tab[j] = (double)std::exp2l((long double)j / 64.0L);
+    hipError_t e = hipMemcpy(h->d_meta, image.data(), image.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipEventCreate(&h->ev0);
     if (e == hipSuccess) e = hipEventCreate(&h->ev1);
     return e;
@@ -408,20 +530,22 @@ extern "C" int cox_init(cox_handle **out, const cox_data *d, const cox_options *
         delete h;
         return hip_fail(nullptr, e, "device allocation");
     }
-    e = upload_meta(h);
+    e = upload_host_state(h);
     if (d->on_device) {
         // X gathered on the device into canonical order at the layout positions: only the
         // 4-byte source row of each device row crosses PCIe
         std::vector<int32_t> src((size_t)ld, -1);
         for (int64_t i = 0; i < n; ++i) src[(size_t)h->pos[i]] = (int32_t)h->perm[i];
-        int32_t *d_src = nullptr;
-        if (e == hipSuccess) e = hipMalloc(&d_src, sizeof(int32_t) * (size_t)ld);
+        void *src_mem = nullptr;
+        if (e == hipSuccess) e = pool_get(&src_mem, sizeof(int32_t) * (size_t)ld, false);
+        int32_t *d_src = static_cast<int32_t *>(src_mem);
         if (e == hipSuccess) e = hipMemcpy(d_src, src.data(), sizeof(int32_t) * (size_t)ld, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = (hipError_t)launch_gather_rows(d->x, d->ldx, d_src, nullptr, nullptr, nullptr, h->d_x, ld, (int)p,
                                                h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        if (d_src) (void)hipFree(d_src);
+        if (e != hipSuccess) (void)hipDeviceSynchronize();
+        pool_put(d_src);
     } else {
         // X in canonical order at the layout positions, column by column
         std::vector<double> col(ld, 0.0);
@@ -434,7 +558,6 @@ extern "C" int cox_init(cox_handle **out, const cox_data *d, const cox_options *
     // q_j = delta'X_j, summed on the device in a fixed order (the same for either source of X)
     if (e == hipSuccess) e = (hipError_t)launch_event_sums(h->d_x, ld, h->d_meta, h->q(), (int)p, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e == hipSuccess) e = upload_tables(h);
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -524,10 +647,9 @@ extern "C" int cox_init_indicator(cox_handle **out, int64_t n, int64_t p, const 
         delete h;
         return hip_fail(nullptr, e, "device allocation");
     }
-    e = upload_meta(h);
+    e = upload_host_state(h);
     if (e == hipSuccess) e = hipMemcpy(h->d_xbits, bits.data(), bits.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->q(), q.data(), sizeof(double) * p, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = upload_tables(h);
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -656,7 +778,7 @@ extern "C" int cox_init_sparse(cox_handle **out, int64_t n, int64_t p, const int
         delete h;
         return hip_fail(nullptr, e, "device allocation");
     }
-    e = upload_meta(h);
+    e = upload_host_state(h);
     if (e == hipSuccess) e = hipMemcpy(h->d_xbits, bits.data(), bits.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !vals.empty())
         e = hipMemcpy(h->d_xvals, vals.data(), sizeof(double) * vals.size(), hipMemcpyHostToDevice);
@@ -664,7 +786,6 @@ extern "C" int cox_init_sparse(cox_handle **out, int64_t n, int64_t p, const int
     if (e == hipSuccess && !woff.empty())
         e = hipMemcpy(h->d_woff, woff.data(), sizeof(int32_t) * woff.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(h->q(), q.data(), sizeof(double) * p, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = upload_tables(h);
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -780,15 +901,15 @@ extern "C" int cox_init_resample(cox_handle **out, const cox_handle *parent, con
     std::vector<int32_t> src((size_t)ld, -1);
     for (int64_t k = 0; k < h->n; ++k) src[(size_t)h->pos[(size_t)k]] = (int32_t)parent->pos[(size_t)from[(size_t)k]];
     hipError_t e = alloc_device(h);
-    int32_t *d_src = nullptr;
-    if (e == hipSuccess) e = hipMalloc(&d_src, sizeof(int32_t) * (size_t)ld);
+    void *src_mem = nullptr;
+    if (e == hipSuccess) e = pool_get(&src_mem, sizeof(int32_t) * (size_t)ld, false);
+    int32_t *d_src = static_cast<int32_t *>(src_mem);
     if (e != hipSuccess) {
-        if (d_src) (void)hipFree(d_src);
         free_device(h);
         delete h;
         return hip_fail(nullptr, e, "device allocation");
     }
-    e = upload_meta(h);
+    e = upload_host_state(h);
     if (e == hipSuccess) e = hipMemcpy(d_src, src.data(), sizeof(int32_t) * (size_t)ld, hipMemcpyHostToDevice);
     if (e == hipSuccess && parent->d_x) {
         e = (hipError_t)launch_gather_rows(parent->d_x, parent->shape.ld, d_src, nullptr, nullptr, nullptr, h->d_x, ld,
@@ -802,8 +923,8 @@ extern "C" int cox_init_resample(cox_handle **out, const cox_handle *parent, con
                                                    h->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    (void)hipFree(d_src);
-    if (e == hipSuccess) e = upload_tables(h);
+    if (e != hipSuccess) (void)hipDeviceSynchronize();
+    pool_put(d_src);
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -938,7 +1059,7 @@ extern "C" int cox_init_intervals(cox_handle **out, const cox_handle *parent, co
         delete h;
         return hip_fail(nullptr, e, "device allocation");
     }
-    e = upload_meta(h);
+    e = upload_host_state(h);
     if (e == hipSuccess) e = hipMemcpy(d_maps, maps.data(), sizeof(int32_t) * maps.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && parent->d_x) {
         e = (hipError_t)launch_gather_rows(parent->d_x, parent->shape.ld, d_maps, d_maps + ld, d_maps + 2 * ld,
@@ -954,7 +1075,6 @@ extern "C" int cox_init_intervals(cox_handle **out, const cox_handle *parent, co
     }
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     (void)hipFree(d_maps);
-    if (e == hipSuccess) e = upload_tables(h);
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -987,11 +1107,9 @@ static int run_kernel(cox_handle *h, int mode, int j0, int j1, const double *bet
         return fail(h, COX_EUNSUPPORTED,
                     "n exceeds the register-resident capacity of the persistent kernel: this handle supports "
                     "cox_fit (by Newton steps), cox_evaluate and cox_evaluate_full only");
-    hipError_t e;
-    if (beta_host) e = hipMemcpyAsync(h->beta(), beta_host, sizeof(double) * h->p, hipMemcpyHostToDevice, h->stream);
-    else e = hipMemsetAsync(h->beta(), 0, sizeof(double) * h->p, h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(h->result(), 0, sizeof(double) * kResultSlots, h->stream);
-    if (e != hipSuccess) return hip_fail(h, e, "staging beta");
+    double *hres = h->hout() + 4 * h->p;
+    std::fill(hres, hres + kResultSlots, 0.0);
+    if (beta_host) std::copy(beta_host, beta_host + h->p, h->hpin);
     CcdLaunch L;
     L.x = h->d_x;
     L.xbits = h->d_xbits;
@@ -1018,20 +1136,19 @@ static int run_kernel(cox_handle *h, int mode, int j0, int j1, const double *bet
     L.g1 = h->g1();
     L.g2 = h->g2();
     L.m2 = h->m2();
-    L.result = h->result();
+    L.beta0 = beta_host ? h->hpin : nullptr;
+    L.hout = h->hout();
     carve_sync_scratch(h->d_sync, h->shape.grid, L);
     int rc = launch_ccd(h->shape, L, h->stream, h->ev0, h->ev1);
     if (rc != (int)hipSuccess) return hip_fail(h, (hipError_t)rc, "kernel launch");
-    if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return hip_fail(h, e, "kernel execution");
+    // the kernel writes its results to hout: one wait and no copy
+    const hipError_t e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return hip_fail(h, e, "kernel execution");
     (void)hipEventElapsedTime(&h->last_kernel_ms, h->ev0, h->ev1);
     h->prof = cox_profile{};
     h->prof.kernel_ms = h->last_kernel_ms;
-    uint32_t ctl[2] = {0, 0};
-    if ((e = hipMemcpy(ctl, L.ctl, sizeof(ctl), hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(h, e, "reading control words");
-    if ((e = hipMemcpy(result, h->result(), sizeof(double) * kResultSlots, hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(h, e, "reading results");
-    if (ctl[0] != 0u || result[kResCompleted] != 1.0)
+    std::copy(hres, hres + kResultSlots, result);
+    if (result[kResAborted] != 0.0 || result[kResCompleted] != 1.0)
         return fail(h, COX_EDEVICE, "device-side synchronisation timed out; results are not valid");
     if (result[kResNumeric] != 0.0)
         return fail(h, COX_ENUMERIC, "a risk-set sum left the FP64 normal range after the global shift");
@@ -1067,10 +1184,8 @@ extern "C" int cox_fit(cox_handle *h, const double *beta0, double *beta_out, cox
         return rc2;
     }
     if (rc != COX_OK && rc != COX_ENUMERIC) return rc;
-    hipError_t e = hipMemcpy(beta_out, h->beta(), sizeof(double) * h->p, hipMemcpyDeviceToHost);
-    std::vector<double> g(h->p);
-    if (e == hipSuccess) e = hipMemcpy(g.data(), h->g1(), sizeof(double) * h->p, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(h, e, "reading beta");
+    std::copy(h->hout(), h->hout() + h->p, beta_out);
+    const double *g = h->hout() + h->p;
     const bool converged = res[kResConverged] == 1.0;
     if (rc == COX_OK && !converged) rc = COX_NOT_CONVERGED;
     if (info) {
@@ -1326,10 +1441,8 @@ extern "C" int cox_evaluate(cox_handle *h, const double *beta, double *objective
         return cox_evaluate_full(h, beta, objective, grad, hess_diag, nullptr);
     }
     if (rc != COX_OK) return rc;
-    hipError_t e = hipSuccess;
-    if (grad) e = hipMemcpy(grad, h->g1(), sizeof(double) * h->p, hipMemcpyDeviceToHost);
-    if (hess_diag && e == hipSuccess) e = hipMemcpy(hess_diag, h->g2(), sizeof(double) * h->p, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(h, e, "reading gradient");
+    if (grad) std::copy(h->hout() + h->p, h->hout() + 2 * h->p, grad);
+    if (hess_diag) std::copy(h->hout() + 2 * h->p, h->hout() + 3 * h->p, hess_diag);
     if (objective) {
         double pen = 0.0;
         for (int64_t j = 0; j < h->p; ++j) pen += h->gamma[j] * std::fabs(beta[j]);
@@ -1346,15 +1459,11 @@ extern "C" int cox_coordinate(cox_handle *h, const double *beta, int64_t j, doub
     double res[kResultSlots];
     int rc = run_kernel(h, kModeEval, (int)j, (int)j + 1, beta, res);
     if (rc != COX_OK) return rc;
-    double v[3];
-    hipError_t e = hipMemcpy(&v[0], h->g1() + j, sizeof(double), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&v[1], h->g2() + j, sizeof(double), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&v[2], h->m2() + j, sizeof(double), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(h, e, "reading coordinate");
-    out[0] = v[0];
-    out[1] = v[1];
+    const double *g1 = h->hout() + h->p;
+    out[0] = g1[j];
+    out[1] = g1[h->p + j];
     out[2] = res[kResObjective];
-    out[3] = v[2];
+    out[3] = g1[2 * h->p + j];
     return COX_OK;
 }
 

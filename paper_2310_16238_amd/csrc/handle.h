@@ -29,9 +29,9 @@ struct NewtonState {
     double *carry = nullptr;       // [ntiles][p]
     double *colpart = nullptr;     // [ntiles][p][3]
     double *vec = nullptr;         // beta, grad, diag1, diag2, dx (p each), scal (8)
-    double *hvec = nullptr;        // pinned host mirror of vec, then flags and status (one double each)
+    double *hvec = nullptr;        // pinned host mirror of vec, then flags and status (one double each); in the handle's hpin
+    void *arena = nullptr;         // one allocation behind the pointers below and above
     unsigned *flags = nullptr;
-    int *status = nullptr;
     uint8_t *free_col = nullptr;   // [p]
     void *z = nullptr;             // [p][ldz] in the contraction type
     float *zscale = nullptr;       // [p]
@@ -58,10 +58,14 @@ struct NewtonState {
     double *erows = nullptr;       // 4 x [ld]: E0', k', l21, l22 at event-group ends
     double *epart = nullptr;       // [p][eblocks] diagonal parts of the multi-event groups
     int eblocks = 0;
-    double *prox = nullptr;        // proximal Newton: g, beta, gamma, D (p each), then the sweep count
+    double *prox = nullptr;        // proximal Newton: gamma (p), then the sweep count
 };
 
+constexpr int kScalSlots = 8;
+
 struct cox_handle {
+    cox_handle();
+    ~cox_handle();
     int64_t n = 0, p = 0;
     int device = 0;
     coxmi::LaunchShape shape;
@@ -72,10 +76,14 @@ struct cox_handle {
     double *d_xvals = nullptr;     // sparse X (cox_init_sparse): the values of the rows d_xbits marks
     int64_t *d_xvoff = nullptr;    // [p] start of each column's values
     int32_t *d_woff = nullptr;     // [p][ld / (64 ipt)] values of the column before each wave's rows
+    void *d_small = nullptr;       // one allocation behind the four below
     uint32_t *d_meta = nullptr;
     double *d_vec = nullptr;       // q, gamma, beta, g1, g2, m2 (p each), result (8), exp table (64)
     void *d_sync = nullptr;
     double *d_trust = nullptr;     // [grid][p] trust half-widths of the persistent kernel
+    // pinned host memory that the kernels write their results to (no copy, one wait per call): a
+    // start point (p); beta, g1, g2, m2 (p each) and result (8) of the persistent kernel; nt.hvec
+    double *hpin = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     float last_kernel_ms = 0.0f;
     cox_profile prof{};
@@ -94,9 +102,22 @@ struct cox_handle {
     double *g1() const { return d_vec + 3 * p; }
     double *g2() const { return d_vec + 4 * p; }
     double *m2() const { return d_vec + 5 * p; }
-    double *result() const { return d_vec + 6 * p; }
+    double *hout() const { return hpin + p; }
+    double *hnewton() const { return hpin + 5 * p + coxmi::kResultSlots; }
+    static size_t hpin_doubles(int64_t p) { return (size_t)(10 * p + coxmi::kResultSlots + kScalSlots + 2); }
     double *exp_tab() const { return d_vec + 6 * p + coxmi::kResultSlots; }
 };
+
+// Memory of handles, device or pinned host.  While some handle lives, blocks that others have given
+// back are kept for the next (a cross-validation or bootstrap makes a handle per refit, and its
+// allocations took as long as its kernels): at most kPoolBytes in blocks of at most kPoolBlock, all
+// released with the last handle.  Every call on a handle ends with its stream's work done, so a
+// block that is given back is idle.  Thread-safe.
+constexpr size_t kPoolBytes = (size_t)256 << 20, kPoolBlock = (size_t)64 << 20;
+hipError_t pool_get(void **p, size_t bytes, bool pinned);
+void pool_put(void *p);
+void pool_handle_born();
+void pool_handle_gone();
 
 int handle_fail(cox_handle *h, int code, const std::string &msg);
 int handle_hip_fail(cox_handle *h, hipError_t e, const char *what);

@@ -64,7 +64,8 @@ struct CcdLaunch {
     double *g1 = nullptr;            // [p] g' of each coordinate's last evaluation
     double *g2 = nullptr;            // [p] g''
     double *m2 = nullptr;            // [p] delta'(S[N2]/S[D])
-    double *result = nullptr;        // [kResultSlots] see ResultSlot
+    const double *beta0 = nullptr;   // [p] start point in host memory (pinned), NULL: zeros
+    double *hout = nullptr;          // host memory (pinned): beta, g1, g2, m2 (p each), then [kResultSlots] see ResultSlot
     void *agg = nullptr;             // [grid][6] packets: tile aggregates for the look-back
     void *part = nullptr;            // [grid][5] packets: per-workgroup partial sums
     void *res = nullptr;             // [2] packets: the step broadcast by workgroup 0
@@ -78,7 +79,8 @@ void carve_sync_scratch(void *base, int grid, CcdLaunch &L);
 
 
 // Launch the persistent CCD / evaluation kernel; returns a hipError_t value.
-// Zeroes the synchronisation words first; records ev0/ev1 around the kernel if non-null.
+// A small kernel zeroes the synchronisation words and places the start point first; records
+// ev0/ev1 around the persistent kernel if non-null.
 int launch_ccd(const LaunchShape &shape, const CcdLaunch &L, hipStream_t stream,
                hipEvent_t ev0, hipEvent_t ev1);
 
@@ -107,7 +109,7 @@ int segscan_f64_noalloc(const double *a, const uint8_t *head, double *b, int64_t
 // Result slots written by the persistent kernel.
 enum ResultSlot {
     kResSweeps = 0, kResLastStep = 1, kResObjective = 2, kResPinned = 3,
-    kResConverged = 4, kResNumeric = 5, kResCompleted = 6
+    kResConverged = 4, kResNumeric = 5, kResCompleted = 6, kResAborted = 7
 };
 constexpr int kResultSlots = 8;
 

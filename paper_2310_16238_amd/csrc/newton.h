@@ -56,6 +56,9 @@ struct FullEvalArgs {
     double *colpart = nullptr;             // [ntiles][p][3]
     double *grad = nullptr, *diag1 = nullptr, *diag2 = nullptr;   // [p] each
     double *scal = nullptr;           // [0] shift c, [1] objective
+    // the same results in pinned host memory: grad, diag1, diag2 (p each); [0] unused, [1] objective; flags
+    double *hgrad = nullptr, *hscal = nullptr;
+    unsigned *hflags = nullptr;
     unsigned *flags = nullptr;        // bit 0: a risk-set sum left the FP64 normal range
     int ztype = kZF64;
     // sqrt(d_g) xbar_g / zscale_j, event groups in order: [p][ldz], or with segments and BF16

@@ -501,13 +501,15 @@ __global__ __launch_bounds__(kRowBlock) void efron_z_kernel(const double *x, int
 }
 
 // diag2[j] += the multi-event groups' parts, summed in block order
-__global__ __launch_bounds__(kWave) void efron_d2_kernel(const double *epart, int eblocks, int p, double *diag2)
+__global__ __launch_bounds__(kWave) void efron_d2_kernel(const double *epart, int eblocks, int p, double *diag2,
+                                                         double *hdiag2)
 {
     const int j = blockIdx.x * kWave + threadIdx.x;
     if (j < p) {
         double s = 0.0;
         for (int k = 0; k < eblocks; ++k) s += epart[(int64_t)j * eblocks + k];
         diag2[j] += s;
+        hdiag2[j] = diag2[j];
     }
 }
 
@@ -529,7 +531,8 @@ __device__ __forceinline__ double tree_sum_256(double v, double *red)
 
 __global__ __launch_bounds__(kRowBlock) void colreduce_kernel(const double *part, int p, int ntiles, double *grad,
                                                               double *diag1, double *diag2, const double *blockobj,
-                                                              int nb, double *scal)
+                                                              int nb, double *scal, const unsigned *flags,
+                                                              double *hgrad, double *hscal, unsigned *hflags)
 {
     __shared__ double red[kRowBlock / kWave];
     __shared__ double tree[256];
@@ -549,12 +552,19 @@ __global__ __launch_bounds__(kRowBlock) void colreduce_kernel(const double *part
             grad[j] = sg;
             diag1[j] = s1;
             diag2[j] = s2;
+            hgrad[j] = sg;
+            hgrad[p + j] = s1;
+            hgrad[2 * p + j] = s2;
         }
     } else {
         double o = 0.0;
         for (int i = threadIdx.x; i < nb; i += kRowBlock) o += blockobj[i];
         o = block_sum(o, red);
-        if (threadIdx.x == 0) scal[1] = o;
+        if (threadIdx.x == 0) {
+            scal[1] = o;
+            hscal[1] = o;
+            *hflags = *flags;
+        }
     }
 }
 
@@ -1168,7 +1178,8 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
         else COXMI_SEGEVAL(__hip_bfloat16, true);
 #undef COXMI_SEGEVAL
         colreduce_kernel<<<A.p + 1, kRowBlock, 0, stream>>>(A.colpart, A.p, grid * seg_parts(A.p), A.grad, A.diag1,
-                                                            A.diag2, A.blockbuf, grid, A.scal);
+                                                            A.diag2, A.blockbuf, grid, A.scal, A.flags, A.hgrad, A.hscal,
+                                                            A.hflags);
         return hipGetLastError() == hipSuccess ? 0 : -3;
     }
     eta_kernel<<<nb, kRowBlock, 0, stream>>>(A.x, ld, A.p, A.beta, A.eta);
@@ -1219,7 +1230,7 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
     }
 #undef COXMI_COLPASS
     colreduce_kernel<<<A.p + 1, kRowBlock, 0, stream>>>(A.colpart, A.p, A.ntiles, A.grad, A.diag1, A.diag2,
-                                                        A.blockbuf, nb, A.scal);
+                                                        A.blockbuf, nb, A.scal, A.flags, A.hgrad, A.hscal, A.hflags);
     if (ef && A.want_xbar) {
         if (A.ztype == kZF32) return -5;
         efron_w_kernel<<<(unsigned)((A.n_multi + kRowBlock - 1) / kRowBlock), kRowBlock, 0, stream>>>(
@@ -1233,7 +1244,8 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
             efron_z_kernel<__hip_bfloat16><<<zg, kRowBlock, 0, stream>>>(
                 A.x, ld, A.p, A.me_ptr, A.me_row, A.me_end, A.me_w, A.s1me, A.zq, A.zq2, A.zq3, A.gidx, A.n_groups,
                 A.n_multi, A.ldz, A.zscale, static_cast<__hip_bfloat16 *>(A.z), A.epart, A.eblocks);
-        efron_d2_kernel<<<(A.p + kWave - 1) / kWave, kWave, 0, stream>>>(A.epart, A.eblocks, A.p, A.diag2);
+        efron_d2_kernel<<<(A.p + kWave - 1) / kWave, kWave, 0, stream>>>(A.epart, A.eblocks, A.p, A.diag2,
+                                                                             A.hgrad + 2 * A.p);
     }
     e = hipGetLastError();
     return e == hipSuccess ? 0 : -3;

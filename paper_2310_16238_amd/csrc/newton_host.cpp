@@ -5,6 +5,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "handle.h"
@@ -15,8 +17,6 @@ using namespace coxmi;
 
 namespace {
 
-constexpr int kScalSlots = 8;
-
 double *nrow(const NewtonState &s, int64_t ld, int k) { return s.rows + (int64_t)k * ld; }
 
 double elapsed_ms(hipEvent_t a, hipEvent_t b)
@@ -25,11 +25,27 @@ double elapsed_ms(hipEvent_t a, hipEvent_t b)
     return hipEventElapsedTime(&ms, a, b) == hipSuccess ? (double)ms : 0.0;
 }
 
-template <typename T>
-hipError_t dalloc(T **p, size_t bytes)
-{
-    return hipMalloc(reinterpret_cast<void **>(p), bytes);
-}
+// Lays arrays out in one allocation: add() each, then allocate() and every pointer is set.
+struct Arena {
+    std::vector<std::pair<void **, size_t>> parts;
+    size_t bytes = 0;
+    template <typename T>
+    void add(T **p, size_t n)
+    {
+        parts.emplace_back(reinterpret_cast<void **>(p), bytes);
+        bytes += (n + 255) & ~size_t(255);
+    }
+    hipError_t allocate(void **base)
+    {
+        const hipError_t e = pool_get(base, bytes, false);
+        if (e != hipSuccess) {
+            *base = nullptr;
+            return e;
+        }
+        for (const auto &q : parts) *q.first = static_cast<char *>(*base) + q.second;
+        return hipSuccess;
+    }
+};
 
 // xbar (Z) is kept in BF16 for both reduced-precision modes
 bool lowp(int prec) { return prec == COX_BF16 || prec == COX_FP8_E4M3; }
@@ -133,83 +149,79 @@ int newton_setup(cox_handle *h)
                             : std::max(syrk_partial_bytes(p, (p <= 256 ? 2 : 1) * kSplitsXF64),
                                        syrk_partial_bytes(p, (p <= 256 ? 2 : 1) * kSplitsZF64));
     s.scan_scratch_bytes = rowscan_scratch_bytes(s.ntiles);
-    const size_t zb = ztype_bytes(h->opt.x_precision);
+    // one allocation for everything (thirty took longer than a small data set's fit); the uploaded
+    // arrays come first, so that one copy fills them
     hipError_t e;
-    if ((e = dalloc(&s.gidx, sizeof(int32_t) * ld)) != hipSuccess ||
-        (e = dalloc(&s.rows, sizeof(double) * 9 * ld)) != hipSuccess ||
-        (e = dalloc(&s.blockbuf, sizeof(double) * s.max_blocks)) != hipSuccess ||
-        (e = dalloc(&s.tile_carry, (size_t)s.ntiles)) != hipSuccess ||
-        (e = dalloc(&s.lasthead, sizeof(int32_t) * s.ntiles)) != hipSuccess ||
-        (e = dalloc(&s.agg_tiles, sizeof(int32_t) * std::max(1, s.n_agg))) != hipSuccess ||
-        (e = dalloc(&s.agg, sizeof(double) * 2 * (size_t)s.ntiles * p)) != hipSuccess ||
-        (e = dalloc(&s.carry, sizeof(double) * (size_t)s.ntiles * p)) != hipSuccess ||
-        (e = dalloc(&s.colpart, sizeof(double) * 3 *
-                                    (size_t)std::max(s.ntiles, s.nseg ? seg_part_slots(p, s.nseg) : 0) * p)) != hipSuccess ||
-        (e = dalloc(&s.seg, sizeof(EvalSeg) * std::max<size_t>(1, segs.size()))) != hipSuccess ||
-        (e = dalloc(&s.vec, sizeof(double) * (5 * (size_t)p + kScalSlots))) != hipSuccess ||
-        (e = dalloc(&s.flags, sizeof(unsigned))) != hipSuccess ||
-        (e = dalloc(&s.status, sizeof(int))) != hipSuccess ||
-        (e = dalloc(&s.free_col, (size_t)p)) != hipSuccess ||
-        (e = dalloc(&s.z, zb * (size_t)p * s.ldz)) != hipSuccess ||
-        (e = dalloc(&s.zscale, sizeof(float) * p)) != hipSuccess ||
-        (e = dalloc(&s.syrk_part, s.syrk_part_bytes)) != hipSuccess ||
-        (e = dalloc(&s.info, sizeof(double) * (size_t)p * p)) != hipSuccess ||
-        (e = dalloc(&s.scan_scratch, s.scan_scratch_bytes)) != hipSuccess ||
-        (e = hipHostMalloc(reinterpret_cast<void **>(&s.hvec), sizeof(double) * (5 * (size_t)p + kScalSlots + 2),
-                           hipHostMallocDefault)) != hipSuccess) {
+    Arena A;
+    std::vector<char> image;
+    auto upload = [&](auto **p, const auto &v) {
+        using T = std::remove_pointer_t<std::remove_pointer_t<decltype(p)>>;
+        const size_t at = A.bytes;
+        A.add(p, sizeof(T) * std::max<size_t>(1, v.size()));
+        image.resize(A.bytes, 0);
+        if (!v.empty()) std::memcpy(image.data() + at, v.data(), sizeof(T) * v.size());
+    };
+    upload(&s.gidx, gidx);
+    upload(&s.tile_carry, tile_carry);
+    upload(&s.lasthead, lasthead);
+    upload(&s.agg_tiles, agg_tiles);
+    upload(&s.seg, segs);
+    if (s.efron) {
+        upload(&s.gidx2, gidx2);
+        upload(&s.gend, gend);
+        upload(&s.me_ptr, me_ptr);
+        upload(&s.me_row, me_row);
+        upload(&s.me_end, me_end);
+        const size_t nm = (size_t)std::max<int64_t>(1, s.n_multi);
+        A.add(&s.me_w, sizeof(double) * std::max<size_t>(1, me_row.size()));
+        A.add(&s.s1me, sizeof(double) * nm * p);
+        A.add(&s.erows, sizeof(double) * 4 * ld);
+        A.add(&s.epart, sizeof(double) * (size_t)s.eblocks * p);
+    }
+    A.add(&s.rows, sizeof(double) * 9 * ld);
+    A.add(&s.blockbuf, sizeof(double) * s.max_blocks);
+    A.add(&s.agg, sizeof(double) * 2 * (size_t)s.ntiles * p);
+    A.add(&s.carry, sizeof(double) * (size_t)s.ntiles * p);
+    A.add(&s.colpart, sizeof(double) * 3 * (size_t)std::max(s.ntiles, s.nseg ? seg_part_slots(p, s.nseg) : 0) * p);
+    A.add(&s.vec, sizeof(double) * (5 * (size_t)p + kScalSlots));
+    A.add(&s.flags, sizeof(unsigned));
+    A.add(&s.free_col, (size_t)p);
+    A.add(&s.zscale, sizeof(float) * p);
+    A.add(&s.syrk_part, s.syrk_part_bytes);
+    A.add(&s.info, sizeof(double) * (size_t)p * p);
+    A.add(&s.scan_scratch, s.scan_scratch_bytes);
+    const size_t zb = ztype_bytes(h->opt.x_precision);
+    A.add(&s.z, zb * (size_t)p * s.ldz);
+    if (h->opt.x_precision == COX_FP8_E4M3) {
+        A.add(&s.xlp, fp8_copy_bytes(ld, p));
+        A.add(&s.xscale, sizeof(float) * p);
+        A.add(&s.wscratch, sizeof(double) * 264);
+    } else if (h->opt.x_precision == COX_BF16) {
+        A.add(&s.xlp, sizeof(uint16_t) * (size_t)p * ld);
+        A.add(&s.xscale, sizeof(float) * p);
+    }
+    if ((e = A.allocate(&s.arena)) != hipSuccess) {
         newton_free(h);
         return handle_hip_fail(h, e, "allocating full-evaluation buffers");
     }
+    s.hvec = h->hnewton();
     for (int k = 0; k < 6 && e == hipSuccess; ++k) e = hipEventCreate(&s.ev[k]);
     if (e != hipSuccess) {
         newton_free(h);
         return handle_hip_fail(h, e, "creating events");
     }
-    e = hipMemcpy(s.gidx, gidx.data(), sizeof(int32_t) * ld, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(s.tile_carry, tile_carry.data(), (size_t)s.ntiles, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(s.lasthead, lasthead.data(), sizeof(int32_t) * s.ntiles, hipMemcpyHostToDevice);
-    if (e == hipSuccess && s.n_agg)
-        e = hipMemcpy(s.agg_tiles, agg_tiles.data(), sizeof(int32_t) * s.n_agg, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(s.z, 0, zb * (size_t)p * s.ldz);
-    if (e == hipSuccess && s.nseg) {
-        // the segments write the weights of their rows only: padding rows keep 0
-        e = hipMemcpy(s.seg, segs.data(), sizeof(EvalSeg) * segs.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemset(nrow(s, ld, 6), 0, sizeof(double) * ld);
-    }
-    if (e == hipSuccess && s.efron) {
-        const size_t nme = std::max<size_t>(1, me_row.size()), nm = (size_t)std::max<int64_t>(1, s.n_multi);
-        if (e == hipSuccess) e = dalloc(&s.gidx2, sizeof(int32_t) * ld);
-        if (e == hipSuccess) e = dalloc(&s.gend, sizeof(int32_t) * ld);
-        if (e == hipSuccess) e = dalloc(&s.me_ptr, sizeof(int32_t) * (nm + 1));
-        if (e == hipSuccess) e = dalloc(&s.me_row, sizeof(int32_t) * nme);
-        if (e == hipSuccess) e = dalloc(&s.me_end, sizeof(int32_t) * nm);
-        if (e == hipSuccess) e = dalloc(&s.me_w, sizeof(double) * nme);
-        if (e == hipSuccess) e = dalloc(&s.s1me, sizeof(double) * nm * p);
-        if (e == hipSuccess) e = dalloc(&s.erows, sizeof(double) * 4 * ld);
-        if (e == hipSuccess) e = dalloc(&s.epart, sizeof(double) * (size_t)s.eblocks * p);
-        if (e == hipSuccess) e = hipMemcpy(s.gidx2, gidx2.data(), sizeof(int32_t) * ld, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(s.gend, gend.data(), sizeof(int32_t) * ld, hipMemcpyHostToDevice);
-        if (e == hipSuccess)
-            e = hipMemcpy(s.me_ptr, me_ptr.data(), sizeof(int32_t) * me_ptr.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess && !me_row.empty())
-            e = hipMemcpy(s.me_row, me_row.data(), sizeof(int32_t) * me_row.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess && !me_end.empty())
-            e = hipMemcpy(s.me_end, me_end.data(), sizeof(int32_t) * me_end.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemset(s.erows, 0, sizeof(double) * 4 * ld);
-    }
+    e = hipMemcpyAsync(s.arena, image.data(), image.size(), hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(s.z, 0, zb * (size_t)p * s.ldz, h->stream);
+    // the segments write the weights of their rows only: padding rows keep 0
+    if (e == hipSuccess && s.nseg) e = hipMemsetAsync(nrow(s, ld, 6), 0, sizeof(double) * ld, h->stream);
+    if (e == hipSuccess && s.efron) e = hipMemsetAsync(s.erows, 0, sizeof(double) * 4 * ld, h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) {
         newton_free(h);
         return handle_hip_fail(h, e, "uploading group indices");
     }
     if (h->opt.x_precision == COX_FP8_E4M3) {
         // e4m3 copy of X with power-of-two column scales (|x / s| <= 224)
-        if ((e = dalloc(&s.xlp, fp8_copy_bytes(ld, p))) != hipSuccess ||
-            (e = dalloc(&s.xscale, sizeof(float) * p)) != hipSuccess ||
-            (e = dalloc(&s.wscratch, sizeof(double) * 264)) != hipSuccess) {
-            newton_free(h);
-            return handle_hip_fail(h, e, "allocating the FP8 copy of X");
-        }
         int rc = make_fp8_copy(h->d_x, ld, p, static_cast<uint8_t *>(s.xlp), s.xscale, s.zscale, h->stream);
         if (rc == 0 && hipStreamSynchronize(h->stream) != hipSuccess) rc = -3;
         if (rc != 0) {
@@ -219,11 +231,6 @@ int newton_setup(cox_handle *h)
     }
     if (h->opt.x_precision == COX_BF16) {
         // low-precision copy of X with power-of-two column scales (|x / s| <= 1)
-        if ((e = dalloc(&s.xlp, sizeof(uint16_t) * (size_t)p * ld)) != hipSuccess ||
-            (e = dalloc(&s.xscale, sizeof(float) * p)) != hipSuccess) {
-            newton_free(h);
-            return handle_hip_fail(h, e, "allocating the BF16 copy of X");
-        }
         int rc = make_bf16_copy(h->d_x, ld, p, s.xlp, s.xscale, s.zscale, h->stream);
         if (rc == 0 && hipStreamSynchronize(h->stream) != hipSuccess) rc = -3;
         if (rc != 0) {
@@ -241,18 +248,18 @@ struct EvalOut {
     unsigned flags = 0;
 };
 
-// Full evaluation at beta (host); xbar (and diag2) only when want_xbar.
-int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out, bool want_rows = false)
+// Full evaluation at beta (host); xbar (and diag2) only when want_xbar.  newton_eval_launch queues
+// it, newton_eval_finish waits for the stream -- and whatever was queued behind -- and reads
+// the results, which the kernels write to pinned host memory.
+int newton_eval_launch(cox_handle *h, const double *beta, bool want_xbar, bool want_rows = false)
 {
     NewtonState &s = h->nt;
     const int64_t ld = h->shape.ld;
     const int p = (int)h->p;
     double *d_beta = s.vec, *d_grad = s.vec + p, *d_d1 = s.vec + 2 * p, *d_d2 = s.vec + 3 * p;
     double *d_scal = s.vec + 5 * p;
-    // beta goes up, and the results come back, through the pinned mirror: one
-    // synchronisation per evaluation
     std::memcpy(s.hvec, beta, sizeof(double) * p);
-    hipError_t e = hipMemcpyAsync(d_beta, s.hvec, sizeof(double) * p, hipMemcpyHostToDevice, h->stream);
+    const hipError_t e = hipMemcpyAsync(d_beta, s.hvec, sizeof(double) * p, hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) return handle_hip_fail(h, e, "staging beta");
     FullEvalArgs A;
     A.x = h->d_x;
@@ -285,6 +292,9 @@ int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out,
     A.diag1 = d_d1;
     A.diag2 = d_d2;
     A.scal = d_scal;
+    A.hgrad = s.hvec + p;
+    A.hscal = s.hvec + 5 * p;
+    A.hflags = reinterpret_cast<unsigned *>(s.hvec + 5 * p + kScalSlots);
     A.flags = s.flags;
     A.ztype = lowp(h->opt.x_precision) ? kZBF16 : kZF64;
     A.z = s.z;
@@ -322,26 +332,33 @@ int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out,
     int rc = full_eval_launch(A, h->stream);
     if (rc != 0) return handle_fail(h, rc == -5 ? COX_EUNSUPPORTED : COX_EDEVICE, "full evaluation launch");
     (void)hipEventRecord(s.ev[1], h->stream);
-    // grad, diag1, diag2, dx and scal are contiguous after beta
-    double *hres = s.hvec + p;
-    unsigned *hflags = reinterpret_cast<unsigned *>(s.hvec + 5 * p + kScalSlots);
-    if ((e = hipMemcpyAsync(hres, d_grad, sizeof(double) * (4 * (size_t)p + kScalSlots), hipMemcpyDeviceToHost,
-                            h->stream)) != hipSuccess ||
-        (e = hipMemcpyAsync(hflags, s.flags, sizeof(unsigned), hipMemcpyDeviceToHost, h->stream)) != hipSuccess ||
-        (e = hipStreamSynchronize(h->stream)) != hipSuccess)
-        return handle_hip_fail(h, e, "full evaluation");
-    (void)d_d1;
-    (void)d_d2;
+    return COX_OK;
+}
+
+int newton_eval_finish(cox_handle *h, bool want_xbar, EvalOut &out)
+{
+    NewtonState &s = h->nt;
+    const int p = (int)h->p;
+    const hipError_t e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return handle_hip_fail(h, e, "full evaluation");
+    const double *hres = s.hvec + p;   // grad, diag1, diag2, dx and scal
+    const unsigned flags = *reinterpret_cast<const unsigned *>(s.hvec + 5 * p + kScalSlots);
     h->prof.evaluations += 1;
     h->prof.evaluation_ms += elapsed_ms(s.ev[0], s.ev[1]);
     out.grad.assign(hres, hres + p);
     out.diag1.assign(hres + p, hres + 2 * p);
     if (want_xbar) out.diag2.assign(hres + 2 * p, hres + 3 * p);
     else out.diag2.assign(p, 0.0);
-    out.flags = *hflags;
+    out.flags = flags;
     out.objective = hres[4 * p + 1];
     if (out.flags & 1u) return handle_fail(h, COX_ENUMERIC, "a risk-set sum left the FP64 normal range");
     return COX_OK;
+}
+
+int newton_eval(cox_handle *h, const double *beta, bool want_xbar, EvalOut &out, bool want_rows = false)
+{
+    const int rc = newton_eval_launch(h, beta, want_xbar, want_rows);
+    return rc != COX_OK ? rc : newton_eval_finish(h, want_xbar, out);
 }
 
 // info = X' diag(b) X - Z'Z in the handle's precision, left in s.info (FP64).
@@ -379,13 +396,9 @@ int newton_info(cox_handle *h)
 void newton_free(cox_handle *h)
 {
     NewtonState &s = h->nt;
-    void *ptrs[] = {s.gidx, s.seg, s.rows, s.blockbuf, s.tile_carry, s.lasthead, s.agg_tiles, s.agg, s.carry,
-                    s.colpart, s.vec, s.flags, s.status, s.free_col, s.z,
-                    s.zscale, s.xlp, s.xscale, s.syrk_part, s.info, s.scan_scratch, s.wscratch,
-                    s.gidx2, s.gend, s.me_ptr, s.me_row, s.me_end, s.me_w, s.s1me, s.erows, s.epart, s.prox};
-    for (void *q : ptrs)
-        if (q) (void)hipFree(q);
-    if (s.hvec) (void)hipHostFree(s.hvec);
+    if (s.arena) (void)hipDeviceSynchronize();   // as for the handle's other blocks: nothing queued may still use it
+    pool_put(s.arena);
+    if (s.prox) (void)hipFree(s.prox);
     for (hipEvent_t ev : s.ev)
         if (ev) (void)hipEventDestroy(ev);
     s = NewtonState();
@@ -401,7 +414,10 @@ extern "C" int cox_evaluate_full(cox_handle *h, const double *beta, double *obje
     if (rc != COX_OK) return rc;
     h->prof = cox_profile{};
     EvalOut ev;
-    rc = newton_eval(h, beta, hess_diag || info, ev);
+    // the information matrix is queued behind the evaluation without a wait between
+    rc = newton_eval_launch(h, beta, hess_diag || info);
+    if (rc == COX_OK && info) rc = newton_info(h);
+    if (rc == COX_OK) rc = newton_eval_finish(h, hess_diag || info, ev);
     if (rc != COX_OK) return rc;
     const int p = (int)h->p;
     if (objective) {
@@ -413,11 +429,8 @@ extern "C" int cox_evaluate_full(cox_handle *h, const double *beta, double *obje
     if (hess_diag)
         for (int j = 0; j < p; ++j) hess_diag[j] = ev.diag1[j] - ev.diag2[j];
     if (info) {
-        rc = newton_info(h);
-        if (rc != COX_OK) return rc;
-        hipError_t e = hipStreamSynchronize(h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpy(info, h->nt.info, sizeof(double) * (size_t)p * p, hipMemcpyDeviceToHost);
+        hipError_t e = hipMemcpyAsync(info, h->nt.info, sizeof(double) * (size_t)p * p, hipMemcpyDeviceToHost, h->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return handle_hip_fail(h, e, "information matrix");
         h->prof.contractions += 1;
         h->prof.contraction_ms += elapsed_ms(h->nt.ev[2], h->nt.ev[3]);
@@ -466,14 +479,16 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
     const std::vector<double> &gam = h->gamma;
     std::vector<double> beta(p, 0.0), prev(p, 0.0), D(p, 0.0);
     if (!s.prox) {
-        const hipError_t e = hipMalloc(&s.prox, sizeof(double) * (4 * (size_t)p + 1));
+        const hipError_t e = hipMalloc(&s.prox, sizeof(double) * ((size_t)p + 1));
         if (e != hipSuccess) {
             s.prox = nullptr;
             return handle_hip_fail(h, e, "proximal Newton buffers");
         }
     }
-    double *d_g = s.prox, *d_beta = s.prox + p, *d_gam = s.prox + 2 * p, *d_D = s.prox + 3 * p;
-    int *d_sweeps = reinterpret_cast<int *>(s.prox + 4 * p);
+    // the score and beta are where the evaluation left them; D goes to pinned host memory
+    double *d_g = s.vec + p, *d_beta = s.vec, *d_gam = s.prox;
+    double *hD = s.hvec + 4 * p;
+    int *d_sweeps = reinterpret_cast<int *>(s.prox + p);
     {
         const hipError_t e = hipMemcpy(d_gam, gam.data(), sizeof(double) * p, hipMemcpyHostToDevice);
         if (e != hipSuccess) return handle_hip_fail(h, e, "l1 weights");
@@ -489,8 +504,30 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
         return v;
     };
     EvalOut ev;
+    // The information matrix (while it is not kept) and the model solve, queued.  The model is
+    // solved to a thousandth of the last outer step (inexact early on), and to 1e-3 tol at the end.
+    bool info_queued = false;
+    auto solve = [&]() {
+        info_queued = !frozen || !have_h;
+        if (info_queued)
+            if (const int rc = newton_info(h)) return rc;
+        double bm = 1.0;
+        for (int j = 0; j < p; ++j) bm = std::max(bm, std::fabs(beta[j]));
+        const double inner_tol = std::max(1e-3 * h->opt.tol * bm, iters ? 1e-3 * last_step : 1e-3 * bm);
+        (void)hipEventRecord(s.ev[4], h->stream);
+        if (prox_model_solve(s.info, p, d_g, d_beta, d_gam, s.free_col, inner_tol, 1000, hD, d_sweeps, h->stream) != 0)
+            return handle_fail(h, COX_EDEVICE, "proximal model solve");
+        (void)hipEventRecord(s.ev[5], h->stream);
+        return COX_OK;
+    };
     while (iters < h->opt.max_iter) {
-        int rc = newton_eval(h, beta.data(), !frozen || !have_free, ev);
+        const bool want_xbar = !frozen || !have_free;
+        int rc = newton_eval_launch(h, beta.data(), want_xbar);
+        // the solve does not wait for the host to see the objective; a step that is then halved
+        // throws it away
+        const bool ahead = have_free;
+        if (rc == COX_OK && ahead) rc = solve();
+        if (rc == COX_OK) rc = newton_eval_finish(h, want_xbar, ev);
         ++evals;
         if (rc != COX_OK) return rc;
         if (!have_free) {
@@ -516,37 +553,21 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
         }
         halvings = 0;
         objective = F;
-        if (!frozen || !have_h) {
-            rc = newton_info(h);
+        if (!ahead) {
+            rc = solve();
             if (rc != COX_OK) return rc;
             const hipError_t e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess) return handle_hip_fail(h, e, "information matrix");
+            if (e != hipSuccess) return handle_hip_fail(h, e, "proximal model solve");
+        }
+        if (info_queued) {
             h->prof.contractions += 1;
             h->prof.contraction_ms += elapsed_ms(s.ev[2], s.ev[3]);
             have_h = true;
         }
-        // coordinate descent on the model (device).  The model is solved to a thousandth of the
-        // last outer step (inexact early on), and to 1e-3 tol at the end
+        h->prof.solves += 1;
+        h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
+        std::memcpy(D.data(), hD, sizeof(double) * p);
         double bmax = 1.0;
-        for (int j = 0; j < p; ++j) bmax = std::max(bmax, std::fabs(beta[j]));
-        const double inner_tol = std::max(1e-3 * h->opt.tol * bmax, iters ? 1e-3 * last_step : 1e-3 * bmax);
-        {
-            hipError_t e = hipMemcpyAsync(d_g, ev.grad.data(), sizeof(double) * p, hipMemcpyHostToDevice, h->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(d_beta, beta.data(), sizeof(double) * p, hipMemcpyHostToDevice, h->stream);
-            if (e == hipSuccess) e = hipEventRecord(s.ev[4], h->stream);
-            if (e == hipSuccess &&
-                prox_model_solve(s.info, p, d_g, d_beta, d_gam, s.free_col, inner_tol, 1000, d_D, d_sweeps,
-                                 h->stream) != 0)
-                e = hipErrorLaunchFailure;
-            if (e == hipSuccess) e = hipEventRecord(s.ev[5], h->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(D.data(), d_D, sizeof(double) * p, hipMemcpyDeviceToHost, h->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess) return handle_hip_fail(h, e, "proximal model solve");
-            h->prof.solves += 1;
-            h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
-        }
         prev = beta;
         obj_prev = F;
         double step = 0.0;
@@ -614,13 +635,29 @@ int newton_fit(cox_handle *h, const double *beta0, double *beta_out, cox_fit_inf
     std::vector<double> beta(p, 0.0), prev(p, 0.0), dx(p, 0.0);
     if (beta0) std::memcpy(beta.data(), beta0, sizeof(double) * p);
     std::vector<uint8_t> freec(p, 1);
-    double *d_grad = s.vec + p, *d_dx = s.vec + 4 * p;
+    double *d_grad = s.vec + p, *hdx = s.hvec + 4 * p;   // the solve writes dx and its status to pinned host memory
+    int *hstatus = reinterpret_cast<int *>(s.hvec + 5 * p + kScalSlots + 1);
     bool frozen = false, have_free = false, converged = false;
     double obj_prev = INFINITY, last_step = 0.0, objective = 0.0;
     int iters = 0, evals = 0, halvings = 0;
     EvalOut ev;
+    auto solve = [&]() {
+        if (!frozen)
+            if (const int rc1 = newton_info(h)) return rc1;
+        (void)hipEventRecord(s.ev[4], h->stream);
+        if (chol_solve(s.info, p, d_grad, s.free_col, frozen ? 1 : 0, hdx, hstatus, h->stream) != 0)
+            return handle_fail(h, COX_EDEVICE, "Cholesky launch");
+        (void)hipEventRecord(s.ev[5], h->stream);
+        return COX_OK;
+    };
     while (iters < h->opt.max_iter) {
-        rc = newton_eval(h, beta.data(), !frozen || !have_free, ev);
+        const bool want_xbar = !frozen || !have_free;
+        rc = newton_eval_launch(h, beta.data(), want_xbar);
+        // information matrix and solve do not wait for the host to see the objective; a step that
+        // is then halved throws them away
+        const bool ahead = have_free;
+        if (rc == COX_OK && ahead) rc = solve();
+        if (rc == COX_OK) rc = newton_eval_finish(h, want_xbar, ev);
         ++evals;
         if (rc != COX_OK) return rc;
         if (!have_free) {
@@ -640,26 +677,18 @@ int newton_fit(cox_handle *h, const double *beta0, double *beta_out, cox_fit_inf
         }
         halvings = 0;
         objective = ev.objective;
-        if (!frozen) {
-            rc = newton_info(h);
+        if (!ahead) {
+            rc = solve();
             if (rc != COX_OK) return rc;
+            const hipError_t e = hipStreamSynchronize(h->stream);
+            if (e != hipSuccess) return handle_hip_fail(h, e, "Cholesky solve");
         }
-        (void)hipEventRecord(s.ev[4], h->stream);
-        if (chol_solve(s.info, p, d_grad, s.free_col, frozen ? 1 : 0, d_dx, s.status, h->stream) != 0)
-            return handle_fail(h, COX_EDEVICE, "Cholesky launch");
-        (void)hipEventRecord(s.ev[5], h->stream);
-        int *hstatus = reinterpret_cast<int *>(s.hvec + 5 * p + kScalSlots + 1);
-        double *hdx = s.hvec + 4 * p;
-        hipError_t e = hipMemcpyAsync(hdx, d_dx, sizeof(double) * p, hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(hstatus, s.status, sizeof(int), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (!frozen) {
             h->prof.contractions += 1;
             h->prof.contraction_ms += elapsed_ms(s.ev[2], s.ev[3]);
         }
         h->prof.solves += 1;
         h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
-        if (e != hipSuccess) return handle_hip_fail(h, e, "Cholesky solve");
         const int status = *hstatus;
         std::memcpy(dx.data(), hdx, sizeof(double) * p);
         if (status) return handle_fail(h, COX_ENUMERIC, "the information matrix is not positive definite");

@@ -64,7 +64,22 @@ __global__ __launch_bounds__(kQBlock) void event_sums_kernel(const double *__res
     const int j = blockIdx.x;
     const double *xj = x + (int64_t)j * ld;
     double acc = 0.0;
-    for (int64_t r = threadIdx.x; r < ld; r += kQBlock)
+    // 8 rows' loads in flight, added in row order (a memory round trip per row took 48 us for 80 rows)
+    constexpr int kAhead = 8;
+    int64_t r = threadIdx.x;
+    for (; r + (kAhead - 1) * kQBlock < ld; r += kAhead * kQBlock) {
+        double v[kAhead];
+        uint32_t m[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            m[i] = meta[r + i * kQBlock];
+            v[i] = xj[r + i * kQBlock];
+        }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (m[i] & kEventBit) acc += v[i];
+    }
+    for (; r < ld; r += kQBlock)
         if (meta[r] & kEventBit) acc += xj[r];
     s[threadIdx.x] = acc;
     __syncthreads();
