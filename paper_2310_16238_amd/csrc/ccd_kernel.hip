@@ -1086,50 +1086,109 @@ __global__ __launch_bounds__(256) void ccd_prepare_kernel(uint32_t *words, int64
 
 constexpr int kScanBlock = 1024;
 
-template <int IPT>
-__global__ __launch_bounds__(kScanBlock) void segscan_kernel(const double *a, const uint8_t *head,
-                                                             double *out, int64_t n, Packet *aggp,
-                                                             SyncCtl *ctl)
+// Where one scan's workgroups meet.  The scan is an ordinary launch: a workgroup takes the next
+// tile by a ticket, so every tile it waits for belongs to a workgroup that has already started
+// (and publishes its aggregate before it waits itself).  Tickets and epochs go on from call to
+// call on the same words, so nothing is cleared between.
+struct ScanSync {
+    SyncCtl *ctl;            // abort; pad[0]: the ticket counter
+    Packet *agg;             // one packet per tile
+    uint32_t epoch, ticket0; // of this call
+    uint32_t *host_abort;    // set when a wait has timed out (may be NULL)
+};
+
+// VEC: a and out are 16-byte aligned and head is IPT-byte aligned, so that a whole tile's rows move
+// 16 bytes per access (8-byte accesses IPT * 8 bytes apart touch every line IPT times).
+template <int IPT, bool VEC>
+__global__ __launch_bounds__(kScanBlock) void segscan_kernel(const double *a, const uint8_t *head, double *out,
+                                                             int64_t n, ScanSync S)
 {
-    const PacketArray agg = packet_array(aggp, sizeof(Packet) * gridDim.x);
+    const PacketArray agg = packet_array(S.agg, sizeof(Packet) * gridDim.x);
     constexpr int NW = kScanBlock / kWave;
     __shared__ SegVal<1> s_wtot[NW];
     __shared__ SegVal<1> s_win[kMaxGroups / kWave];
-    __shared__ int s_abort;
-    const int b = blockIdx.x, t = threadIdx.x;
-    const int lane = t & (kWave - 1), w = t / kWave;
+    __shared__ int s_abort, s_tile;
+    const int t = threadIdx.x;
+    if (t == 0) {
+        s_abort = 0;
+        s_tile = (int)(__hip_atomic_fetch_add(&S.ctl->pad[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - S.ticket0);
+    }
+    __syncthreads();
+    const int b = __builtin_amdgcn_readfirstlane(s_tile);
     const int64_t tile0 = (int64_t)b * kScanBlock * IPT;
     const int64_t row0 = tile0 + (int64_t)t * IPT;
+    const bool whole = VEC && tile0 + kScanBlock * IPT <= n;
     SegVal<1> e[IPT];
     SegVal<1> tagg = seg_identity<1>();
+    if (whole) {
+        double v[IPT];
+        load_rows<IPT>(v, a + row0);
+        uint32_t h[IPT];
+        if constexpr (IPT == 16) {
+            const uint4 w = *reinterpret_cast<const uint4 *>(head + row0);
+            const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const int64_t r = row0 + i;
-        if (r < n) {
-            e[i].f = (r == 0 || head[r] != 0) ? 1u : 0u;
-            e[i].v[0] = a[r];
+            for (int i = 0; i < IPT; ++i) h[i] = (ws[i / 4] >> (8 * (i % 4))) & 0xffu;
+        } else if constexpr (IPT == 8) {
+            const uint2 w = *reinterpret_cast<const uint2 *>(head + row0);
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) h[i] = ((i < 4 ? w.x : w.y) >> (8 * (i % 4))) & 0xffu;
+        } else if constexpr (IPT == 4) {
+            const uint32_t w = *reinterpret_cast<const uint32_t *>(head + row0);
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) h[i] = (w >> (8 * i)) & 0xffu;
         } else {
-            e[i].f = 1u;
-            e[i].v[0] = 0.0;
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) h[i] = head[row0 + i];
         }
-        tagg = seg_combine(tagg, e[i]);
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            e[i].f = (row0 + i == 0 || h[i] != 0) ? 1u : 0u;
+            e[i].v[0] = v[i];
+            tagg = seg_combine(tagg, e[i]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            const int64_t r = row0 + i;
+            if (r < n) {
+                e[i].f = (r == 0 || head[r] != 0) ? 1u : 0u;
+                e[i].v[0] = a[r];
+            } else {
+                e[i].f = 1u;
+                e[i].v[0] = 0.0;
+            }
+            tagg = seg_combine(tagg, e[i]);
+        }
     }
-    if (t == 0) s_abort = 0;
-    const uint32_t epoch = 1;
     SegVal<1> btot;
     SegVal<1> exc = block_exclusive_scan<1, NW>(tagg, s_wtot, btot);
-    if (t == 0) publish_aggregate<1>(agg, b, btot, epoch, false);
+    if (t == 0) publish_aggregate<1>(agg, b, btot, S.epoch, false);
     const bool tile_head = tile0 >= n || tile0 == 0 || head[tile0] != 0;
     if (!tile_head) {
         SegVal<1> carry;
-        if (!look_back<1>(b, epoch, agg, ctl, s_win, &s_abort, carry)) return;
+        if (!look_back<1>(b, S.epoch, agg, S.ctl, s_win, &s_abort, carry)) {
+            if (t == 0 && S.host_abort) __hip_atomic_store(S.host_abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            return;
+        }
         exc = seg_combine(carry, exc);
     }
     SegVal<1> run = exc;
+    if (whole && IPT % 2 == 0) {
+        double o[IPT];
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        run = seg_combine(run, e[i]);
-        if (row0 + i < n) out[row0 + i] = run.v[0];
+        for (int i = 0; i < IPT; ++i) {
+            run = seg_combine(run, e[i]);
+            o[i] = run.v[0];
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < IPT; i += 2) *reinterpret_cast<double2 *>(out + row0 + i) = double2{o[i], o[i + 1]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            run = seg_combine(run, e[i]);
+            if (row0 + i < n) out[row0 + i] = run.v[0];
+        }
     }
 }
 
@@ -1257,49 +1316,165 @@ int launch_ccd(const LaunchShape &shape, const CcdLaunch &L, hipStream_t stream,
     return (int)hipSuccess;
 }
 
+namespace {
+
+constexpr size_t kScanScratchBytes = 256 + sizeof(Packet) * kMaxGroups;
+static_assert(sizeof(SyncCtl) <= 256, "control block");
+
+// Rows per thread and workgroups for n rows; 0 rows: too long for one workgroup per compute unit.
+int scan_shape(int64_t n, int cus, int64_t *grid)
+{
+    for (int c : {1, 2, 4, 8, 16}) {
+        *grid = (n + (int64_t)kScanBlock * c - 1) / ((int64_t)kScanBlock * c);
+        if (*grid <= cus && *grid <= kMaxGroups) return c;
+    }
+    return 0;
+}
+
+template <int IPT>
+void launch_segscan_ipt(unsigned grid, const double *a, const uint8_t *head, double *b, int64_t n, const ScanSync &S,
+                        hipStream_t stream)
+{
+    const bool vec = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(head) % IPT == 0;
+    if (vec) segscan_kernel<IPT, true><<<grid, kScanBlock, 0, stream>>>(a, head, b, n, S);
+    else segscan_kernel<IPT, false><<<grid, kScanBlock, 0, stream>>>(a, head, b, n, S);
+}
+
+hipError_t launch_segscan(int ipt, unsigned grid, const double *a, const uint8_t *head, double *b, int64_t n,
+                          const ScanSync &S, hipStream_t stream)
+{
+    switch (ipt) {
+    case 1: launch_segscan_ipt<1>(grid, a, head, b, n, S, stream); break;
+    case 2: launch_segscan_ipt<2>(grid, a, head, b, n, S, stream); break;
+    case 4: launch_segscan_ipt<4>(grid, a, head, b, n, S, stream); break;
+    case 8: launch_segscan_ipt<8>(grid, a, head, b, n, S, stream); break;
+    default: launch_segscan_ipt<16>(grid, a, head, b, n, S, stream); break;
+    }
+    return hipGetLastError();
+}
+
+ScanSync scan_sync(void *base, uint32_t epoch, uint32_t ticket0, uint32_t *host_abort)
+{
+    char *cb = static_cast<char *>(base);
+    return ScanSync{reinterpret_cast<SyncCtl *>(cb), reinterpret_cast<Packet *>(cb + 256), epoch, ticket0, host_abort};
+}
+
+constexpr int kMaxDevices = 64;
+
+}  // namespace
+
+// ------------------------------------------------------------------ scan slots
+//
+// The synchronisation words of cox_segscan_f64: kScanSlots sets in the library's device memory
+// (139 KB per GPU), one held by each call while it runs, so calls on several threads and streams
+// do not meet.  A call that finds all of them taken allocates its own.  With an allocation, a clear,
+// a cooperative launch, a copy of the abort word and a release on every call a scan of 1e6 rows
+// took 61 us, now 20, most of it the launch and the wait for it.
+constexpr int kScanSlots = 32;
+static __device__ __align__(256) unsigned char scan_slots[kScanSlots * kScanScratchBytes];
+
+namespace {
+
+struct ScanSlot {
+    bool taken = false, broken = false;   // broken: a wait timed out or the device failed; not used again
+    uint32_t epoch = 0, ticket = 0;       // of the last call; the ticket counter's value
+};
+
+struct ScanSlots {
+    std::mutex mu;
+    void *base[kMaxDevices] = {};
+    ScanSlot slot[kMaxDevices][kScanSlots];
+    uint32_t *aborts = nullptr;           // pinned, one word per device and slot
+};
+
+ScanSlots &scan_slot_table()
+{
+    static ScanSlots *t = new ScanSlots;
+    return *t;
+}
+
+// A free slot of the current device, or -1.
+int take_scan_slot(int dev, void **base, uint32_t **host_abort)
+{
+    ScanSlots &T = scan_slot_table();
+    std::lock_guard<std::mutex> lock(T.mu);
+    if (!T.aborts) {
+        void *p = nullptr;
+        const size_t bytes = sizeof(uint32_t) * kMaxDevices * kScanSlots;
+        if (hipHostMalloc(&p, bytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        T.aborts = static_cast<uint32_t *>(p);
+        for (int i = 0; i < kMaxDevices * kScanSlots; ++i) T.aborts[i] = 0u;
+    }
+    if (!T.base[dev] &&
+        (hipGetSymbolAddress(&T.base[dev], HIP_SYMBOL(scan_slots)) != hipSuccess || !T.base[dev])) {
+        (void)hipGetLastError();
+        T.base[dev] = nullptr;
+        return -1;
+    }
+    for (int k = 0; k < kScanSlots; ++k) {
+        ScanSlot &s = T.slot[dev][k];
+        if (s.taken || s.broken) continue;
+        s.taken = true;
+        if (++s.epoch == 0u) ++s.epoch;   // packets start out with epoch 0
+        *base = static_cast<char *>(T.base[dev]) + (size_t)k * kScanScratchBytes;
+        *host_abort = T.aborts + dev * kScanSlots + k;
+        return k;
+    }
+    return -1;
+}
+
+void release_scan_slot(int dev, int k, bool ok)
+{
+    ScanSlots &T = scan_slot_table();
+    std::lock_guard<std::mutex> lock(T.mu);
+    T.slot[dev][k].broken = !ok;
+    T.slot[dev][k].taken = false;
+}
+
+}  // namespace
+
 int segscan_f64(const double *a, const uint8_t *head, double *b, int64_t n, hipStream_t stream)
 {
     if (n < 0 || (n > 0 && (!a || !head || !b))) return -1;
     if (n == 0) return 0;
-    int cus = 0;
-    if (device_cus(&cus) != (int)hipSuccess || cus <= 0) return -3;
-    const int ipts[] = {1, 2, 4, 8, 16};
-    int ipt = 0;
+    int cus = 0, dev = -1;
+    if (device_cus(&cus) != (int)hipSuccess || cus <= 0 || hipGetDevice(&dev) != hipSuccess) return -3;
     int64_t grid = 0;
-    for (int c : ipts) {
-        grid = (n + (int64_t)kScanBlock * c - 1) / ((int64_t)kScanBlock * c);
-        if (grid <= cus && grid <= kMaxGroups) {
-            ipt = c;
-            break;
-        }
-    }
+    const int ipt = scan_shape(n, cus, &grid);
     if (!ipt) return -5;
-    const size_t bytes = up256(sizeof(SyncCtl)) + up256(sizeof(Packet) * (size_t)grid);
-    void *scratch = nullptr;
-    if (hipMalloc(&scratch, bytes) != hipSuccess) return -2;
-    char *cb = static_cast<char *>(scratch);
-    SyncCtl *ctl = reinterpret_cast<SyncCtl *>(cb);
-    Packet *agg = reinterpret_cast<Packet *>(cb + up256(sizeof(SyncCtl)));
-    int rc = 0;
-    hipError_t e = hipMemsetAsync(scratch, 0, bytes, stream);
-    if (e == hipSuccess) {
-        void *args[] = {(void *)&a, (void *)&head, (void *)&b, (void *)&n, (void *)&agg, (void *)&ctl};
-        const void *fn = nullptr;
-        switch (ipt) {
-        case 1: fn = reinterpret_cast<const void *>(&segscan_kernel<1>); break;
-        case 2: fn = reinterpret_cast<const void *>(&segscan_kernel<2>); break;
-        case 4: fn = reinterpret_cast<const void *>(&segscan_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void *>(&segscan_kernel<8>); break;
-        default: fn = reinterpret_cast<const void *>(&segscan_kernel<16>); break;
+    void *base = nullptr;
+    uint32_t *host_abort = nullptr;
+    // (a stream that is being captured cannot wait for its result: that call is refused further down)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool plain = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+    if (!plain) (void)hipGetLastError();
+    const int k = plain && dev >= 0 && dev < kMaxDevices ? take_scan_slot(dev, &base, &host_abort) : -1;
+    if (k >= 0) {
+        ScanSlot &slot = scan_slot_table().slot[dev][k];   // ours until released
+        hipError_t e = launch_segscan(ipt, (unsigned)grid, a, head, b, n,
+                                      scan_sync(base, slot.epoch, slot.ticket, host_abort), stream);
+        if (e == hipSuccess) {
+            slot.ticket += (uint32_t)grid;
+            e = hipStreamSynchronize(stream);
         }
-        e = hipLaunchCooperativeKernel(fn, dim3((unsigned)grid), dim3(kScanBlock), args, 0, stream);
+        const bool ok = e == hipSuccess && __atomic_load_n(host_abort, __ATOMIC_ACQUIRE) == 0u;
+        release_scan_slot(dev, k, ok);
+        return ok ? 0 : -3;
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    void *scratch = nullptr;
+    if (hipMalloc(&scratch, kScanScratchBytes) != hipSuccess) return -2;
+    const ScanSync S = scan_sync(scratch, 1u, 0u, nullptr);
     uint32_t aborted = 0;
-    if (e == hipSuccess) e = hipMemcpy(&aborted, &ctl->abort, sizeof(uint32_t), hipMemcpyDeviceToHost);
-    if (e != hipSuccess || aborted) rc = -3;
+    hipError_t e = hipMemsetAsync(scratch, 0, kScanScratchBytes, stream);
+    if (e == hipSuccess) e = launch_segscan(ipt, (unsigned)grid, a, head, b, n, S, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = hipMemcpy(&aborted, &S.ctl->abort, sizeof(uint32_t), hipMemcpyDeviceToHost);
     (void)hipFree(scratch);
-    return rc;
+    return (e != hipSuccess || aborted) ? -3 : 0;
 }
 
 // ------------------------------------------------------------------ the scan without allocation
@@ -1308,13 +1483,10 @@ int segscan_f64(const double *a, const uint8_t *head, double *b, int64_t n, hipS
 // packet per workgroup (at most kMaxGroups), in library-owned device memory that
 // exists once per GPU for the life of the process.  Host code never uses this name
 // as an address: its per-device address comes from hipGetSymbolAddress.
-constexpr size_t kNoAllocScratchBytes = 256 + sizeof(Packet) * kMaxGroups;
-static_assert(sizeof(SyncCtl) <= 256, "control block");
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScanScratchBytes];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
 
@@ -1352,44 +1524,21 @@ int segscan_f64_noalloc(const double *a, const uint8_t *head, double *b, int64_t
     if (n == 0) return 0;
     int cus = 0;
     if (device_cus(&cus) != (int)hipSuccess || cus <= 0) return -3;
-    const int ipts[] = {1, 2, 4, 8, 16};
-    int ipt = 0;
     int64_t grid = 0;
-    for (int c : ipts) {
-        grid = (n + (int64_t)kScanBlock * c - 1) / ((int64_t)kScanBlock * c);
-        if (grid <= cus && grid <= kMaxGroups) {
-            ipt = c;
-            break;
-        }
-    }
+    const int ipt = scan_shape(n, cus, &grid);
     if (!ipt) return -5;
     void *base = nullptr;
     if (scratch_address(&base) != 0) return -3;
-    const size_t bytes = up256(sizeof(SyncCtl)) + up256(sizeof(Packet) * (size_t)grid);
-    if (bytes > kNoAllocScratchBytes) return -5;
-    char *cb = static_cast<char *>(base);
-    SyncCtl *ctl = reinterpret_cast<SyncCtl *>(cb);
-    Packet *agg = reinterpret_cast<Packet *>(cb + up256(sizeof(SyncCtl)));
+    const ScanSync S = scan_sync(base, 1u, 0u, nullptr);
     // the previous call's packets carry the same epoch: clear them before this scan reads any
-    const int words = (int)(bytes / sizeof(uint32_t));
+    const int words = (int)((256 + sizeof(Packet) * (size_t)grid) / sizeof(uint32_t));
     hipLaunchKernelGGL(zero_words_kernel, dim3((words + 255) / 256), dim3(256), 0, stream,
                        reinterpret_cast<uint32_t *>(base), words);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        void *args[] = {(void *)&a, (void *)&head, (void *)&b, (void *)&n, (void *)&agg, (void *)&ctl};
-        const void *fn = nullptr;
-        switch (ipt) {
-        case 1: fn = reinterpret_cast<const void *>(&segscan_kernel<1>); break;
-        case 2: fn = reinterpret_cast<const void *>(&segscan_kernel<2>); break;
-        case 4: fn = reinterpret_cast<const void *>(&segscan_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void *>(&segscan_kernel<8>); break;
-        default: fn = reinterpret_cast<const void *>(&segscan_kernel<16>); break;
-        }
-        e = hipLaunchCooperativeKernel(fn, dim3((unsigned)grid), dim3(kScanBlock), args, 0, stream);
-    }
+    if (e == hipSuccess) e = launch_segscan(ipt, (unsigned)grid, a, head, b, n, S, stream);
     uint32_t aborted = 0;
     if (e == hipSuccess)
-        e = hipMemcpyAsync(&aborted, &ctl->abort, sizeof(uint32_t), hipMemcpyDeviceToHost, stream);
+        e = hipMemcpyAsync(&aborted, &S.ctl->abort, sizeof(uint32_t), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     return (e != hipSuccess || aborted) ? -3 : 0;
 }
