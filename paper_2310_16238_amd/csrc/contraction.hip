@@ -254,266 +254,514 @@ __global__ __launch_bounds__(64 * kRedWaves) void syrk_reduce_kernel(const doubl
     }
 }
 
-// One workgroup: A (p x p, row-major, symmetric positive definite on the free
-// columns) is overwritten by its Cholesky factor L (lower triangle) unless
-// `factored`; then dx = -A^{-1} g on the free columns, 0 on the others.
-// status[0] = 1 if a pivot was not positive.
-__global__ __launch_bounds__(256) void chol_solve_kernel(double *A, int p, const double *g, const uint8_t *free_col,
-                                                         int factored, double *dx, int *status)
+// Newton step: A (p x p, symmetric, restricted to the free columns: the others become unit
+// rows) is factored as U'U unless `factored`, U overwriting A's upper triangle; then
+// dx = -A^{-1} g on the free columns, 0 on the others.  status[0] = 1 if a pivot was not
+// positive (that pivot is stored as -1).
+//
+// A single chain of p pivots bounds it, and around it the accesses between dependent steps.
+// Up to kCholTail columns the packed triangle stays in one workgroup's LDS: 16-column panels, a
+// wave factoring the diagonal block in registers, a thread per column for the rows to its
+// right, and the rest updated by v_mfma_f64_16x16x4_f64 while the first wave already factors
+// the next diagonal block.  Larger matrices are cut down to that by 64-column panels, two
+// launches each over all tiles of what is left.  Before (one workgroup on global memory, a
+// division per pivot and per solve step; beyond 512 columns unblocked) -> now, us by events:
+// p = 20: 29 -> 18, 64: 77 -> 32, 200: 312 -> 120 (78 of it the factor, 26 the solves), 500:
+// 1642 -> 403, 1000: 306,000 -> 1005.
+constexpr int kCholTail = 200;   // 8 * (200 * 201 / 2 + 16 + 200) bytes of the 160 KB
+constexpr int kPan = 16, kBlk = 64;
+
+__device__ __forceinline__ void wave_order()
 {
-    extern __shared__ double sy[];   // [p]
-    __shared__ double s_piv;
-    __shared__ int s_bad;
-    const int t = threadIdx.x;
-    if (t == 0) s_bad = 0;
-    if (!factored) {
-        for (int64_t e = t; e < (int64_t)p * p; e += 256) {
-            const int i = (int)(e / p), j = (int)(e % p);
-            if (!free_col[i] || !free_col[j]) A[e] = (i == j) ? 1.0 : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 1 / sqrt(d) and sqrt(d) to about an ulp for 0 < d < 1e300: the hardware estimate, two Newton
+// steps, and one for the root (a division and a root are several times as long a chain).
+__device__ __forceinline__ void pivot_root(double d, double &root, double &inv)
+{
+    d = fmin(d, 1e300);   // an overflowed diagonal takes its row and column out
+    double y = __builtin_amdgcn_rsq(d);
+    const double h = -0.5 * d;
+    y = fma(y, fma(h * y, y, 0.5), y);
+    y = fma(y, fma(h * y, y, 0.5), y);
+    const double r = d * y;
+    root = fma(0.5 * y, fma(-r, r, d), r);
+    inv = y;
+}
+
+// An index that the compiler does not follow from one phase to the next: it would keep every
+// address of every phase in a register of its own.
+__device__ __forceinline__ int opaque(int x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// Element (j, i), i >= j, of a packed upper triangle of order n: (j + 1, i) is n - 1 - j on.
+__device__ __forceinline__ int tri(int j, int i, int n) { return j * n - j * (j + 1) / 2 + i; }
+
+// The diagonal block at c0 (nb <= 16 columns) of the packed triangle T, by one wave: lane i
+// holds column c0 + i.  Entries below the diagonal or beyond nb hold whatever is there (reads stay
+// within kTriPad doubles of the triangle): nothing that is stored depends on them.
+constexpr int kTriPad = 16;
+
+__device__ __forceinline__ void factor_diagonal(double *T, int n, int c0, double *s_inv)
+{
+    const int lane = threadIdx.x & (kWaveC - 1), l16 = lane < kPan ? lane : kPan - 1;
+    c0 = opaque(c0);
+    const int nb = n - c0 < kPan ? n - c0 : kPan;
+    double D[kPan];
+    {
+        int at = tri(c0, c0 + l16, n);
+#pragma unroll
+        for (int c = 0; c < kPan; at += c + 1 < nb ? n - 1 - c0 - c : 0, ++c) D[c] = T[at];
+    }
+#pragma unroll
+    for (int k = 0; k < kPan; ++k) {
+        const double d = lane_value(D[k], k);
+        double root, inv;
+        pivot_root(d, root, inv);
+        if (!(d > 0.0)) root = -1.0;   // what is computed from here on is not used
+        if (lane == 0) s_inv[k] = inv;
+        D[k] = lane == k ? root : D[k] * inv;
+#pragma unroll
+        for (int q = k + 1; q < kPan; ++q) {
+            D[q] = fma(-D[k], lane_value(D[k], q), D[q]);
+            asm volatile("" : "+v"(D[q]));   // now: put off, the steps' rows would not fit in scalar registers
         }
-        __syncthreads();
-        for (int k = 0; k < p; ++k) {
-            if (t == 0) {
-                double d = A[(int64_t)k * p + k];
-                if (!(d > 0.0)) {
-                    s_bad = 1;
-                    d = 1.0;
+    }
+    int at = tri(opaque(c0), c0 + lane, n);
+    const int last = lane < nb ? lane : -1;
+#pragma unroll
+    for (int c = 0; c < kPan; at += n - 1 - c0 - c, ++c)
+        if (c <= last) T[at] = D[c];
+}
+
+// The packed triangle T (order n, in LDS, complete before the call) becomes its factor.
+__device__ __forceinline__ void factor_packed(double *T, int n, double *s_inv)
+{
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWaveC), lane = t & (kWaveC - 1), waves = blockDim.x / kWaveC;
+    const int r16 = lane & 15, kq = lane >> 4;
+    for (int r0 = 0;; r0 += kPan) {
+        if (r0 > 0) {
+            const int c0 = r0 - kPan;
+            // the panel's rows right of the block: U11' x = a, a column per thread
+            for (int i = r0 + t; i < n; i += blockDim.x) {
+                double a[kPan];
+                const int cc = opaque(c0);
+                int at = tri(cc, i, n);
+#pragma unroll
+                for (int c = 0; c < kPan; at += n - 1 - cc - c, ++c) a[c] = T[at];
+                const double *row = T + tri(cc, cc, n);   // row[q]: entry (c0 + c, c0 + q)
+#pragma unroll
+                for (int c = 0; c < kPan; row += n - 1 - cc - c, ++c) {
+                    a[c] *= s_inv[c];
+#pragma unroll
+                    for (int q = c + 1; q < kPan; ++q) a[q] = fma(-row[q], a[c], a[q]);
+                    if (c % 4 == 3) asm volatile("" ::: "memory");   // all rows' reads would not fit in registers
                 }
-                s_piv = sqrt(d);
-                A[(int64_t)k * p + k] = s_piv;
-            }
-            __syncthreads();
-            const double piv = s_piv;
-            for (int i = k + 1 + t; i < p; i += 256) A[(int64_t)i * p + k] /= piv;
-            __syncthreads();
-            const int m = p - k - 1;
-            for (int64_t e = t; e < (int64_t)m * m; e += 256) {
-                const int i = k + 1 + (int)(e / m), j = k + 1 + (int)(e % m);
-                if (j <= i) A[(int64_t)i * p + j] -= A[(int64_t)i * p + k] * A[(int64_t)j * p + k];
+                at = tri(opaque(cc), i, n);
+#pragma unroll
+                for (int c = 0; c < kPan; at += n - 1 - cc - c, ++c) T[at] = a[c];
             }
             __syncthreads();
         }
+        // A22 -= U12' U12 in 16 x 16 tiles; operands beyond n belong to results that are not stored
+        const int nt = (n - r0 + kPan - 1) / kPan;
+        auto tile = [&](int bi, int bj) {
+            const int rb = opaque(r0), ri = rb + bi * kPan, rj = rb + bj * kPan;
+            f64x4 acc;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = ri + kq + 4 * r, col = rj + r16;
+                acc[r] = (col < n && row <= col) ? T[tri(row, col, n)] : 0.0;
+            }
+#pragma unroll
+            for (int ks = 0; ks < kPan; ks += 4) {
+                const int k = rb - kPan + ks + kq;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-T[tri(k, ri + r16, n)], T[tri(k, rj + r16, n)], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = ri + kq + 4 * r, col = rj + r16;
+                if (col < n && row <= col) T[tri(row, col, n)] = acc[r];
+            }
+        };
+        if (w == 0) {
+            if (r0 > 0) {
+                tile(0, 0);
+                wave_order();
+            }
+            factor_diagonal(T, n, r0, s_inv);
+        } else if (r0 > 0) {
+            for (int q = w; q < nt * (nt + 1) / 2; q += waves - 1) {   // tile 0 is the first wave's
+                int i = 0, rem = q;
+                while (rem >= nt - i) {
+                    rem -= nt - i;
+                    ++i;
+                }
+                tile(i, i + rem);
+            }
+        }
+        __syncthreads();
+        if (r0 + kPan >= n) return;
     }
-    for (int i = t; i < p; i += 256) sy[i] = free_col[i] ? -g[i] : 0.0;
+}
+
+// Rows and columns [r0, p) of A, p - r0 <= kCholTail: factored in LDS.  With r0 = 0 the step is
+// solved as well (from A's stored factor if `factored`).  blockDim: at least 256 threads.
+constexpr int kTailRows = 9;     // rows in flight per wave: 8 waves load 200 rows in three rounds
+constexpr int kTailThreads = 512;   // more waves would leave too few registers (the diagonal block, the rows in flight)
+
+__global__ __launch_bounds__(kTailThreads) void chol_tail_kernel(double *A, int p, int r0, const double *g,
+                                                         const uint8_t *free_col, int factored, double *dx, int *status)
+{
+    extern __shared__ double T[];   // the packed triangle, kTriPad doubles, y [n] (r0 = 0)
+    __shared__ double s_inv[kPan];
+    __shared__ int s_bad;
+    const int n = p - r0;
+    double *y = T + n * (n + 1) / 2 + kTriPad;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWaveC), lane = t & (kWaveC - 1), waves = blockDim.x / kWaveC;
+    const bool mask = r0 == 0 && !factored;   // larger matrices were masked by their first launch
+    constexpr int kQ = (kCholTail + kWaveC - 1) / kWaveC;
+    int fi[kQ];   // of column 64 q + lane
+    for (int j0 = w; j0 < n; j0 += kTailRows * waves) {
+        double v[kTailRows][kQ];
+#pragma unroll
+        for (int m = 0; m < kTailRows; ++m) {
+            const int j = j0 + m * waves < n ? j0 + m * waves : n - 1;
+            const double *row = A + (int64_t)(r0 + j) * p + r0;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int i = q * kWaveC + lane;
+                v[m][q] = 0.0;
+                if (q * kWaveC < n && (q + 1) * kWaveC > j) v[m][q] = row[i < n ? i : n - 1];
+            }
+        }
+        if (j0 == w) {
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int i = q * kWaveC + lane;
+                fi[q] = mask ? free_col[i < n ? i : n - 1] : 1;
+            }
+            if (t == 0) s_bad = 0;
+            if (t < kTriPad) T[n * (n + 1) / 2 + t] = 0.0;
+            if (r0 == 0)
+                for (int i = t; i < n; i += blockDim.x) y[i] = free_col[i] ? -g[i] : 0.0;
+        }
+#pragma unroll
+        for (int m = 0; m < kTailRows; ++m) {
+            const int j = j0 + m * waves;
+            const int fl = j < kWaveC ? fi[0] : j < 2 * kWaveC ? fi[1] : j < 3 * kWaveC ? fi[2] : fi[kQ - 1];
+            const int fj = __builtin_amdgcn_readlane(fl, j & (kWaveC - 1));
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int i = q * kWaveC + lane;
+                if (j < n && i >= j && i < n) T[tri(j, i, n)] = (fj && fi[q]) ? v[m][q] : (i == j ? 1.0 : 0.0);
+            }
+        }
+    }
+    static_assert(kQ == 4, "the row's own flag is taken from one of four registers");
     __syncthreads();
-    for (int k = 0; k < p; ++k) {          // L y = -g
-        if (t == 0) sy[k] /= A[(int64_t)k * p + k];
+    if (!factored) {
+        factor_packed(T, n, s_inv);
+        for (int j = w; j < n; j += waves)
+            for (int i = j + lane; i < n; i += kWaveC) A[(int64_t)(r0 + j) * p + r0 + i] = T[tri(j, i, n)];
+    }
+    if (r0 != 0) return;
+    __syncthreads();
+    // the diagonal becomes its inverse
+    for (int i = t; i < n; i += blockDim.x) {
+        const double d = T[tri(i, i, n)];
+        if (!(d > 0.0)) s_bad = 1;
+        T[tri(i, i, n)] = 1.0 / d;
+    }
+    __syncthreads();
+    // U' y = -g, then U x = y: 64 unknowns by one wave (an unknown per lane), the others by all
+    for (int k0 = 0; k0 < n; k0 += kBlk) {
+        const int nb = n - k0 < kBlk ? n - k0 : kBlk;
+        if (w == 0) {
+            const int i = k0 + lane;
+            double yi = lane < nb ? y[i] : 0.0;
+            const double inv = lane < nb ? T[tri(i, i, n)] : 0.0;
+            int at = tri(k0, i < n ? i : n - 1, n);
+            for (int c0 = 0; c0 < nb; c0 += kPan) {
+                double u[kPan];   // rows beyond nb: the last one again, times y = 0
+#pragma unroll
+                for (int c = 0; c < kPan; at += c0 + c + 1 < nb ? n - 1 - k0 - c0 - c : 0, ++c) u[c] = T[at];
+#pragma unroll
+                for (int c = 0; c < kPan; ++c) {
+                    const double yc = lane_value(yi * inv, c0 + c);
+                    yi = fma(lane > c0 + c ? -u[c] : 0.0, yc, yi);
+                }
+            }
+            if (lane < nb) y[i] = yi * inv;
+        }
         __syncthreads();
-        const double yk = sy[k];
-        for (int i = k + 1 + t; i < p; i += 256) sy[i] -= A[(int64_t)i * p + k] * yk;
+        for (int i = k0 + nb + t; i < n; i += blockDim.x) {
+            double acc = y[i];
+#pragma unroll 16
+            for (int c = 0; c < nb; ++c) acc = fma(-T[tri(k0 + c, i, n)], y[k0 + c], acc);
+            y[i] = acc;
+        }
         __syncthreads();
     }
-    for (int k = p - 1; k >= 0; --k) {     // L' x = y
-        if (t == 0) sy[k] /= A[(int64_t)k * p + k];
+    for (int k0 = (n - 1) / kBlk * kBlk; k0 >= 0; k0 -= kBlk) {
+        const int nb = n - k0 < kBlk ? n - k0 : kBlk;
+        if (w == 0) {
+            const int i = k0 + lane;
+            double xi = lane < nb ? y[i] : 0.0;
+            const double inv = lane < nb ? T[tri(i, i, n)] : 0.0;
+            const double *row = T + tri(i < n ? i : n - 1, k0, n);
+            for (int c0 = (nb - 1) / kPan * kPan; c0 >= 0; c0 -= kPan) {
+                double u[kPan];   // at most kTriPad - 1 entries beyond the triangle
+#pragma unroll
+                for (int c = 0; c < kPan; ++c) u[c] = row[c0 + c];
+#pragma unroll
+                for (int c = kPan - 1; c >= 0; --c) {
+                    const double xc = lane_value(xi * inv, c0 + c);
+                    xi = fma(lane < c0 + c && c0 + c < nb ? -u[c] : 0.0, xc, xi);
+                }
+            }
+            if (lane < nb) y[i] = xi * inv;
+        }
         __syncthreads();
-        const double xk = sy[k];
-        for (int i = t; i < k; i += 256) sy[i] -= A[(int64_t)k * p + i] * xk;
+        for (int i = t; i < k0; i += blockDim.x) {
+            double acc = y[i];
+            const double *row = T + tri(i, k0, n);
+#pragma unroll 16
+            for (int c = 0; c < nb; ++c) acc = fma(-row[c], y[k0 + c], acc);
+            y[i] = acc;
+        }
         __syncthreads();
     }
-    for (int i = t; i < p; i += 256) dx[i] = free_col[i] ? sy[i] : 0.0;
+    for (int i = t; i < n; i += blockDim.x) dx[i] = free_col[i] ? y[i] : 0.0;
     if (t == 0) status[0] = s_bad;
 }
 
-// Blocked variant for p <= kCholMaxP, 16-column panels, three barriers each:
-//   1. wave 0 factors the 16 x 16 diagonal block, a row per lane in registers
-//      (each scaled column goes through LDS to the lanes below it);
-//   2. every thread takes one row below the block and solves x L11' = a for it
-//      (L11 read from LDS by all lanes at once), giving the panel L21;
-//   3. all threads update the trailing lower triangle in 4 x 4 register blocks
-//      from L21 (kept in LDS): A22 -= L21 L21'.
-// Triangular solves by 32-row blocks (one wave solves the diagonal block with
-// lane shuffles).  Same contract as chol_solve_kernel.
-constexpr int kCholNB = 32, kCholThreads = 512, kCholMaxP = 512, kPanNB = 16;
-
-__global__ __launch_bounds__(kCholThreads) void chol_blocked_kernel(double *A, int p, const double *g,
-                                                                    const uint8_t *free_col, int factored,
-                                                                    double *dx, int *status)
+// One 64 x 64 tile (bi <= bj) of what is left from column r0 on: the first launch (c0 < 0) makes
+// the rows and columns that are not free unit rows, the later ones subtract the panel of rows
+// [c0, c0 + 64) = [r0 - 64, r0).  The first tile's workgroup goes on to factor it when another
+// panel follows.  Grid: the tiles; 256 threads.
+__global__ __launch_bounds__(256) void chol_tile_kernel(double *A, int p, int c0, int r0, const uint8_t *free_col,
+                                                        int panel_follows)
 {
-    // panel L21 [kPanNB][p] (column-major: entry (i, c) at c * p + i), then y at p * kCholNB
-    extern __shared__ double lds[];
-    double *pan = lds;
-    double *y = lds + (size_t)p * kCholNB;
-    __shared__ double s_l11[kPanNB][kPanNB + 1];   // the factored diagonal block, row-major
-    __shared__ double s_inv[kPanNB];                 // 1 / its diagonal
-    __shared__ double s_col[kPanNB];                 // one scaled column of the block
-    __shared__ int s_bad;
-    const int t = threadIdx.x;
-    const int lane = t & (kWaveC - 1), wv = t / kWaveC;
-    constexpr int kWaves = kCholThreads / kWaveC;
-    if (t == 0) s_bad = 0;
-    if (!factored) {
-        // rows and columns not free become unit rows
-        for (int i = wv; i < p; i += kWaves)
-            for (int j = lane; j < p; j += kWaveC)
-                if (!free_col[i] || !free_col[j]) A[(int64_t)i * p + j] = (i == j) ? 1.0 : 0.0;
-        __syncthreads();
-        for (int c0 = 0; c0 < p; c0 += kPanNB) {
-            const int nb = p - c0 < kPanNB ? p - c0 : kPanNB;
-            // 1. diagonal block: lane r holds row c0 + r (entries up to the diagonal)
-            if (wv == 0) {
-                double D[kPanNB];
-#pragma unroll
-                for (int c = 0; c < kPanNB; ++c)
-                    D[c] = (lane < nb && c <= lane) ? A[(int64_t)(c0 + lane) * p + c0 + c] : 0.0;
-#pragma unroll
-                for (int kk = 0; kk < kPanNB; ++kk) {
-                    if (kk < nb) {
-                        double d = lane_value(D[kk], kk);
-                        const bool ok = d > 0.0;
-                        if (!ok) d = 1.0;
-                        const double piv = sqrt(d), inv = 1.0 / piv;
-                        if (lane == 0) {
-                            if (!ok) s_bad = 1;
-                            s_inv[kk] = inv;
-                        }
-                        if (lane == kk) D[kk] = piv;
-                        else if (lane > kk) D[kk] *= inv;
-                        if (lane < kPanNB) s_col[lane] = D[kk];
-                        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                        for (int jj = kk + 1; jj < kPanNB; ++jj)
-                            if (jj < nb && lane >= jj) D[jj] = fma(-D[kk], s_col[jj], D[jj]);
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-                if (lane < nb) {
-#pragma unroll
-                    for (int c = 0; c < kPanNB; ++c)
-                        if (c <= lane) {
-                            s_l11[lane][c] = D[c];
-                            A[(int64_t)(c0 + lane) * p + c0 + c] = D[c];
-                        }
-                }
-            }
-            __syncthreads();
-            // 2. the rows below the block: x L11' = a, one row per thread
-            const int r0 = c0 + nb;
-            for (int i = r0 + t; i < p; i += kCholThreads) {
-                double a[kPanNB];
-                const double *row = A + (int64_t)i * p + c0;
-#pragma unroll
-                for (int c = 0; c < kPanNB; ++c) a[c] = c < nb ? row[c] : 0.0;
-#pragma unroll
-                for (int c = 0; c < kPanNB; ++c) {
-                    if (c < nb) {
-                        double v = a[c];
-#pragma unroll
-                        for (int q = 0; q < c; ++q) v = fma(-a[q], s_l11[c][q], v);
-                        a[c] = v * s_inv[c];
-                    }
-                    // keep the LDS reads of row c + 1 of L11 from being hoisted above this
-                    // point (hoisting all of them would not fit in registers)
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                double *wrow = A + (int64_t)i * p + c0;
-#pragma unroll
-                for (int c = 0; c < kPanNB; ++c)
-                    if (c < nb) {
-                        wrow[c] = a[c];
-                        pan[c * p + i] = a[c];
-                    }
-            }
-            __syncthreads();
-            // 3. trailing update of the lower triangle: A22 -= L21 L21'
-            const int m2 = p - r0;
-            if (m2 > 0) {
-                const int nb4 = (m2 + 3) / 4;
-                const int nblk = nb4 * (nb4 + 1) / 2;
-                for (int bk = t; bk < nblk; bk += kCholThreads) {
-                    // block (bi, bj), bj <= bi, in row-major order of the lower triangle
-                    int bi = (int)((sqrt(8.0 * bk + 1.0) - 1.0) * 0.5);
-                    while ((bi + 1) * (bi + 2) / 2 <= bk) ++bi;
-                    while (bi * (bi + 1) / 2 > bk) --bi;
-                    const int bj = bk - bi * (bi + 1) / 2;
-                    double acc[4][4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-                    for (int c = 0; c < nb; ++c) {
-                        double ai[4], aj[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int ii = r0 + 4 * bi + u, jj = r0 + 4 * bj + u;
-                            ai[u] = ii < p ? pan[c * p + ii] : 0.0;
-                            aj[u] = jj < p ? pan[c * p + jj] : 0.0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) acc[u][v] = fma(ai[u], aj[v], acc[u][v]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int i = r0 + 4 * bi + u, j = r0 + 4 * bj + v;
-                            if (i < p && j <= i) A[(int64_t)i * p + j] -= acc[u][v];
-                        }
-                }
-            }
-            __syncthreads();
-        }
+    __shared__ double ui[kBlk][kBlk + 1], uj[kBlk][kBlk + 1];
+    __shared__ double s_inv[kPan];
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWaveC), lane = t & (kWaveC - 1);
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int nt = (p - r0 + kBlk - 1) / kBlk;
+    int bi = 0, rem = blockIdx.x;
+    while (rem >= nt - bi) {
+        rem -= nt - bi;
+        ++bi;
     }
-    // solves: L y = -g, then L' x = y (free columns only)
-    for (int i = t; i < p; i += kCholThreads) y[i] = free_col[i] ? -g[i] : 0.0;
+    const int ri = r0 + bi * kBlk, rj = r0 + (bi + rem) * kBlk;
+    if (c0 >= 0) {
+        double vi[kBlk / 4], vj[kBlk / 4];
+#pragma unroll
+        for (int m = 0; m < kBlk / 4; ++m) {
+            const double *row = A + (int64_t)(c0 + w + 4 * m) * p;
+            vi[m] = ri + lane < p ? row[ri + lane] : 0.0;
+            vj[m] = rj + lane < p ? row[rj + lane] : 0.0;
+        }
+#pragma unroll
+        for (int m = 0; m < kBlk / 4; ++m) {
+            ui[w + 4 * m][lane] = vi[m];
+            uj[w + 4 * m][lane] = vj[m];
+        }
+        __syncthreads();
+    }
+    // wave w: rows 16 w .. 16 w + 15 of the tile
+    f64x4 acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = ri + w * kPan + kq + 4 * r, col = rj + b * kPan + r16;
+            acc[b][r] = 0.0;
+            if (col < p && row <= col) {
+                acc[b][r] = A[(int64_t)row * p + col];
+                if (c0 < 0 && !(free_col[row] && free_col[col])) acc[b][r] = row == col ? 1.0 : 0.0;
+            }
+        }
+    if (c0 >= 0) {
+#pragma unroll 4
+        for (int ks = 0; ks < kBlk; ks += 4) {
+            const double a = -ui[ks + kq][w * kPan + r16];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, uj[ks + kq][b * kPan + r16], acc[b], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    const bool factor = blockIdx.x == 0 && panel_follows;   // ri = rj = r0 and r0 + 64 < p
+    double *T = &ui[0][0];   // packed, order 64
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = ri + w * kPan + kq + 4 * r, col = rj + b * kPan + r16;
+            if (col < p && row <= col) {
+                if (factor) T[tri(row - r0, col - r0, kBlk)] = acc[b][r];
+                else A[(int64_t)row * p + col] = acc[b][r];
+            }
+        }
+    if (!factor) return;
     __syncthreads();
-    // the diagonal block's entries a lane needs are loaded into registers first
-    // (all loads in flight together), so the sequential steps wait only on shuffles
-    for (int k0 = 0; k0 < p; k0 += kCholNB) {
-        const int nb = p - k0 < kCholNB ? p - k0 : kCholNB;
-        if (wv == 0) {
-            double Lr[kCholNB];   // row k0 + lane of the block (entries up to the diagonal)
+    factor_packed(T, kBlk, s_inv);
+    for (int j = w; j < kBlk; j += 4)
+        if (lane >= j) A[(int64_t)(r0 + j) * p + r0 + lane] = T[tri(j, lane, kBlk)];
+}
+
+// The rows [c0, c0 + 64) right of their factored diagonal block: U11' X = A12, 64 columns per workgroup
+// of 256 threads.
+__global__ __launch_bounds__(256) void chol_rows_kernel(double *A, int p, int c0)
+{
+    __shared__ double U[kBlk][kBlk + 1], X[kBlk][kBlk + 1];
+    __shared__ double s_inv[kBlk];
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWaveC), lane = t & (kWaveC - 1);
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int col = c0 + kBlk + blockIdx.x * kBlk + lane;
+    double vu[kBlk / 4], vx[kBlk / 4];
 #pragma unroll
-            for (int c = 0; c < kCholNB; ++c)
-                Lr[c] = (lane < nb && c <= lane) ? A[(int64_t)(k0 + lane) * p + k0 + c] : 1.0;
+    for (int m = 0; m < kBlk / 4; ++m) {
+        const double *row = A + (int64_t)(c0 + w + 4 * m) * p;
+        vu[m] = lane >= w + 4 * m ? row[c0 + lane] : 0.0;
+        vx[m] = col < p ? row[col] : 0.0;
+    }
+#pragma unroll
+    for (int m = 0; m < kBlk / 4; ++m) {
+        const int j = w + 4 * m;
+        U[j][lane] = vu[m];
+        X[j][lane] = vx[m];
+        if (lane == j) s_inv[j] = vu[m] > 0.0 ? 1.0 / vu[m] : 1.0;
+    }
+    __syncthreads();
+    for (int b0 = 0; b0 < kBlk; b0 += kPan) {
+        if (w == 0) {
+            double a[kPan];
+#pragma unroll
+            for (int c = 0; c < kPan; ++c) a[c] = X[b0 + c][lane];
+#pragma unroll
+            for (int c = 0; c < kPan; ++c) {
+                a[c] *= s_inv[b0 + c];
+#pragma unroll
+                for (int q = c + 1; q < kPan; ++q) a[q] = fma(-U[b0 + c][b0 + q], a[c], a[q]);
+                if (c % 4 == 3) asm volatile("" ::: "memory");
+            }
+#pragma unroll
+            for (int c = 0; c < kPan; ++c) X[b0 + c][lane] = a[c];
+        }
+        __syncthreads();
+        // the rows below, wave w the 16 columns from 16 w on
+        for (int rb = b0 + kPan; rb < kBlk; rb += kPan) {
+            f64x4 acc;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = X[rb + kq + 4 * r][w * kPan + r16];
+#pragma unroll
+            for (int ks = 0; ks < kPan; ks += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-U[b0 + ks + kq][rb + r16], X[b0 + ks + kq][w * kPan + r16],
+                                                           acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) X[rb + kq + 4 * r][w * kPan + r16] = acc[r];
+        }
+        __syncthreads();
+    }
+    if (col < p)
+#pragma unroll
+        for (int m = 0; m < kBlk / 4; ++m) A[(int64_t)(c0 + w + 4 * m) * p + col] = X[w + 4 * m][lane];
+}
+
+// U'U x = -g from the stored factor, for p > kCholTail: blocks of 64 unknowns, their diagonal
+// block staged in LDS (the next one loaded while the others are updated).
+constexpr int kSolveThreads = 1024;
+
+__global__ __launch_bounds__(kSolveThreads) void chol_solve_kernel(const double *A, int p, const double *g,
+                                                                   const uint8_t *free_col, double *dx, int *status)
+{
+    extern __shared__ double y[];   // [p]
+    __shared__ double U[kBlk][kBlk + 1];
+    __shared__ int s_bad;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWaveC), lane = t & (kWaveC - 1);
+    constexpr int kWaves = kSolveThreads / kWaveC, kM = kBlk / kWaves;
+    static_assert(kBlk == kWaveC && kBlk % kWaves == 0, "a wave stages whole rows");
+    if (t == 0) s_bad = 0;
+    for (int i = t; i < p; i += kSolveThreads) y[i] = free_col[i] ? -g[i] : 0.0;
+    double v[kM];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int m = 0; m < kM; ++m) {
+            const int j = w + kWaves * m;
+            v[m] = (k0 >= 0 && k0 + lane < p && lane >= j) ? A[(int64_t)(k0 + j) * p + k0 + lane] : (lane == j ? 1.0 : 0.0);
+        }
+    };
+    auto stage = [&]() {   // the diagonal as its inverse
+#pragma unroll
+        for (int m = 0; m < kM; ++m) {
+            const int j = w + kWaves * m;
+            if (lane == j && !(v[m] > 0.0)) s_bad = 1;
+            U[j][lane] = lane == j ? 1.0 / v[m] : v[m];
+        }
+    };
+    __syncthreads();
+    fetch(0);
+    for (int k0 = 0; k0 < p; k0 += kBlk) {
+        stage();
+        __syncthreads();
+        fetch(k0 + kBlk < p ? k0 + kBlk : k0);   // the last block is the next solve's first
+        const int nb = p - k0 < kBlk ? p - k0 : kBlk;
+        if (w == 0) {
             double yi = lane < nb ? y[k0 + lane] : 0.0;
-#pragma unroll
-            for (int c = 0; c < kCholNB; ++c) {
-                if (c < nb) {
-                    if (lane == c) yi /= Lr[c];
-                    const double yc = lane_value(yi, c);
-                    if (lane > c && lane < nb) yi = fma(-Lr[c], yc, yi);
-                }
+            const double inv = U[lane][lane];
+#pragma unroll 16
+            for (int c = 0; c < kBlk; ++c) {
+                const double u = U[c][lane];
+                yi = fma(lane > c ? -u : 0.0, lane_value(yi * inv, c), yi);
             }
-            if (lane < nb) y[k0 + lane] = yi;
+            if (lane < nb) y[k0 + lane] = yi * inv;
         }
         __syncthreads();
-        for (int i = k0 + nb + t; i < p; i += kCholThreads) {
-            const double *row = A + (int64_t)i * p + k0;
-            double s = 0.0;
-            for (int c = 0; c < nb; ++c) s = fma(row[c], y[k0 + c], s);
-            y[i] -= s;
+        // 64 columns per wave
+        for (int i = k0 + kBlk + t; i < p; i += kSolveThreads) {
+            double acc = y[i];
+#pragma unroll 16
+            for (int c = 0; c < kBlk; ++c) acc = fma(-A[(int64_t)(k0 + c) * p + i], y[k0 + c], acc);
+            y[i] = acc;
         }
-        __syncthreads();
     }
-    for (int k0 = ((p - 1) / kCholNB) * kCholNB; k0 >= 0; k0 -= kCholNB) {
-        const int nb = p - k0 < kCholNB ? p - k0 : kCholNB;
-        if (wv == 0) {
-            double Lc[kCholNB];   // column k0 + lane of the block (entries from the diagonal down)
-#pragma unroll
-            for (int c = 0; c < kCholNB; ++c)
-                Lc[c] = (lane < nb && c >= lane && c < nb) ? A[(int64_t)(k0 + c) * p + k0 + lane] : 1.0;
+    for (int k0 = (p - 1) / kBlk * kBlk; k0 >= 0; k0 -= kBlk) {
+        __syncthreads();
+        stage();
+        __syncthreads();
+        fetch(k0 - kBlk);
+        const int nb = p - k0 < kBlk ? p - k0 : kBlk;
+        if (w == 0) {
             double xi = lane < nb ? y[k0 + lane] : 0.0;
-#pragma unroll
-            for (int c = kCholNB - 1; c >= 0; --c) {
-                if (c < nb) {
-                    if (lane == c) xi /= Lc[c];
-                    const double xc = lane_value(xi, c);
-                    if (lane < c) xi = fma(-Lc[c], xc, xi);
-                }
+            const double inv = U[lane][lane];
+#pragma unroll 16
+            for (int c = kBlk - 1; c >= 0; --c) {
+                const double u = U[lane][c];
+                xi = fma(lane < c ? -u : 0.0, lane_value(xi * inv, c), xi);
             }
-            if (lane < nb) y[k0 + lane] = xi;
+            if (lane < nb) y[k0 + lane] = xi * inv;
         }
         __syncthreads();
-        for (int i = t; i < k0; i += kCholThreads) {
-            double s = 0.0;
-            for (int c = 0; c < nb; ++c) s = fma(A[(int64_t)(k0 + c) * p + i], y[k0 + c], s);
-            y[i] -= s;
+        // a row per wave, a column per lane
+        const double xc = lane < nb ? y[k0 + lane] : 0.0;
+#pragma unroll 4
+        for (int i = w; i < k0; i += kWaves) {
+            double acc = lane < nb ? A[(int64_t)i * p + k0 + lane] * xc : 0.0;
+#pragma unroll
+            for (int o = kWaveC / 2; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, kWaveC);
+            if (lane == 0) y[i] -= acc;
         }
-        __syncthreads();
     }
-    for (int i = t; i < p; i += kCholThreads) dx[i] = free_col[i] ? y[i] : 0.0;
+    __syncthreads();
+    for (int i = t; i < p; i += kSolveThreads) dx[i] = free_col[i] ? y[i] : 0.0;
     if (t == 0) status[0] = s_bad;
 }
 
@@ -1533,19 +1781,34 @@ int prox_model_solve(const double *H, int p, const double *g, const double *beta
 int chol_solve(double *A, int p, const double *g, const uint8_t *free_col, int factored, double *dx, int *status,
                hipStream_t stream)
 {
-    if (p <= kCholMaxP) {
-        const size_t lds = sizeof(double) * ((size_t)p * kCholNB + 2 * (size_t)p);
-        static bool attr = false;
-        if (!attr) {
-            const size_t most = sizeof(double) * ((size_t)kCholMaxP * kCholNB + 2 * (size_t)kCholMaxP);
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_blocked_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                return -3;
-            attr = true;
-        }
-        chol_blocked_kernel<<<1, kCholThreads, lds, stream>>>(A, p, g, free_col, factored, dx, status);
+    auto tail_lds = [](int n) { return sizeof(double) * ((size_t)n * (n + 1) / 2 + kTriPad + n); };
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_tail_kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                       (int)tail_lds(kCholTail));
+    if (attr != hipSuccess) return -3;
+    auto tail = [&](int r0) {
+        const int n = p - r0;
+        // four waves have enough tiles up to 64 columns, and their barriers are shorter
+        chol_tail_kernel<<<1, n <= kBlk ? 256 : kTailThreads, tail_lds(n), stream>>>(A, p, r0, g, free_col, factored, dx, status);
+    };
+    if (p <= kCholTail) {
+        tail(0);
     } else {
-        chol_solve_kernel<<<1, 256, sizeof(double) * (size_t)p, stream>>>(A, p, g, free_col, factored, dx, status);
+        if (!factored) {
+            auto tiles = [&](int r0) {
+                const int nt = (p - r0 + kBlk - 1) / kBlk;
+                return (unsigned)(nt * (nt + 1) / 2);
+            };
+            chol_tile_kernel<<<tiles(0), 256, 0, stream>>>(A, p, -1, 0, free_col, 1);
+            int r0 = 0;
+            while (p - r0 > kCholTail) {
+                chol_rows_kernel<<<(unsigned)((p - r0 - 1) / kBlk), 256, 0, stream>>>(A, p, r0);
+                r0 += kBlk;
+                chol_tile_kernel<<<tiles(r0), 256, 0, stream>>>(A, p, r0 - kBlk, r0, free_col, p - r0 > kCholTail);
+            }
+            tail(r0);
+        }
+        chol_solve_kernel<<<1, kSolveThreads, sizeof(double) * (size_t)p, stream>>>(A, p, g, free_col, dx, status);
     }
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
