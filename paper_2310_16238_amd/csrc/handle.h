@@ -25,7 +25,7 @@ struct NewtonState {
     uint8_t *tile_carry = nullptr; // [ntiles]
     int32_t *lasthead = nullptr;   // [ntiles]
     int32_t *agg_tiles = nullptr;  // [n_agg]
-    double *agg = nullptr;         // [ntiles][p][2]
+    double *agg = nullptr;         // [ntiles][p], [ntiles]
     double *carry = nullptr;       // [ntiles][p]
     double *colpart = nullptr;     // [ntiles][p][3]
     double *vec = nullptr;         // beta, grad, diag1, diag2, dx (p each), scal (8)

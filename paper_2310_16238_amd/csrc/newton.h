@@ -51,7 +51,7 @@ struct FullEvalArgs {
     const int32_t *lasthead = nullptr;     // [ntiles] row of the tile's last stratum head, -1 if none
     const int32_t *agg_tiles = nullptr;    // [n_agg] tiles whose successor needs a carry
     int n_agg = 0;
-    double *agg = nullptr;                 // [ntiles][p][2]: map S -> A S + B of the tile's tail rows
+    double *agg = nullptr;                 // map S -> A S + B of the tiles' tail rows: B [ntiles][p], A [ntiles]
     double *carry = nullptr;               // [ntiles][p]
     double *colpart = nullptr;             // [ntiles][p][3]
     double *grad = nullptr, *diag1 = nullptr, *diag2 = nullptr;   // [p] each

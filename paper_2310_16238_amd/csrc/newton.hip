@@ -233,51 +233,112 @@ __device__ __forceinline__ void load4(const double *p, double *v)
     v[3] = hi.y;
 }
 
-// agg[t][j] = the map S -> A S + B of the rows of tile t from its last head (or
-// its first row) to its end for the recurrence S'_r = alpha_r S'_{r-1} + u_r x_rj
-// (stored as A, B), for the tiles listed in `tiles`.
-__global__ __launch_bounds__(kWave * kColWaves) void colagg_kernel(const double *x, int64_t ld, int p, const double *alpha,
-                                                                   const double *u, const uint32_t *meta, int64_t tile,
-                                                                   const int32_t *tiles, int ntl,
-                                                                   const int32_t *lasthead, double *agg)
+// The map S -> A S + B of the rows of tile t from its last head (or its first row) to its
+// end for the recurrence S'_r = alpha_r S'_{r-1} + u_r x_rj, for the tiles listed in `tiles`.
+// Unrolled, B = sum_r W_r x_rj with W_r = u_r times the alphas after r, which no column changes:
+// colweight_kernel forms W and A, one workgroup per tile, and
+// colagg_kernel is then a product of X with it, bound by reading X (200,000 x 100: 34 us at
+// the rate of a copy).  A scan per column and tile took 79 us there, the two kernels 32.
+constexpr int kWeightBlock = 256;
+
+__global__ __launch_bounds__(kWeightBlock) void colweight_kernel(const double *alpha, const double *u, int64_t tile,
+                                                                 const int32_t *tiles, const int32_t *lasthead,
+                                                                 double *wsuf, double *taila)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kColWaves + threadIdx.x / kWave);
-    if (item >= ntl * p) return;
-    const int t = tiles[item / p], j = item % p;
+    __shared__ double s_p[2][kWeightBlock];
+    const int t = tiles[blockIdx.x], i = threadIdx.x;
     const int64_t r1 = (int64_t)(t + 1) * tile;
     const int64_t r0 = lasthead[t] >= 0 ? (int64_t)lasthead[t] : (int64_t)t * tile;
-    const double *xj = x + (int64_t)j * ld;
-    AffE acc = AffOp::id();
-    for (int64_t base = r0; base < r1; base += kWave) {
-        const int64_t r = base + lane;
-        AffE e = AffOp::id();
-        if (r < r1) e = AffE{(meta[r] & kHeadBit) ? 1u : 0u, alpha[r], u[r] * xj[r]};
-        const AffE tot = lane63_e(wave_scan_e<AffOp>(e));
-        acc = AffOp::combine(acc, tot);
+    const int64_t per = (r1 - r0 + kWeightBlock - 1) / kWeightBlock;
+    const int64_t a = r0 + i * per < r1 ? r0 + i * per : r1, e = a + per < r1 ? a + per : r1;
+    double prod = 1.0;
+    for (int64_t r = a; r < e; ++r) prod *= alpha[r];
+    s_p[0][i] = prod;
+    int cur = 0;
+    for (int o = 1; o < kWeightBlock; o *= 2, cur ^= 1) {
+        __syncthreads();
+        s_p[cur ^ 1][i] = i + o < kWeightBlock ? s_p[cur][i] * s_p[cur][i + o] : s_p[cur][i];
     }
-    if (lane == 0) {
-        agg[((int64_t)t * p + j) * 2] = acc.a;
-        agg[((int64_t)t * p + j) * 2 + 1] = acc.b;
+    __syncthreads();
+    double run = i + 1 < kWeightBlock ? s_p[cur][i + 1] : 1.0;   // the alphas after this thread's rows
+    for (int64_t r = e - 1; r >= a; --r) {
+        wsuf[r] = u[r] * run;
+        run *= alpha[r];
+    }
+    if (i == 0) taila[t] = run;
+}
+
+// One wave per tile and 4 columns.
+constexpr int kAggCols = 4;
+
+__global__ __launch_bounds__(kWave * kColWaves) void colagg_kernel(const double *x, int64_t ld, int p, const double *wsuf,
+                                                                   int64_t tile, const int32_t *tiles, int ntl,
+                                                                   const int32_t *lasthead, double *aggb)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int groups = (p + kAggCols - 1) / kAggCols;
+    const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kColWaves + threadIdx.x / kWave);
+    if (item >= ntl * groups) return;
+    const int t = tiles[item / groups], j0 = (item % groups) * kAggCols;
+    const int64_t start = (int64_t)t * tile, r1 = start + tile;
+    const int64_t r0 = lasthead[t] >= 0 ? (int64_t)lasthead[t] : start;
+    constexpr int kRows = 2 * kWave;   // two rows per lane and load
+    const double *xj[kAggCols];
+    double acc[kAggCols];
+#pragma unroll
+    for (int c = 0; c < kAggCols; ++c) {
+        xj[c] = x + (int64_t)(j0 + c < p ? j0 + c : p - 1) * ld;
+        acc[c] = 0.0;
+    }
+#pragma unroll 4
+    for (int64_t base = start + (r0 - start) / kRows * kRows; base < r1; base += kRows) {
+        const int64_t r = base + 2 * lane;
+        if (r + 1 < r1 && r >= r0) {
+            const double2 w = *reinterpret_cast<const double2 *>(wsuf + r);
+#pragma unroll
+            for (int c = 0; c < kAggCols; ++c) {
+                const double2 v = *reinterpret_cast<const double2 *>(xj[c] + r);
+                acc[c] = fma(w.y, v.y, fma(w.x, v.x, acc[c]));
+            }
+        } else {   // the pair at the last head or at an odd end
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (r + k >= r0 && r + k < r1)
+#pragma unroll
+                    for (int c = 0; c < kAggCols; ++c) acc[c] = fma(wsuf[r + k], xj[c][r + k], acc[c]);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < kAggCols; ++c) {
+#pragma unroll
+        for (int o = kWave / 2; o >= 1; o >>= 1) acc[c] += __shfl_xor(acc[c], o, kWave);
+        if (lane == 0 && j0 + c < p) aggb[(int64_t)t * p + j0 + c] = acc[c];
     }
 }
 
-// carry[t][j] = S'_j entering tile t (for tiles whose first row continues a
-// stratum).  One thread per column, tiles in order.
-__global__ __launch_bounds__(256) void colcarry_kernel(int p, int ntiles, const uint8_t *tile_carry,
-                                                       const int32_t *lasthead, const double *agg, double *carry)
+// carry[t][j] = S'_j entering tile t (for tiles whose first row continues a stratum): one
+// wave per column scans the tiles' maps, 64 at a time.  (A thread per column, tile after tile,
+// waited for memory at every one: 196 tiles 84 us, now 5.)
+__global__ __launch_bounds__(kWave * kColWaves) void colcarry_kernel(int p, int ntiles, const uint8_t *tile_carry,
+                                                                     const int32_t *lasthead, const double *taila,
+                                                                     const double *aggb, double *carry)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int j = __builtin_amdgcn_readfirstlane(blockIdx.x * kColWaves + threadIdx.x / kWave);
     if (j >= p) return;
-    double c = 0.0;
-    for (int t = 0; t < ntiles; ++t) {
-        carry[(int64_t)t * p + j] = c;
-        if (t + 1 < ntiles && tile_carry[t + 1]) {
-            const double A = agg[((int64_t)t * p + j) * 2], B = agg[((int64_t)t * p + j) * 2 + 1];
-            c = lasthead[t] >= 0 ? B : fma(A, c, B);
-        } else {
-            c = 0.0;
+    if (lane == 0) carry[j] = 0.0;
+    double c = 0.0;   // S' entering the chunk's first tile
+    for (int base = 0; base + 1 < ntiles; base += kWave) {
+        const int t = base + lane;
+        AffE e = AffOp::id();
+        if (t + 1 < ntiles) {
+            e = AffE{1u, 0.0, 0.0};
+            if (tile_carry[t + 1]) e = AffE{lasthead[t] >= 0 ? 1u : 0u, taila[t], aggb[(int64_t)t * p + j]};
         }
+        const AffE inc = wave_scan_e<AffOp>(e);
+        const double out = inc.f ? inc.b : fma(inc.a, c, inc.b);
+        if (t + 1 < ntiles) carry[(int64_t)(t + 1) * p + j] = out;
+        c = readlane63(out);
     }
 }
 
@@ -1207,10 +1268,14 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
     else
         rowweight_kernel<<<nb, kRowBlock, 0, stream>>>(A.w, A.lam, ld, A.b);
     if (A.n_agg > 0) {
-        colagg_kernel<<<(A.n_agg * A.p + kColWaves - 1) / kColWaves, kWave * kColWaves, 0, stream>>>(
-            A.x, ld, A.p, A.alpha, A.w, A.meta, A.tile, A.agg_tiles, A.n_agg, A.lasthead, A.agg);
-        colcarry_kernel<<<(A.p + 255) / 256, 256, 0, stream>>>(A.p, A.ntiles, A.tile_carry, A.lasthead, A.agg,
-                                                               A.carry);
+        double *wsuf = A.s0;   // read last by the hazards
+        const int groups = (A.p + kAggCols - 1) / kAggCols;
+        colweight_kernel<<<A.n_agg, kWeightBlock, 0, stream>>>(A.alpha, A.w, A.tile, A.agg_tiles, A.lasthead, wsuf,
+                                                               A.agg + (int64_t)A.ntiles * A.p);
+        colagg_kernel<<<(A.n_agg * groups + kColWaves - 1) / kColWaves, kWave * kColWaves, 0, stream>>>(
+            A.x, ld, A.p, wsuf, A.tile, A.agg_tiles, A.n_agg, A.lasthead, A.agg);
+        colcarry_kernel<<<(A.p + kColWaves - 1) / kColWaves, kWave * kColWaves, 0, stream>>>(
+            A.p, A.ntiles, A.tile_carry, A.lasthead, A.agg + (int64_t)A.ntiles * A.p, A.agg, A.carry);
     }
     const int grid = 8 * ((A.ntiles + 7) / 8) * ((A.p + kColWaves * kColBlock - 1) / (kColWaves * kColBlock));
 #define COXMI_COLPASS(ZT, XB, EF)                                                                              \

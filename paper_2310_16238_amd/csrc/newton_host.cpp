@@ -180,7 +180,7 @@ int newton_setup(cox_handle *h)
     }
     A.add(&s.rows, sizeof(double) * 9 * ld);
     A.add(&s.blockbuf, sizeof(double) * s.max_blocks);
-    A.add(&s.agg, sizeof(double) * 2 * (size_t)s.ntiles * p);
+    A.add(&s.agg, sizeof(double) * (size_t)s.ntiles * (p + 1));
     A.add(&s.carry, sizeof(double) * (size_t)s.ntiles * p);
     A.add(&s.colpart, sizeof(double) * 3 * (size_t)std::max(s.ntiles, s.nseg ? seg_part_slots(p, s.nseg) : 0) * p);
     A.add(&s.vec, sizeof(double) * (5 * (size_t)p + kScalSlots));
