@@ -137,32 +137,44 @@ __global__ __launch_bounds__(kSyrkThreads) void syrk_f64_kernel(const double *u,
 // r = 0..3, of its block (rows interleaved by 4).  The partials go to the 64 x 64 tile-pair
 // layout of syrk_f64_kernel (blocks below the diagonal of a diagonal tile are never
 // written, and syrk_reduce_kernel never reads them).
+//
+// Up to 256 columns the latency of a chunk's loads bounds it, then the matrix cores (100 columns:
+// 36 us of their time for 200,000 rows).  So the next chunk is loaded while one is multiplied,
+// and the kernel is built for several column counts: branches around absent row blocks and
+// blocks, 17 + 2 x 16 of them per chunk whatever the count, cost more than the work at few
+// columns.  A second LDS buffer (107 us against 93) and blocks without branches (138) did not
+// pay.  Both products and their sums, 100,000 rows, before -> now, us: 10 columns 70 -> 31, 50: 102 -> 54,
+// 150: 210 -> 161, 256: 455 -> 348.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kF64Waves = 8, kF64KC = 32;
 constexpr int kF64PerWave = 17, kF64Group = kF64Waves * kF64PerWave;   // 136 = all blocks at p <= 256
 
-// MAXB: the most 16-row blocks (16: p <= 256, staged rows 256 x 33 doubles; 32: p <= 512, 135 KB)
+// MAXB: the most 16-row blocks, each with its own registers and LDS (32: p <= 512, 135 KB).
 template <int MAXB>
 __global__ __launch_bounds__(64 * kF64Waves, 1) void syrk_f64_mfma_kernel(const double *u, int64_t ldu, int p,
                                                                          const double *c, int64_t K,
                                                                          int64_t kchunk, double *part)
 {
-    __shared__ double xs[MAXB * 16][kF64KC + 1];
+    constexpr bool kAhead = MAXB <= 16;
+    // + 4: an operand, 16 rows x 4 columns, falls on all banks alike (beyond 256 columns + 1 measured the same)
+    __shared__ double xs[MAXB * 16][kF64KC + (kAhead ? 4 : 1)];
     __shared__ double cs[kF64KC];
+    // a wave's share of one group's blocks
+    constexpr int kPW = MAXB <= 16 ? (MAXB * (MAXB + 1) / 2 + kF64Waves - 1) / kF64Waves : kF64PerWave;
     const int nb = (p + 15) / 16;
     const int nblk = nb * (nb + 1) / 2;
     const int nt = (p + kTile - 1) / kTile;
     const int npairs = nt * (nt + 1) / 2;
-    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    const int lane = threadIdx.x & 63, w = kAhead ? __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : (int)(threadIdx.x / 64);
     int s, grp;
     split_group(s, grp);
     const int q0 = grp * kF64Group;
     const int64_t k0 = (int64_t)s * kchunk;
     const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
-    int bi[kF64PerWave], bj[kF64PerWave];
-    f64x4 acc[kF64PerWave];
+    int bi[kPW], bj[kPW];
+    f64x4 acc[kPW];
 #pragma unroll
-    for (int m = 0; m < kF64PerWave; ++m) {
+    for (int m = 0; m < kPW; ++m) {
         const int q = q0 + w + kF64Waves * m;
         int i = 0, rem = q < nblk ? q : 0;
         while (rem >= nb - i) {
@@ -173,23 +185,47 @@ __global__ __launch_bounds__(64 * kF64Waves, 1) void syrk_f64_mfma_kernel(const 
         bj[m] = i + rem;
         acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
     }
-    const int rows = nb * 16;
     const int r16 = lane & 15, kq = lane >> 4;
-    for (int64_t kc = k0; kc < k1; kc += kF64KC) {
-        // stage rows x kF64KC (zero beyond p and beyond k1)
-        for (int e = threadIdx.x; e < rows * kF64KC; e += 64 * kF64Waves) {
-            const int r = e / kF64KC, kk = e % kF64KC;
-            const int64_t kr = kc + kk;
-            xs[r][kk] = (r < p && kr < k1) ? u[(int64_t)r * ldu + kr] : 0.0;
+    // This thread's entries of a chunk: column sk of rows sr, sr + 16, ...; columns beyond k1 count
+    // as zero, rows beyond p as row p - 1 (their products are never read).  With up to 16 row
+    // blocks the next chunk's are loaded while this one is multiplied, MAXB of them without a
+    // branch around each; with more there are no registers for that.  Offsets from a uniform base take
+    // 32 bits (ldu < 2^25).
+    static_assert(64 * kF64Waves == 16 * kF64KC, "a pass of the workgroup stages 16 rows");
+    const int sr = threadIdx.x / kF64KC, sk = threadIdx.x % kF64KC;
+    const int srl = sr < p - 16 * (nb - 1) ? sr : p - 16 * (nb - 1) - 1;   // in the last row block
+    double reg[kAhead ? MAXB : 1], creg = 1.0;
+    auto load_chunk = [&](int64_t kc) {
+        const int64_t left = k1 - 1 - kc;
+        const uint32_t col = left < sk ? (uint32_t)left : (uint32_t)sk;
+        const uint32_t at = (uint32_t)sr * (uint32_t)ldu + col, atl = (uint32_t)srl * (uint32_t)ldu + col;
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int m = 0; m < MAXB; ++m)
+                reg[m] = (u + ((int64_t)16 * (m < nb ? m : nb - 1) * ldu + kc))[m >= nb - 1 ? atl : at];
         }
-        if (threadIdx.x < kF64KC) cs[threadIdx.x] = (c && kc + threadIdx.x < k1) ? c[kc + threadIdx.x] : 1.0;
+        if (c && threadIdx.x < kF64KC) creg = kc + sk < k1 ? c[kc + sk] : 1.0;
+    };
+    if (kAhead && k0 < k1) load_chunk(k0);
+    for (int64_t kc = k0; kc < k1; kc += kF64KC) {
+        if constexpr (kAhead) {
+            const bool in = kc + sk < k1;
+#pragma unroll
+            for (int m = 0; m < MAXB; ++m) xs[16 * m + sr][sk] = in ? reg[m] : 0.0;
+        } else {
+            load_chunk(kc);
+            for (int r = sr; r < nb * 16; r += 16)
+                xs[r][sk] = (r < p && kc + sk < k1) ? u[(int64_t)r * ldu + kc + sk] : 0.0;
+        }
+        if (threadIdx.x < kF64KC) cs[threadIdx.x] = creg;
         __syncthreads();
+        if (kAhead && kc + kF64KC < k1) load_chunk(kc + kF64KC);
 #pragma unroll
         for (int ks = 0; ks < kF64KC; ks += 4) {
             const int kk = ks + kq;
             const double ck = cs[kk];
 #pragma unroll
-            for (int m = 0; m < kF64PerWave; ++m) {
+            for (int m = 0; m < kPW; ++m) {
                 if (q0 + w + kF64Waves * m < nblk) {
                     const double a = xs[bi[m] * 16 + r16][kk] * ck;
                     const double b = xs[bj[m] * 16 + r16][kk];
@@ -200,7 +236,7 @@ __global__ __launch_bounds__(64 * kF64Waves, 1) void syrk_f64_mfma_kernel(const 
         __syncthreads();   // the next chunk rewrites the staged rows
     }
 #pragma unroll
-    for (int m = 0; m < kF64PerWave; ++m) {
+    for (int m = 0; m < kPW; ++m) {
         if (q0 + w + kF64Waves * m < nblk) {
             const int ti = bi[m] / 4, tj = bj[m] / 4;
             const int pair = ti * nt - ti * (ti - 1) / 2 + (tj - ti);
@@ -1459,7 +1495,7 @@ int syrk_f64(const double *u, int64_t ldu, int p, const double *c, int64_t K, in
     const int nt = (p + kTile - 1) / kTile;
     const int npairs = nt * (nt + 1) / 2;
     int64_t kchunk = (K + splits - 1) / splits;
-    if (p <= 512) {
+    if (p <= 512 && ldu < (1 << 25)) {
         // matrix cores, every row of u staged once per K chunk: 2 * splits K ranges at p <= 256
         // (one group of blocks), splits ranges of 4 groups beyond; fewer ranges when K is short
         // (at least 4 chunks each), the reduction reading every range's tiles
@@ -1470,8 +1506,16 @@ int syrk_f64(const double *u, int64_t ldu, int p, const double *c, int64_t K, in
         if (ngroups > 1 && s2 >= 8) s2 = s2 / 8 * 8;   // whole groups of 8 ranges: one XCD runs all groups of a range
         kchunk = (K + s2 - 1) / s2;
         kchunk = (kchunk + kF64KC - 1) / kF64KC * kF64KC;
-        if (p <= 256) syrk_f64_mfma_kernel<16><<<dim3(s2, ngroups), 64 * kF64Waves, 0, stream>>>(u, ldu, p, c, K, kchunk, part);
-        else syrk_f64_mfma_kernel<32><<<dim3(s2, ngroups), 64 * kF64Waves, 0, stream>>>(u, ldu, p, c, K, kchunk, part);
+#define COXMI_SYRKF64(MB) \
+    syrk_f64_mfma_kernel<MB><<<dim3(s2, ngroups), 64 * kF64Waves, 0, stream>>>(u, ldu, p, c, K, kchunk, part)
+        if (nb > 16) COXMI_SYRKF64(32);
+        else if (nb > 12) COXMI_SYRKF64(16);
+        else if (nb > 8) COXMI_SYRKF64(12);
+        else if (nb > 4) COXMI_SYRKF64(8);
+        else if (nb > 2) COXMI_SYRKF64(4);
+        else if (nb > 1) COXMI_SYRKF64(2);
+        else COXMI_SYRKF64(1);
+#undef COXMI_SYRKF64
         syrk_reduce_kernel<<<dim3(npairs, kTile * kTile / 64), 64 * kRedWaves, 0, stream>>>(part, p, s2, sign,
                                                                                            accumulate, C);
         return hipGetLastError() == hipSuccess ? 0 : -3;
