@@ -438,7 +438,8 @@ int cox_segscan_f64(const double *a, const uint8_t *head, double *b, int64_t n, 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * arguments, scan and results, but the scan's synchronisation words live in a fixed
  * 4,352-byte array of the library's device memory (one copy per GPU, held until the
- * process ends) instead of a per-call allocation.  A fill kernel on `stream` clears
+ * process ends), whereas cox_segscan_f64 takes one of 32 such arrays and allocates one
+ * when all are in use.  A fill kernel on `stream` clears
  * the array before each scan.  Calls no hipMalloc, hipFree or other allocating
  * routine.  Limit: n <= CUs x 1024 x 16 rows (4,194,304 on 256 compute units), else
  * COX_EUNSUPPORTED (as for cox_segscan_f64).  Calls that overlap on one GPU (other

@@ -1829,7 +1829,10 @@ int chol_solve(double *A, int p, const double *g, const uint8_t *free_col, int f
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_tail_kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                                        (int)tail_lds(kCholTail));
-    if (attr != hipSuccess) return -3;
+    static const hipError_t sattr = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_solve_kernel),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                        (int)sizeof(double) * 8192);
+    if (attr != hipSuccess || sattr != hipSuccess) return -3;
     auto tail = [&](int r0) {
         const int n = p - r0;
         // four waves have enough tiles up to 64 columns, and their barriers are shorter
