@@ -1660,8 +1660,8 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
 // in one workgroup.  With z_j = beta_j + D_j and a_j = H_jj, coordinate j moves to
 // soft(u_j, gamma_j) / a_j where u_j = a_j z_j - g_j - (HD)_j, and a move of another coordinate i by
 // delta changes u_j by -H_ij delta (its own move leaves u_j as it is).  Coordinates not free, or
-// with H_jj <= 0 or not finite, stay.  Stops after the first sweep whose largest |change| is
-// <= tol, or after max_sweeps sweeps.
+// with H_jj <= 0 or not finite, stay, and their rows of H, which may hold NaN or infinities, are
+// not read.  Stops after the first sweep whose largest |change| is <= tol, or after max_sweeps sweeps.
 //
 // The chain is what bounds it: each coordinate needs the one before.  Coordinates go in blocks
 // of 64: wave 0 holds a block's u in its lanes and takes its 64 decisions in turn from the
@@ -1684,15 +1684,24 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
     __shared__ double s_delta[kProxB];
     __shared__ int s_row[kProxB], s_moved;
     __shared__ double s_change;
+    __shared__ unsigned long long s_live[kMaxNewtonP / kProxB];   // a bit per coordinate: it may move
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t / 64);
     const int nblk = (p + kProxB - 1) / kProxB;
+    for (int b = w; b < nblk; b += kProxThreads / 64) {
+        const int j = b * kProxB + lane;
+        const double a = j < p ? H[(size_t)j * p + j] : 0.0;
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(j < p && free_col[j] && a > 0.0 && a < INFINITY);
+        if (lane == 0) s_live[b] = mask;
+    }
+    __syncthreads();
+    // (the decisions subtract row i times coordinate i's move, 0 for one that stays: 0 times NaN)
     auto stage = [&](int block, int first, int threads) {
         double *dst = blk + (block & 1) * (kProxB * kProxB);
         const int j0 = block * kProxB;
         for (int e = t - first; e < kProxB * kProxB; e += threads) {
             const int r = e / kProxB, c = e % kProxB;
-            dst[e] = (r != c && j0 + r < p && j0 + c < p) ? H[(size_t)(j0 + r) * p + j0 + c] : 0.0;
+            dst[e] = (r != c && ((s_live[block] >> r) & 1ull) && j0 + c < p) ? H[(size_t)(j0 + r) * p + j0 + c] : 0.0;
         }
     };
     for (int k = t; k < p; k += kProxThreads) {
@@ -1705,13 +1714,8 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
     double ga = 0.0, inv = 0.0;
     auto inputs = [&](int block, double &gm, double &iv) {
         const int j = block * kProxB + lane;
-        gm = 0.0;
-        iv = 0.0;
-        if (j < p) {
-            const double a = H[(size_t)j * p + j];
-            gm = gam[j];
-            iv = (free_col[j] && a > 0.0 && a < INFINITY) ? 1.0 / a : 0.0;
-        }
+        gm = j < p ? gam[j] : 0.0;
+        iv = ((s_live[block] >> lane) & 1ull) ? 1.0 / H[(size_t)j * p + j] : 0.0;
     };
     if (w == 0) inputs(0, ga, inv);
     int sweep = 0;
