@@ -1657,17 +1657,20 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
 // Proximal Newton's model solve: cyclic coordinate descent with soft thresholding (the l1
 // rule of Sec. 2.4, applied to the quadratic model of the objective)
 //   min_D  g'D + D'HD/2 + sum_j gamma_j |beta_j + D_j|
-// in one workgroup.  With z_j = beta_j + D_j and a_j = H_jj, coordinate j moves to
-// soft(u_j, gamma_j) / a_j where u_j = a_j z_j - g_j - (HD)_j, and a move of another coordinate i by
-// delta changes u_j by -H_ij delta (its own move leaves u_j as it is).  Coordinates not free, or
-// with H_jj <= 0 or not finite, stay, and their rows of H, which may hold NaN or infinities, are
-// not read.  Stops after the first sweep whose largest |change| is <= tol, or after max_sweeps sweeps.
+// in one workgroup.  With z_j = beta_j + D_j, a_j = H_jj and v_j = sum_{i != j} H_ji D_i, coordinate
+// j moves to soft(u_j, gamma_j) / a_j where u_j = a_j beta_j - g_j - v_j; a move of another coordinate
+// i by delta adds H_ij delta to v_j.  The parts that stay (a_j beta_j - g_j -+ gamma_j) are rounded
+// once and v alone takes the moves: it is as small as D, so a move rounds at the size of the moves,
+// not at that of a_j beta_j (with u itself carried along, an AR(1) fit of 300 columns ended 3e-14
+// from the model's minimum, now 5e-16).  Coordinates not free, or with H_jj <= 0 or not finite,
+// stay, and their rows of H, which may hold NaN or infinities, are not read.  Stops after the first
+// sweep whose largest |change| is <= tol, or after max_sweeps sweeps.
 //
 // The chain is what bounds it: each coordinate needs the one before.  Coordinates go in blocks
-// of 64: wave 0 holds a block's u in its lanes and takes its 64 decisions in turn from the
+// of 64: wave 0 holds a block's v in its lanes and takes its 64 decisions in turn from the
 // 64 x 64 diagonal block in LDS (7 dependent FP64 operations and a lane broadcast each), while the
 // other waves stage the next diagonal block; then all 16 waves apply the block's moves to the
-// rest of u, a row of H per moved coordinate, 32 rows in flight.  One wave that
+// rest of v, a row of H per moved coordinate, 32 rows in flight.  One wave that
 // fetched a row of H per coordinate (a memory round trip each) took 9.9 ms per solve in a
 // p = 1000 fit; this takes 2.0 ms.
 constexpr int kProxB = 64;         // coordinates of a block
@@ -1679,8 +1682,8 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
                                                                const uint8_t *free_col, double tol, int max_sweeps,
                                                                double *D, int *sweeps_out)
 {
-    extern __shared__ double sm[];   // u[p], z[p], two diagonal blocks (row-major, zero diagonal)
-    double *u = sm, *z = sm + p, *blk = sm + 2 * (size_t)p;
+    extern __shared__ double sm[];   // v[p], z[p], two diagonal blocks (row-major, zero diagonal)
+    double *v = sm, *z = sm + p, *blk = sm + 2 * (size_t)p;
     __shared__ double s_delta[kProxB];
     __shared__ int s_row[kProxB], s_moved;
     __shared__ double s_change;
@@ -1705,19 +1708,23 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
         }
     };
     for (int k = t; k < p; k += kProxThreads) {
-        const double bk = beta[k];
-        u[k] = fma(H[(size_t)k * p + k], bk, -g[k]);
-        z[k] = bk;
+        v[k] = 0.0;
+        z[k] = beta[k];
     }
     stage(0, 0, kProxThreads);
-    // wave 0's inputs of its lane's coordinate, one block ahead; inverse 0: the coordinate stays
-    double ga = 0.0, inv = 0.0;
-    auto inputs = [&](int block, double &gm, double &iv) {
+    // wave 0's inputs of its lane's coordinate, one block ahead: a beta - g -+ gamma and 1 / a (0: it stays)
+    double lo = 0.0, hi = 0.0, inv = 0.0;
+    auto inputs = [&](int block, double &l, double &h, double &iv) {
         const int j = block * kProxB + lane;
-        gm = j < p ? gam[j] : 0.0;
-        iv = ((s_live[block] >> lane) & 1ull) ? 1.0 / H[(size_t)j * p + j] : 0.0;
+        l = h = iv = 0.0;
+        if ((s_live[block] >> lane) & 1ull) {
+            const double a = H[(size_t)j * p + j], c = fma(a, beta[j], -g[j]), gm = gam[j];
+            l = c - gm;
+            h = c + gm;
+            iv = 1.0 / a;
+        }
     };
-    if (w == 0) inputs(0, ga, inv);
+    if (w == 0) inputs(0, lo, hi, inv);
     int sweep = 0;
     while (sweep < max_sweeps) {
         ++sweep;
@@ -1727,12 +1734,12 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
             const int j0 = b * kProxB, nb = p - j0 < kProxB ? p - j0 : kProxB;
             // one block stays where it is; with an odd number the first one's buffer is the last one's too
             const bool restage = nblk > 1, clash = restage && nextb == 0 && (b & 1) == 0;
-            __syncthreads();   // u holds every earlier move, the diagonal block is staged
+            __syncthreads();   // v holds every earlier move, the diagonal block is staged
             if (w == 0) {
-                double gn, invn;
-                inputs(nextb, gn, invn);   // in flight during the decisions
+                double lon, hin, invn;
+                inputs(nextb, lon, hin, invn);   // in flight during the decisions
                 const bool live = lane < nb && inv != 0.0;
-                double ul = lane < nb ? u[j0 + lane] : 0.0, zl = lane < nb ? z[j0 + lane] : 0.0;
+                double vl = lane < nb ? v[j0 + lane] : 0.0, zl = lane < nb ? z[j0 + lane] : 0.0;
                 double moved = 0.0;
                 const double *row = blk + (b & 1) * (kProxB * kProxB) + lane;
                 double hc[8], hn[8];
@@ -1745,20 +1752,20 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
                         // every lane's move as of now; lane i0 + q takes its own
-                        const double soft = ul > ga ? ul - ga : (ul < -ga ? ul + ga : 0.0);
+                        const double soft = vl < lo ? lo - vl : (vl > hi ? hi - vl : 0.0);
                         const double znew = live ? soft * inv : zl;
                         const double delta = lane_value(znew - zl, i0 + q);
                         if (lane == i0 + q) {
                             moved = znew - zl;
                             zl = znew;
                         }
-                        ul = fma(-hc[q], delta, ul);
+                        vl = fma(hc[q], delta, vl);
                     }
 #pragma unroll
                     for (int q = 0; q < 8; ++q) hc[q] = hn[q];
                 }
                 if (lane < nb) {
-                    u[j0 + lane] = ul;
+                    v[j0 + lane] = vl;
                     z[j0 + lane] = zl;
                 }
                 change = fmax(change, fabs(moved));
@@ -1770,7 +1777,8 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
                     s_row[at] = j0 + lane;
                 }
                 if (lane == 0) s_moved = __popcll(mask);
-                ga = gn;
+                lo = lon;
+                hi = hin;
                 inv = invn;
             } else if (restage && !clash) {
                 stage(nextb, 64, kProxThreads - 64);
@@ -1779,7 +1787,7 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
             const int m = s_moved;
             for (int k = t; k < p; k += kProxThreads) {
                 if (k >= j0 && k < j0 + nb) continue;
-                double acc = u[k];
+                double acc = v[k];
                 for (int q0 = 0; q0 < m; q0 += kProxRows) {
                     double h[kProxRows];
 #pragma unroll
@@ -1789,9 +1797,9 @@ __global__ __launch_bounds__(kProxThreads) void prox_cd_kernel(const double *H, 
                     }
 #pragma unroll
                     for (int q = 0; q < kProxRows; ++q)
-                        if (q0 + q < m) acc = fma(-h[q], s_delta[q0 + q], acc);
+                        if (q0 + q < m) acc = fma(h[q], s_delta[q0 + q], acc);
                 }
-                u[k] = acc;
+                v[k] = acc;
             }
             if (clash) stage(nextb, 0, kProxThreads);   // nobody reads the buffer before the next barrier
         }
