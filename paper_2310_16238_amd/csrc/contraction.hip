@@ -314,15 +314,15 @@ __device__ __forceinline__ void wave_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 1 / sqrt(d) and sqrt(d) to about an ulp for 0 < d < 1e300: the hardware estimate, two Newton
-// steps, and one for the root (a division and a root are several times as long a chain).
+// 1 / sqrt(d) and sqrt(d) to about an ulp for every d > 0: the hardware estimate, two Newton
+// steps, and one for the root (a division and a root are several times as long a chain).  The steps go
+// by d y, about sqrt(d), which neither overflows nor underflows where d itself does not.
 __device__ __forceinline__ void pivot_root(double d, double &root, double &inv)
 {
-    d = fmin(d, 1e300);   // an overflowed diagonal takes its row and column out
+    d = fmin(d, 0x1.fffffffffffffp+1023);   // an overflowed diagonal takes its row and column out
     double y = __builtin_amdgcn_rsq(d);
-    const double h = -0.5 * d;
-    y = fma(y, fma(h * y, y, 0.5), y);
-    y = fma(y, fma(h * y, y, 0.5), y);
+    y = fma(0.5 * y, fma(-(d * y), y, 1.0), y);
+    y = fma(0.5 * y, fma(-(d * y), y, 1.0), y);
     const double r = d * y;
     root = fma(0.5 * y, fma(-r, r, d), r);
     inv = y;
