@@ -841,7 +841,7 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
         Partial v = partial_identity();
 #pragma unroll
         for (int i = 0; i < IPT; ++i)
-            if (!(meta[i] & kPadBit)) {
+            if (!(meta[i] & kPadBit) && eta[i] == eta[i]) {   // a NaN would be the largest key: its row has no weight
                 const uint32_t key = float_key((float)eta[i]);
                 v.top = key > v.top ? key : v.top;
             }
