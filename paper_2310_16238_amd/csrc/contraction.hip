@@ -1550,9 +1550,8 @@ int launch_syrk_bf16(const uint16_t *u, int64_t ldu, int p, const double *c, int
         kchunk = (kchunk + 63) / 64 * 64;
         constexpr size_t per_tile = sizeof(uint16_t) * kMT * (64 + 8) * (WEIGHT ? 2 : 1);
         auto *fn = &syrk_bf16_lds_kernel<WEIGHT, BLK, 64, 8, 4, 8, 4>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)(8 * per_tile));
-        if (attr != hipSuccess) return -3;
+        static LdsLimit limit;
+        if (limit.raise(reinterpret_cast<const void *>(fn), 8 * per_tile) != hipSuccess) return -3;
         fn<<<dim3(*splits, ngroups), 64 * 8, nt * per_tile, stream>>>(u, ldu, p, c, K64, kchunk, part);
     } else {
         const int nb = (nt + kWideTiles - 1) / kWideTiles;
@@ -1562,9 +1561,8 @@ int launch_syrk_bf16(const uint16_t *u, int64_t ldu, int p, const double *c, int
         kchunk = (kchunk + kWideKC - 1) / kWideKC * kWideKC;
         constexpr size_t lds = sizeof(uint16_t) * (size_t)4 * kWideRows * kWideStride;
         auto *fn = &syrk_bf16_wide_kernel<WEIGHT, BLK>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (attr != hipSuccess) return -3;
+        static LdsLimit limit;
+        if (limit.raise(reinterpret_cast<const void *>(fn), lds) != hipSuccess) return -3;
         fn<<<dim3(*splits, nblocks), 64 * kWideWaves, lds, stream>>>(u, ldu, p, c, K64, kchunk, part);
     }
     return 0;
@@ -1621,13 +1619,8 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
         int64_t kchunk = (K64 + bsplits - 1) / bsplits;
         kchunk = (kchunk + kF8WideKC - 1) / kF8WideKC * kF8WideKC;
         const size_t lds = (size_t)4 * kWideRows * kF8WideStride;
-        static bool wattr = false;
-        if (!wattr) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(&syrk_fp8_wide_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return -3;
-            wattr = true;
-        }
+        static LdsLimit limit;
+        if (limit.raise(reinterpret_cast<const void *>(&syrk_fp8_wide_kernel), lds) != hipSuccess) return -3;
         float *fpart = reinterpret_cast<float *>(part);
         syrk_fp8_wide_kernel<<<dim3(bsplits, nblocks), 64 * kWideWaves, lds, stream>>>(u, p, c, wsc, K64, kchunk, fpart);
         syrk_bf16_reduce_kernel<<<dim3(npairs, 16), 64 * kRedWaves, 0, stream>>>(fpart, p, bsplits, scale, sign, accumulate, C,
@@ -1822,14 +1815,10 @@ int prox_model_solve(const double *H, int p, const double *g, const double *beta
 {
     if (p < 1 || p > 4096) return -1;
     const size_t lds = sizeof(double) * (2 * (size_t)p + 2 * kProxB * kProxB);
-    static bool attr = false;
-    if (!attr) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&prox_cd_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(sizeof(double) * (2 * 4096 + 2 * kProxB * kProxB))) != hipSuccess)
-            return -3;
-        attr = true;
-    }
+    static LdsLimit limit;
+    if (limit.raise(reinterpret_cast<const void *>(&prox_cd_kernel),
+                    sizeof(double) * (2 * kMaxNewtonP + 2 * kProxB * kProxB)) != hipSuccess)
+        return -3;
     prox_cd_kernel<<<1, kProxThreads, lds, stream>>>(H, p, g, beta, gam, free_col, tol, max_sweeps, D, sweeps);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
@@ -1838,13 +1827,10 @@ int chol_solve(double *A, int p, const double *g, const uint8_t *free_col, int f
                hipStream_t stream)
 {
     auto tail_lds = [](int n) { return sizeof(double) * ((size_t)n * (n + 1) / 2 + kTriPad + n); };
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_tail_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)tail_lds(kCholTail));
-    static const hipError_t sattr = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_solve_kernel),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                        (int)sizeof(double) * 8192);
-    if (attr != hipSuccess || sattr != hipSuccess) return -3;
+    static LdsLimit tail_limit, solve_limit;
+    if (tail_limit.raise(reinterpret_cast<const void *>(&chol_tail_kernel), tail_lds(kCholTail)) != hipSuccess ||
+        solve_limit.raise(reinterpret_cast<const void *>(&chol_solve_kernel), sizeof(double) * 8192) != hipSuccess)
+        return -3;
     auto tail = [&](int r0) {
         const int n = p - r0;
         // four waves have enough tiles up to 64 columns, and their barriers are shorter

@@ -4,9 +4,31 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 
 namespace coxmi {
+
+// A kernel's limit of dynamic LDS belongs to the device's copy of the function, so it is raised once on
+// every device that launches it (one object per kernel, of static storage; any thread may call).
+class LdsLimit {
+public:
+    // Allows `bytes` of dynamic LDS to `fn` on the current device; the same fn and bytes on every call.
+    hipError_t raise(const void *fn, size_t bytes)
+    {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;   // beyond 64 devices: on every call
+        if (raised_.load(std::memory_order_acquire) & bit) return hipSuccess;
+        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e == hipSuccess) raised_.fetch_or(bit, std::memory_order_release);
+        return e;
+    }
+
+private:
+    std::atomic<uint64_t> raised_{0};
+};
 
 // Row word in canonical order (see cox_layout in include/coxmi.h).
 constexpr uint32_t kHeadBit = 0x80000000u;

@@ -28,7 +28,6 @@
 #include <hip/hip_bf16.h>
 #include <math.h>
 
-#include <mutex>
 #include <type_traits>
 
 #include "internal.h"
@@ -1219,17 +1218,12 @@ int full_eval_launch(const FullEvalArgs &A, hipStream_t stream)
         const int grid = A.nseg < kSegGrid ? A.nseg : kSegGrid;
         const int wpp = (A.seg_rows + kWave - 1) / kWave;
         const size_t lds = seg_lds_bytes(A.p, wpp * kWave);
-        static std::once_flag once;
-        static hipError_t attr = hipSuccess;
-        std::call_once(once, [] {
-            const void *fns[] = {reinterpret_cast<const void *>(&strata_eval_kernel<double, true>),
-                                 reinterpret_cast<const void *>(&strata_eval_kernel<__hip_bfloat16, true>),
-                                 reinterpret_cast<const void *>(&strata_eval_kernel<double, false>)};
-            for (const void *fn : fns)
-                if (attr == hipSuccess)
-                    attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSegMaxLds);
-        });
-        if (attr != hipSuccess) return -3;
+        static LdsLimit limits[3];
+        const void *fns[] = {reinterpret_cast<const void *>(&strata_eval_kernel<double, true>),
+                             reinterpret_cast<const void *>(&strata_eval_kernel<__hip_bfloat16, true>),
+                             reinterpret_cast<const void *>(&strata_eval_kernel<double, false>)};
+        const int k = !A.want_xbar ? 2 : (A.ztype == kZF64 ? 0 : 1);
+        if (limits[k].raise(fns[k], kSegMaxLds) != hipSuccess) return -3;
 #define COXMI_SEGEVAL(ZT, XB)                                                                                     \
     strata_eval_kernel<ZT, XB><<<grid, kSegThreads, lds, stream>>>(                                               \
         A.x, ld, A.p, A.beta, A.meta, A.seg, A.nseg, wpp, A.b, A.want_rows ? A.m : nullptr,                       \

@@ -1463,14 +1463,10 @@ int launch_step(const FitDesc *fits, const int *slots, int nslots, int max_p, hi
 {
     if (nslots <= 0) return 0;
     const size_t lds = sizeof(double) * ((size_t)max_p * max_p + max_p);
-    static bool attr_set = false;
-    if (!attr_set) {
-        const size_t most = sizeof(double) * ((size_t)kMaxP * kMaxP + kMaxP);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&step_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-        if (e != hipSuccess) return (int)e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    const size_t most = sizeof(double) * ((size_t)kMaxP * kMaxP + kMaxP);
+    const hipError_t e = limit.raise(reinterpret_cast<const void *>(&step_kernel), most);
+    if (e != hipSuccess) return (int)e;
     step_kernel<<<nslots, kStepThreads, lds, s>>>(fits, slots);
     return (int)hipGetLastError();
 }
@@ -1486,15 +1482,11 @@ size_t round_lds_bytes(int max_p)
 
 int round_grid(int max_p, int *grid)
 {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&round_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)round_lds_bytes(kMaxP));
-        if (e != hipSuccess) return (int)e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    hipError_t e = limit.raise(reinterpret_cast<const void *>(&round_kernel), round_lds_bytes(kMaxP));
+    if (e != hipSuccess) return (int)e;
     int dev = 0, cus = 0, per_cu = 0;
-    hipError_t e = hipGetDevice(&dev);
+    e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&round_kernel),
