@@ -1466,7 +1466,7 @@ int segscan_f64(const double *a, const uint8_t *head, double *b, int64_t n, hipS
         return ok ? 0 : -3;
     }
     void *scratch = nullptr;
-    if (hipMalloc(&scratch, kScanScratchBytes) != hipSuccess) return -2;
+    if (device_malloc(&scratch, kScanScratchBytes) != hipSuccess) return -2;
     const ScanSync S = scan_sync(scratch, 1u, 0u, nullptr);
     uint32_t aborted = 0;
     hipError_t e = hipMemsetAsync(scratch, 0, kScanScratchBytes, stream);

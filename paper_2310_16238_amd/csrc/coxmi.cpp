@@ -85,7 +85,46 @@ void pool_release(const PoolBlock &b)
     else (void)hipFree(b.p);
 }
 
+// Releases the idle blocks of one kind (a device's, or with -1 pinned ones); false if there are none.
+bool pool_trim(int device)
+{
+    Pool &P = pool();
+    std::vector<PoolBlock> out;
+    {
+        std::lock_guard<std::mutex> lock(P.mu);
+        for (size_t i = 0; i < P.idle.size();) {
+            if (P.idle[i].device != device) {
+                ++i;
+                continue;
+            }
+            out.push_back(P.idle[i]);
+            P.idle_bytes -= P.idle[i].bytes;
+            P.idle.erase(P.idle.begin() + (std::ptrdiff_t)i);
+        }
+    }
+    for (const PoolBlock &b : out) pool_release(b);
+    return !out.empty();
+}
+
+// An allocation of memory on `device` (-1: pinned), and once more without the idle blocks if refused.
+template <typename F>
+hipError_t allocate_or_trim(int device, F allocate)
+{
+    const hipError_t e = allocate();
+    if (e == hipSuccess || !pool_trim(device)) return e;
+    (void)hipGetLastError();   // the refusal is not the call's result
+    return allocate();
+}
+
 }  // namespace
+
+hipError_t coxmi::device_malloc(void **out, size_t bytes)
+{
+    *out = nullptr;
+    int device = 0;
+    const hipError_t e = hipGetDevice(&device);
+    return e != hipSuccess ? e : allocate_or_trim(device, [&] { return hipMalloc(out, bytes); });
+}
 
 hipError_t pool_get(void **out, size_t bytes, bool pinned)
 {
@@ -114,7 +153,8 @@ hipError_t pool_get(void **out, size_t bytes, bool pinned)
         }
     }
     void *p = nullptr;
-    const hipError_t e = pinned ? hipHostMalloc(&p, bytes, hipHostMallocPortable) : hipMalloc(&p, bytes);
+    const hipError_t e = allocate_or_trim(
+        device, [&] { return pinned ? hipHostMalloc(&p, bytes, hipHostMallocPortable) : hipMalloc(&p, bytes); });
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(P.mu);
     P.used.push_back(PoolBlock{p, bytes, device});
@@ -346,7 +386,7 @@ static hipError_t alloc_device(cox_handle *h)
     hipError_t e;
     void *x = nullptr, *pin = nullptr;
     if ((h->ldb == 0 && (e = pool_get(&x, sizeof(double) * (size_t)ld * p, false)) != hipSuccess) ||
-        (h->ldb != 0 && (e = hipMalloc(&h->d_xbits, indicator_unit(h->shape.ipt) * (size_t)h->ldb * p)) != hipSuccess) ||
+        (h->ldb != 0 && (e = device_malloc(&h->d_xbits, indicator_unit(h->shape.ipt) * (size_t)h->ldb * p)) != hipSuccess) ||
         (e = pool_get(&h->d_small, meta + vec + sync + trust, false)) != hipSuccess ||
         (e = pool_get(&pin, sizeof(double) * cox_handle::hpin_doubles(p), true)) != hipSuccess) {
         pool_put(x);
@@ -770,9 +810,9 @@ extern "C" int cox_init_sparse(cox_handle **out, int64_t n, int64_t p, const int
         q[(size_t)j] = event_sum_device_order(col, ev_dev);
     }
     hipError_t e = alloc_device(h);
-    if (e == hipSuccess) e = hipMalloc(&h->d_xvals, sizeof(double) * std::max<size_t>(vals.size(), 1));
-    if (e == hipSuccess) e = hipMalloc(&h->d_xvoff, sizeof(int64_t) * (size_t)p);
-    if (e == hipSuccess) e = hipMalloc(&h->d_woff, sizeof(int32_t) * std::max<size_t>(woff.size(), 1));
+    if (e == hipSuccess) e = device_malloc(reinterpret_cast<void **>(&h->d_xvals), sizeof(double) * std::max<size_t>(vals.size(), 1));
+    if (e == hipSuccess) e = device_malloc(reinterpret_cast<void **>(&h->d_xvoff), sizeof(int64_t) * (size_t)p);
+    if (e == hipSuccess) e = device_malloc(reinterpret_cast<void **>(&h->d_woff), sizeof(int32_t) * std::max<size_t>(woff.size(), 1));
     if (e != hipSuccess) {
         free_device(h);
         delete h;
@@ -1052,7 +1092,7 @@ extern "C" int cox_init_intervals(cox_handle **out, const cox_handle *parent, co
     }
     hipError_t e = alloc_device(h);
     int32_t *d_maps = nullptr;
-    if (e == hipSuccess) e = hipMalloc(&d_maps, sizeof(int32_t) * maps.size());
+    if (e == hipSuccess) e = device_malloc(reinterpret_cast<void **>(&d_maps), sizeof(int32_t) * maps.size());
     if (e != hipSuccess) {
         if (d_maps) (void)hipFree(d_maps);
         free_device(h);

@@ -111,8 +111,9 @@ struct cox_handle {
 // Memory of handles, device or pinned host.  While some handle lives, blocks that others have given
 // back are kept for the next (a cross-validation or bootstrap makes a handle per refit, and its
 // allocations took as long as its kernels): at most kPoolBytes in blocks of at most kPoolBlock, all
-// released with the last handle.  Every call on a handle ends with its stream's work done, so a
-// block that is given back is idle.  Thread-safe.
+// released with the last handle, or earlier where one of the library's allocations would otherwise
+// be refused.  Every call on a handle ends with its stream's work done, so a block that is given
+// back is idle.  Thread-safe.
 constexpr size_t kPoolBytes = (size_t)256 << 20, kPoolBlock = (size_t)64 << 20;
 hipError_t pool_get(void **p, size_t bytes, bool pinned);
 void pool_put(void *p);

@@ -118,6 +118,10 @@ int launch_gather_rows(const double *x_in, int64_t ld_in, const int32_t *src, co
 constexpr int kEventSumThreads = 256;
 int launch_event_sums(const double *x, int64_t ld, const uint32_t *meta, double *q, int p, hipStream_t stream);
 
+// hipMalloc on the current device; when it is refused, the idle blocks that the handles keep for later
+// ones (see pool_get) are released and it is tried once more.
+hipError_t device_malloc(void **out, size_t bytes);
+
 // True when [ptr, ptr + bytes) lies inside one device (or managed) allocation of `device`
 // (host code; clears the HIP error state when the pointer is not device memory).
 bool device_range_ok(const void *ptr, size_t bytes, int device);

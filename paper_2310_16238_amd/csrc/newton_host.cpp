@@ -479,7 +479,7 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
     const std::vector<double> &gam = h->gamma;
     std::vector<double> beta(p, 0.0), prev(p, 0.0), D(p, 0.0);
     if (!s.prox) {
-        const hipError_t e = hipMalloc(&s.prox, sizeof(double) * ((size_t)p + 1));
+        const hipError_t e = device_malloc(reinterpret_cast<void **>(&s.prox), sizeof(double) * ((size_t)p + 1));
         if (e != hipSuccess) {
             s.prox = nullptr;
             return handle_hip_fail(h, e, "proximal Newton buffers");

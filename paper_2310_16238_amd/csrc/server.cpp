@@ -458,7 +458,7 @@ bool ensure_list(cox_server::List &l, size_t bytes, std::string &err)
     l.h = l.d = nullptr;
     l.cap = 0;
     if (hipHostMalloc(reinterpret_cast<void **>(&l.h), cap, hipHostMallocDefault) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&l.d), cap) != hipSuccess) {
+        device_malloc(reinterpret_cast<void **>(&l.d), cap) != hipSuccess) {
         err = "allocating a work list";
         return false;
     }
@@ -1148,9 +1148,9 @@ extern "C" int cox_server_create(cox_server **out, const cox_server_options *o)
     if ((e = hipStreamCreateWithFlags(&s->compute, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&s->iter_ev, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipMalloc(reinterpret_cast<void **>(&s->arena), opt.hbm_budget)) != hipSuccess ||
-        (e = hipMalloc(reinterpret_cast<void **>(&s->d_desc), sizeof(FitDesc) * ns)) != hipSuccess ||
-        (e = hipMalloc(reinterpret_cast<void **>(&s->d_state), sizeof(FitState) * ns)) != hipSuccess ||
+        (e = device_malloc(reinterpret_cast<void **>(&s->arena), opt.hbm_budget)) != hipSuccess ||
+        (e = device_malloc(reinterpret_cast<void **>(&s->d_desc), sizeof(FitDesc) * ns)) != hipSuccess ||
+        (e = device_malloc(reinterpret_cast<void **>(&s->d_state), sizeof(FitState) * ns)) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void **>(&s->staging), opt.staging_bytes, hipHostMallocDefault)) !=
             hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void **>(&s->h_desc), sizeof(FitDesc) * ns, hipHostMallocDefault)) !=
@@ -1162,7 +1162,7 @@ extern "C" int cox_server_create(cox_server **out, const cox_server_options *o)
                            hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
         (e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->dh_state), s->h_state, 0)) != hipSuccess ||
         (e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->dh_beta), s->h_beta, 0)) != hipSuccess ||
-        (e = hipMalloc(&s->d_round_ctl, round_ctl_bytes())) != hipSuccess ||
+        (e = device_malloc(&s->d_round_ctl, round_ctl_bytes())) != hipSuccess ||
         (e = hipHostMalloc(reinterpret_cast<void **>(&s->h_round), 16 * sizeof(uint64_t),
                            hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
         (e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->dh_round), s->h_round, 0)) != hipSuccess) {

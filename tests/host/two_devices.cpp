@@ -3,6 +3,7 @@
 // of each device, and checks
 //   lds     that a kernel launched with more dynamic LDS than the default had its limit raised on the
 //           device of the launch, and that what one device was asked for the other is asked for too
+//   memory  that blocks kept for later handles are released when an allocation needs their room
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -152,9 +153,41 @@ static void lds()
     CHECK(over.empty());
 }
 
+static void memory()
+{
+    const size_t mb = (size_t)1 << 20;
+    pool_handle_born();
+    for (const bool pinned : {false, true}) {
+        size_t &left = pinned ? pinned_room : room[0];
+        left = 100 * mb;
+        void *a = nullptr, *b = nullptr, *other = nullptr;
+        device = 1;
+        CHECK(pool_get(&other, 8 * mb, false) == hipSuccess);
+        pool_put(other);   // stays: the other device's memory is of no use here
+        device = 0;
+        CHECK(pool_get(&a, 60 * mb, pinned) == hipSuccess);
+        pool_put(a);
+        CHECK(left == 40 * mb);                                 // kept
+        CHECK(pool_get(&b, 90 * mb, pinned) == hipSuccess);     // needs its room
+        CHECK(hipGetLastError() == hipSuccess);
+        CHECK(pool_get(&a, 60 * mb, pinned) != hipSuccess);     // does not fit at all
+        (void)hipGetLastError();
+        pool_put(b);
+        device = 1;
+        void *again = nullptr;
+        CHECK(pool_get(&again, 8 * mb, false) == hipSuccess && again == other);
+        pool_put(again);
+        device = 0;
+        left = SIZE_MAX / 2;
+    }
+    pool_handle_gone();
+    CHECK(blocks.empty());
+}
+
 int main(int argc, char **argv)
 {
     if (argc > 1 && !std::strcmp(argv[1], "lds")) lds();
+    if (argc > 1 && !std::strcmp(argv[1], "memory")) memory();
     std::puts(fails ? "FAILED" : "OK");
     return fails != 0;
 }
