@@ -391,6 +391,19 @@ int newton_info(cox_handle *h)
     return COX_OK;
 }
 
+// Device time of a solve, and of the information matrix queued before it, once the stream is done
+// (whether or not the step is then taken).
+void count_solve(cox_handle *h, bool with_info)
+{
+    NewtonState &s = h->nt;
+    if (with_info) {
+        h->prof.contractions += 1;
+        h->prof.contraction_ms += elapsed_ms(s.ev[2], s.ev[3]);
+    }
+    h->prof.solves += 1;
+    h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
+}
+
 }  // namespace
 
 void newton_free(cox_handle *h)
@@ -524,10 +537,13 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
         const bool want_xbar = !frozen || !have_free;
         int rc = newton_eval_launch(h, beta.data(), want_xbar);
         // the solve does not wait for the host to see the objective; a step that is then halved
-        // throws it away
-        const bool ahead = have_free;
+        // throws it away (after a halving, which others often follow, it does wait)
+        const bool ahead = have_free && halvings == 0;
         if (rc == COX_OK && ahead) rc = solve();
-        if (rc == COX_OK) rc = newton_eval_finish(h, want_xbar, ev);
+        if (rc == COX_OK) {
+            rc = newton_eval_finish(h, want_xbar, ev);
+            if (ahead) count_solve(h, info_queued);
+        }
         ++evals;
         if (rc != COX_OK) return rc;
         if (!have_free) {
@@ -558,14 +574,9 @@ static int newton_fit_l1(cox_handle *h, const double *beta0, double *beta_out, c
             if (rc != COX_OK) return rc;
             const hipError_t e = hipStreamSynchronize(h->stream);
             if (e != hipSuccess) return handle_hip_fail(h, e, "proximal model solve");
+            count_solve(h, info_queued);
         }
-        if (info_queued) {
-            h->prof.contractions += 1;
-            h->prof.contraction_ms += elapsed_ms(s.ev[2], s.ev[3]);
-            have_h = true;
-        }
-        h->prof.solves += 1;
-        h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
+        have_h = have_h || info_queued;
         std::memcpy(D.data(), hD, sizeof(double) * p);
         double bmax = 1.0;
         prev = beta;
@@ -654,10 +665,13 @@ int newton_fit(cox_handle *h, const double *beta0, double *beta_out, cox_fit_inf
         const bool want_xbar = !frozen || !have_free;
         rc = newton_eval_launch(h, beta.data(), want_xbar);
         // information matrix and solve do not wait for the host to see the objective; a step that
-        // is then halved throws them away
-        const bool ahead = have_free;
+        // is then halved throws them away (after a halving, which others often follow, they do wait)
+        const bool ahead = have_free && halvings == 0;
         if (rc == COX_OK && ahead) rc = solve();
-        if (rc == COX_OK) rc = newton_eval_finish(h, want_xbar, ev);
+        if (rc == COX_OK) {
+            rc = newton_eval_finish(h, want_xbar, ev);
+            if (ahead) count_solve(h, !frozen);
+        }
         ++evals;
         if (rc != COX_OK) return rc;
         if (!have_free) {
@@ -682,13 +696,8 @@ int newton_fit(cox_handle *h, const double *beta0, double *beta_out, cox_fit_inf
             if (rc != COX_OK) return rc;
             const hipError_t e = hipStreamSynchronize(h->stream);
             if (e != hipSuccess) return handle_hip_fail(h, e, "Cholesky solve");
+            count_solve(h, !frozen);
         }
-        if (!frozen) {
-            h->prof.contractions += 1;
-            h->prof.contraction_ms += elapsed_ms(s.ev[2], s.ev[3]);
-        }
-        h->prof.solves += 1;
-        h->prof.solve_ms += elapsed_ms(s.ev[4], s.ev[5]);
         const int status = *hstatus;
         std::memcpy(dx.data(), hdx, sizeof(double) * p);
         if (status) return handle_fail(h, COX_ENUMERIC, "the information matrix is not positive definite");
