@@ -1202,11 +1202,16 @@ size_t ccd_smem_bytes(int, int p)
     return sizeof(double) * (size_t)p;
 }
 
-// One instantiation per workgroup shape (kShapes).
+// One instantiation per workgroup shape (kShapes; some are for Efron's ties alone).
 template <int XK, bool EFRON, bool WAVE>
 const void *ccd_fn(int threads, int ipt)
 {
     if (threads == 512) {
+        if constexpr (EFRON) {
+            if (ipt == 1) return reinterpret_cast<const void *>(&ccd_kernel<512, 1, XK, EFRON, WAVE>);
+            if (ipt == 2) return reinterpret_cast<const void *>(&ccd_kernel<512, 2, XK, EFRON, WAVE>);
+            if (ipt == 4) return reinterpret_cast<const void *>(&ccd_kernel<512, 4, XK, EFRON, WAVE>);
+        }
         if (ipt == 8) return reinterpret_cast<const void *>(&ccd_kernel<512, 8, XK, EFRON, WAVE>);
         if (ipt == 16) return reinterpret_cast<const void *>(&ccd_kernel<512, 16, XK, EFRON, WAVE>);
     } else if (threads == 256) {
@@ -1232,14 +1237,15 @@ const void *ccd_function(int threads, int ipt, int xk, bool efron, bool wave)
     return wave ? ccd_function_w<true>(threads, ipt, xk, efron) : ccd_function_w<false>(threads, ipt, xk, efron);
 }
 
-// Workgroups of the persistent kernel that fit on one compute unit; every variant
+// Workgroups of the persistent kernel that fit on one compute unit; every variant of the shape
 // (indicator or sparse X, Efron, wave-aligned layout) must fit, since a handle may run any of them.
 int occupancy_for(int threads, int ipt, int p, int *blocks)
 {
     *blocks = 1 << 30;
+    if (!ccd_function(threads, ipt, 0, true, false)) return (int)hipErrorInvalidValue;
     for (int v = 0; v < 12; ++v) {
         const void *fn = ccd_function(threads, ipt, v % 3, ((v / 3) & 1) != 0, ((v / 3) & 2) != 0);
-        if (!fn) return (int)hipErrorInvalidValue;
+        if (!fn) continue;
         int nb = 0;
         const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, ccd_smem_bytes(ipt, p));
         if (e != hipSuccess) return (int)e;
