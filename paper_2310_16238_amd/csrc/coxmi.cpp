@@ -245,7 +245,7 @@ static int64_t aligned_positions(const std::vector<uint32_t> &meta, int64_t R, s
         int64_t e = i + 1;
         while (e < n && !(meta[e] & kHeadBit)) ++e;
         const int64_t m = e - i;
-        const int64_t room = R - (cur % R);
+        const int64_t room = R - (cur & (R - 1));   // R: a power of two
         if (m <= R && m > room) cur += room;
         if (pos)
             for (int64_t k = 0; k < m; ++k) (*pos)[i + k] = cur + k;
@@ -269,7 +269,7 @@ static int64_t aligned_length(const std::vector<int64_t> &strata, int64_t R)
 {
     int64_t cur = 0;
     for (const int64_t m : strata) {
-        const int64_t room = R - (cur % R);
+        const int64_t room = R - (cur & (R - 1));   // R: a power of two
         if (m <= R && m > room) cur += room;
         cur += m;
     }
@@ -291,39 +291,41 @@ static double coordinate_us(int threads, int ipt, int grid, int spread, bool wav
     return 0.75 + passes + hop + (carries ? hop : 0.0);
 }
 
-// Iterations of the longest SIMD over Efron's tie groups, `ends` their (canonical row, events) in
-// order: the lane that holds a group's end takes one per event, a wave the most of its lanes for each
-// of a thread's rows in turn, and the waves of a SIMD (w, w + 4) wait for its FP64 units.  So where
-// groups are large, few rows per thread win: N = 1e5 in one stratum, groups of 50 events, 512 x 1 26 us
-// per coordinate (111 iterations) and 512 x 8 on one XCD 75 (499).  (By canonical rows; the positions
-// differ by the padding.)
-static int64_t efron_loops(const std::vector<std::pair<int64_t, uint32_t>> &ends, int threads, int ipt)
-{
-    const int64_t Rw = (int64_t)kWaveRows * ipt, waves = threads / kWaveRows;
-    int64_t most = 0, wave = -1, tile = -1, simd[4] = {0, 0, 0, 0};
-    uint32_t row[16] = {};   // of the current wave: the most events at each of a thread's rows
-    auto flush = [&](int64_t next) {
-        if (wave < 0) return;
-        int64_t sum = 0;
-        for (int i = 0; i < ipt; ++i) {
-            sum += row[i];
-            row[i] = 0;
+// Efron's tie groups as the kernel meets them.  The lane that holds a group's end takes an iteration per
+// event, a wave the most of its lanes for each of a thread's rows in turn, and the waves of a SIMD
+// (w, w + 4) wait for its FP64 units.  So where groups are large, few rows per thread win: N = 1e5 in one
+// stratum, groups of 50 events, 512 x 1 26 us per coordinate (111 iterations) and 512 x 8 on one XCD 75
+// (499).  (By canonical rows; the positions differ by the padding.)
+class EfronLoops {
+public:
+    explicit EfronLoops(const std::vector<uint32_t> &meta) : meta_(meta) {}
+
+    // Iterations of the longest SIMD in tiles of threads x ipt rows.
+    int64_t longest(int threads, int ipt)
+    {
+        const int shift = ipt == 1 ? 0 : ipt == 2 ? 1 : ipt == 4 ? 2 : ipt == 8 ? 3 : 4;
+        std::vector<uint32_t> &wave = waves_[shift];
+        if (wave.empty()) {
+            const size_t n = meta_.size(), rows = (size_t)kWaveRows << shift;
+            wave.resize((n + rows - 1) / rows);
+            for (size_t w = 0; w < wave.size(); ++w) {
+                uint32_t most[16] = {};   // events at each of a thread's rows
+                for (size_t r = w * rows; r < std::min(n, (w + 1) * rows); ++r)
+                    most[r & (ipt - 1)] = std::max(most[r & (ipt - 1)], meta_[r] & kCountMask);
+                for (const uint32_t d : most) wave[w] += d;
+            }
         }
-        most = std::max(most, simd[wave % waves % 4] += sum);
-        if (next / waves != tile) std::fill(simd, simd + 4, 0);
-    };
-    for (const auto &g : ends) {
-        const int64_t w = g.first / Rw;
-        if (w != wave) {
-            flush(w);
-            wave = w;
-            tile = w / waves;
-        }
-        row[g.first % ipt] = std::max(row[g.first % ipt], g.second);
+        const size_t per = (size_t)(threads / kWaveRows);
+        int64_t longest = 0;
+        for (size_t w = 0; w < wave.size(); ++w)
+            longest = std::max(longest, (int64_t)wave[w] + (w % per >= 4 ? (int64_t)wave[w - 4] : 0));
+        return longest;
     }
-    flush(-1);
-    return most;
-}
+
+private:
+    const std::vector<uint32_t> &meta_;
+    std::vector<uint32_t> waves_[5];   // iterations of each wave, by rows per thread
+};
 
 // Microseconds of one such iteration (a division, a reciprocal and the sums): 0.11 where one group is all
 // there is, more with one wave per SIMD (nothing runs while it waits) and with more rows per thread.
@@ -352,34 +354,45 @@ static int choose_layout(const std::vector<uint32_t> &meta, int p, bool latency,
         strata.push_back(e - i);
         i = e;
     }
-    std::vector<std::pair<int64_t, uint32_t>> ends;   // Efron's tie groups
-    if (efron && latency)
-        for (int64_t i = 0; i < n; ++i)
-            if (meta[i] & kCountMask) ends.emplace_back(i, meta[i] & kCountMask);
-    std::vector<size_t> order;
-    for (size_t k = 0; k < std::size(kShapes); ++k)
-        if (latency ? efron || !kShapes[k].efron
-                    : (efron ? kShapes[k].threads == 512 : !kShapes[k].efron && kShapes[k].threads * kShapes[k].ipt >= 512))
-            order.push_back(k);
-    auto rows = [](size_t k) { return kShapes[k].threads * kShapes[k].ipt; };
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return rows(a) < rows(b); });
+    EfronLoops loops(meta);
+    // The shapes that n rows may fit, with the least time each can take; CCD handles go through them from
+    // the least on and stop where none can be better (a layout's length takes a pass over the strata).
+    struct Candidate {
+        int threads, ipt, groups;
+        double least;
+    };
+    std::vector<Candidate> order;
+    for (const auto &sh : kShapes) {
+        if (latency ? sh.efron && !efron : (efron ? sh.threads != 512 : sh.efron || sh.threads * sh.ipt < 512)) continue;
+        Candidate c{sh.threads, sh.ipt, 0, 0.0};
+        if (max_resident_groups(sh.threads, sh.ipt, p, &c.groups, err) != 0) return COX_EDEVICE;
+        const int64_t R = (int64_t)sh.threads * sh.ipt, grid = (n + R - 1) / R;
+        if (grid > c.groups) continue;
+        const bool wave = longest <= (int64_t)kWaveRows * sh.ipt, carries = grid > 1 && longest > R;
+        c.least = latency ? coordinate_us(sh.threads, sh.ipt, (int)grid, 1, wave, carries) : (double)R;
+        if (latency && grid * kXcds <= c.groups)
+            c.least = std::min(c.least, coordinate_us(sh.threads, sh.ipt, (int)grid, kXcds, wave, carries));
+        order.push_back(c);
+    }
+    std::sort(order.begin(), order.end(), [](const Candidate &a, const Candidate &b) { return a.least < b.least; });
     int kind = 0;             // of the best shape: 1 wave-aligned, 2 tile-aligned, 3 as they are
     double best = INFINITY;
-    for (const size_t which : order) {
-        const auto &sh = kShapes[which];
-        int groups = 0;
-        if (max_resident_groups(sh.threads, sh.ipt, p, &groups, err) != 0) return COX_EDEVICE;
-        if (groups < 1) continue;
+    for (const Candidate &sh : order) {
+        if (latency ? sh.least >= best : kind != 0) break;
         const int64_t R = (int64_t)sh.threads * sh.ipt, Rw = (int64_t)kWaveRows * sh.ipt;
-        const int64_t lens[] = {longest <= Rw ? aligned_length(strata, Rw) : INT64_MAX, aligned_length(strata, R), n};
         for (int k = 0; k < 3; ++k) {
-            if (lens[k] == INT64_MAX || (lens[k] + R - 1) / R > groups) continue;
-            const int grid = (int)((lens[k] + R - 1) / R);
-            const double ties = ends.empty() ? 0.0 : efron_us(sh.threads, sh.ipt) * (double)efron_loops(ends, sh.threads, sh.ipt);
+            if (k == 0 && longest > Rw) continue;
+            const int64_t len = k == 0 ? aligned_length(strata, Rw) : (k == 1 ? aligned_length(strata, R) : n);
+            if ((len + R - 1) / R > sh.groups) continue;
+            const int grid = (int)((len + R - 1) / R);
+            double ties = -1.0;
             for (int spread = 1; spread <= kXcds; spread *= kXcds) {
-                if (spread > 1 && (!latency || (int64_t)grid * spread > groups || grid < 2)) continue;
-                const double us =
-                    ties + coordinate_us(sh.threads, sh.ipt, grid, spread, k == 0, grid > 1 && (k == 2 || longest > R));
+                if (spread > 1 && (!latency || (int64_t)grid * spread > sh.groups || grid < 2)) continue;
+                double us = coordinate_us(sh.threads, sh.ipt, grid, spread, k == 0, grid > 1 && (k == 2 || longest > R));
+                if (us >= best) continue;
+                if (ties < 0.0)
+                    ties = efron && latency ? efron_us(sh.threads, sh.ipt) * (double)loops.longest(sh.threads, sh.ipt) : 0.0;
+                us += ties;
                 if (us >= best) continue;
                 best = us;
                 kind = k + 1;
@@ -392,7 +405,6 @@ static int choose_layout(const std::vector<uint32_t> &meta, int p, bool latency,
             }
             break;
         }
-        if (!latency && kind) break;
     }
     if (!kind) {
         err = "n exceeds the register-resident capacity of the persistent kernel (CUs x 512 x 16 rows)";
