@@ -23,7 +23,7 @@ def _data(n, K, per_unit, seed):
     return X, time, (rng.random(n) < 0.5).astype(np.uint8), rng.integers(0, K, n).astype(np.int32)
 
 
-@pytest.mark.parametrize("n", [700, 5_000, 40_000, 120_000, 200_000, 400_000, 600_000])
+@pytest.mark.parametrize("n", [700, 5_000, 40_000, 120_000, 200_000, 400_000, 600_000, 1_200_000])
 @pytest.mark.parametrize("rows", [20, 400, 10_000, 10**9])
 @pytest.mark.parametrize("per_unit", [5, 1000])
 def test_evaluation(n, rows, per_unit):
