@@ -20,6 +20,7 @@ struct NewtonState {
     int32_t *gidx = nullptr;       // [ld]
     coxmi::EvalSeg *seg = nullptr; // [nseg] runs of whole strata (0: some stratum is too long, or Efron)
     int nseg = 0, seg_rows = 0;
+    bool seg_xbar = false, seg_score = false;   // evaluations with xbar, and without, go by segments
     double *rows = nullptr;        // 9 x [ld]: eta, u, s0', h', R, alpha, b, zq, m
     double *blockbuf = nullptr;    // [max_blocks]
     uint8_t *tile_carry = nullptr; // [ntiles]

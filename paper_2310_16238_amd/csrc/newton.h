@@ -24,8 +24,14 @@ struct EvalSeg {
 };
 // True when segments can serve p columns, strata of up to `longest` rows, X of ld and Z of ldz rows.
 bool segments_fit(int p, int64_t longest, int64_t ld, int64_t ldz);
-// Most rows of a segment for n rows and p columns (at least `longest`).
+// Most rows of a segment for n rows and p columns (at least `longest`); segments that run at a time;
+// whether segments of twice the rows are an option.
 int segment_rows(int64_t n, int p, int64_t longest);
+int seg_round();
+bool segment_may_grow(int rows, int p);
+// True when nseg segments of `rows` rows are the faster evaluation of n rows in strata of up to `longest`,
+// tiles otherwise (xbar: with xbar and Z, in FP64 or BF16).
+bool segments_pay(int64_t n, int p, int64_t longest, int rows, int nseg, bool xbar, bool f64);
 // Partial records per column that nseg segments write to colpart.
 int seg_part_slots(int p, int nseg);
 

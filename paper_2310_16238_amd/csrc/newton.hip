@@ -28,6 +28,8 @@
 #include <hip/hip_bf16.h>
 #include <math.h>
 
+#include <cmath>
+
 #include <type_traits>
 
 #include "internal.h"
@@ -1201,6 +1203,40 @@ int segment_rows(int64_t n, int p, int64_t longest)
     while (R > kWave && (int64_t)R * kSegGrid > 2 * n) R /= 2;
     while (R < longest) R *= 2;
     return R;
+}
+
+int seg_round() { return kSegGrid; }
+bool segment_may_grow(int rows, int p) { return 2 * rows <= kSegRows && (int64_t)2 * rows * p <= 66560; }
+
+// The segments run kSegGrid at a time, one workgroup each, and a workgroup's time is the walk down the rows
+// of its longest part (a stratum is never cut): where few strata fill a segment most of its waves
+// stand idle, and tiles, which cut anywhere, win from a few columns on (N = 5e5, P = 20, strata of 350
+// rows, score 116 us against 108, with xbar 213 against 126).  Microseconds of both, fitted to
+// N = 2e3 ... 2e6, P = 5 ... 500, strata of 2 to 500 rows (within 13% and 9%); against the faster of the
+// two on those the rule loses 3% on average.  Tiles grow with N, and beyond 2^20 rows (8192 to a tile) they
+// lose to all segments but, with xbar, those of one long stratum each (N = 2e6, P = 20: strata of 20 rows
+// 780 us against 355, of 256 rows 790 against 480, of 350 rows 700 against 750).
+// FP64 Z is [p][ldz]: 64-byte runs per column, which the segments' waves write at once, so that beyond
+// half a gigabyte of X (or 200 MB, with more than one segment per workgroup) the tiles' longer runs win
+// (N = 1e6, P = 200: 1.02 ms against 1.40; N = 5e5, P = 64: 0.20 against 0.23).
+bool segments_pay(int64_t n, int p, int64_t longest, int rows, int nseg, bool xbar, bool f64)
+{
+    const bool one_round = nseg <= kSegGrid;
+    if (xbar && f64 && (double)n * p > (n > kSegGrid * (kSegRows / 2) && n <= 1 << 20 ? 2.4e7 : 6.4e7)) return false;
+    if (n > 1 << 20) return !xbar || longest <= 300;
+    const int groups = seg_groups(p), parts = seg_parts(p);
+    const int strata = longest < rows ? rows / (int)longest : 1;   // of a segment
+    const double part = (double)longest * ((strata + parts - 1) / parts) * ((groups * parts + kSegWaves - 1) / kSegWaves);
+    const double mb = 8e-6 * (double)n * p, rounds = one_round ? 1.0 : std::ceil((double)nseg / kSegGrid);
+    const double walk = rounds * (xbar ? (f64 ? 12.0 : 14.0) + 0.139 * part : 7.8 + 0.067 * part);
+    const double bytes = mb * (xbar ? (f64 ? 0.78 : 0.50) : 0.36);
+    // bound by reading X (and writing BF16 Z in its blocks), segments are the faster: BF16 fits of N = 1e6
+    // in strata of 20 rows, P = 200: 10.35 ms against 11.38, P = 1000: 77.2 against 79.5
+    if (!(xbar && f64) && !one_round && walk <= 0.6 * bytes) return true;
+    const double segments = (xbar ? 17.0 : 16.5) + std::sqrt(walk * walk + bytes * bytes);
+    const double tiles = xbar ? 49.0 + (f64 ? 0.50 : 0.43) * (mb + 1.4e-4 * (double)n) + 0.24 * p
+                              : 47.0 + 0.33 * (mb + 1.6e-4 * (double)n) + 0.23 * p;
+    return segments <= (one_round ? 1.15 : (xbar && f64 ? 0.95 : 1.0)) * tiles;
 }
 
 int seg_part_slots(int p, int nseg) { return (nseg < kSegGrid ? nseg : kSegGrid) * seg_parts(p); }

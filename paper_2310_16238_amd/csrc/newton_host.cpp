@@ -115,15 +115,30 @@ int newton_setup(cox_handle *h)
         }
         if (segments_fit(p, longest, ld, s.ldz)) {
             s.seg_rows = segment_rows(n, p, longest);
-            int32_t g = 0;
-            for (int64_t i = 0; i < n;) {
-                int64_t e = i + 1;
-                while (e < n && !(h->meta[e] & kHeadBit)) ++e;
-                const int32_t row0 = (int32_t)h->pos[i], m = (int32_t)(e - i);
-                if (segs.empty() || row0 + m - segs.back().row0 > s.seg_rows) segs.push_back(EvalSeg{row0, 0, g});
-                segs.back().n = row0 + m - segs.back().row0;
-                for (; i < e; ++i) g += (h->meta[i] & kCountMask) ? 1 : 0;
+            auto cut = [&]() {
+                segs.clear();
+                int32_t g = 0;
+                for (int64_t i = 0; i < n;) {
+                    int64_t e = i + 1;
+                    while (e < n && !(h->meta[e] & kHeadBit)) ++e;
+                    const int32_t row0 = (int32_t)h->pos[i], m = (int32_t)(e - i);
+                    if (segs.empty() || row0 + m - segs.back().row0 > s.seg_rows) segs.push_back(EvalSeg{row0, 0, g});
+                    segs.back().n = row0 + m - segs.back().row0;
+                    for (; i < e; ++i) g += (h->meta[i] & kCountMask) ? 1 : 0;
+                }
+            };
+            cut();
+            // not a second round of workgroups for the few segments beyond one (N = 1e5 in strata of 90
+            // rows: 256 rows hold two of them, 556 segments, 95 us at P = 64; 512 hold five: 63)
+            while ((int)segs.size() > seg_round() && (int)segs.size() <= 2 * seg_round() &&
+                   segment_may_grow(s.seg_rows, p)) {
+                s.seg_rows *= 2;
+                cut();
             }
+            const bool f64 = !lowp(h->opt.x_precision);
+            s.seg_xbar = segments_pay(n, p, longest, s.seg_rows, (int)segs.size(), true, f64);
+            s.seg_score = segments_pay(n, p, longest, s.seg_rows, (int)segs.size(), false, f64);
+            if (!s.seg_xbar && !s.seg_score) segs.clear();
         }
     }
     s.nseg = (int)segs.size();
@@ -302,10 +317,7 @@ int newton_eval_launch(cox_handle *h, const double *beta, bool want_xbar, bool w
     A.zscale = lowp(h->opt.x_precision) ? s.zscale : nullptr;
     A.want_xbar = want_xbar;
     A.seg = s.seg;
-    // FP64 Z keeps [p][ldz], whose 64-byte runs per column the segments' waves write at once: beyond
-    // half a gigabyte of X the tiles' longer runs win (N = 1e6, P = 200: 1.02 ms against 1.40; P = 50:
-    // 0.37 against 0.35; without Z, or in BF16, the segments are faster throughout)
-    A.nseg = want_xbar && !lowp(h->opt.x_precision) && (double)h->n * p > 6.4e7 ? 0 : s.nseg;
+    A.nseg = (want_xbar ? s.seg_xbar : s.seg_score) ? s.nseg : 0;
     A.seg_rows = s.seg_rows;
     A.want_rows = want_rows;
     A.scan_scratch = s.scan_scratch;
@@ -378,7 +390,7 @@ int newton_info(cox_handle *h)
             rc = syrk_bf16(static_cast<const uint16_t *>(s.xlp), ld, p, false, s.xscale, b, ld, kSplitsXBF16, s.syrk_part,
                            1.0, 0, s.info, h->stream);
         if (rc == 0 && s.n_zrows > 0)
-            rc = syrk_bf16(static_cast<const uint16_t *>(s.z), s.ldz, p, s.nseg > 0, s.zscale, nullptr, s.n_zrows, kSplitsZBF16,
+            rc = syrk_bf16(static_cast<const uint16_t *>(s.z), s.ldz, p, s.nseg > 0 && s.seg_xbar, s.zscale, nullptr, s.n_zrows, kSplitsZBF16,
                            s.syrk_part, -1.0, 1, s.info, h->stream);
     } else {
         rc = syrk_f64(h->d_x, ld, p, b, ld, kSplitsXF64, s.syrk_part, 1.0, 0, s.info, h->stream);
