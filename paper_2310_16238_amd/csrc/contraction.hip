@@ -1106,7 +1106,11 @@ __global__ __launch_bounds__(64 * kWideWaves, 2) void syrk_bf16_wide_kernel(cons
 
 constexpr float kFp8Max = 224.0f;   // below the e4m3 maximum of either encoding
 constexpr int kF8KC = 64, kF8Stride = 80;   // bytes per LDS row (64 + 16 pad)
-constexpr int kF8Rows = 256;                   // most staged rows of the one-pass kernel (p rounded up to 32)
+// Most staged rows of the one-pass kernel (p rounded up to 32).  Up to 320 its two groups of tile pairs convert
+// 640 rows per chunk, three blocks of 256 x 256 convert 1024 (N = 4e5, P = 257: 181 us against 218 with
+// the product of Z, P = 320: 193 against 224); from a third group on the blocks win (P = 352: 292
+// against 237).
+constexpr int kF8Rows = 320;
 typedef int i32x8v __attribute__((ext_vector_type(8)));
 
 // The e4m3 copy is stored in blocks of kF8KC rows of X: block k holds, for each
@@ -1272,7 +1276,7 @@ __global__ __launch_bounds__(64 * NWV, NWV / 2) void syrk_fp8_lds_kernel(const u
     }
 }
 
-// More than 8 row tiles in FP8: blocks of 8 x 8 tile pairs as in syrk_bf16_wide_kernel.  Per
+// More than 10 row tiles in FP8: blocks of 8 x 8 tile pairs as in syrk_bf16_wide_kernel.  Per
 // 128-row chunk (two of the copy's 64-row blocks) the rows of block I, and off the diagonal
 // those of block J, are decoded, weighted and re-encoded into LDS -- both operands are the same
 // matrix, so a diagonal block stages 256 rows only.  What bounds it is that conversion
@@ -1587,6 +1591,19 @@ int syrk_bf16(const uint16_t *u, int64_t ldu, int p, bool blocked, const float *
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+namespace {
+
+int compute_units()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
+}  // namespace
+
 size_t fp8_copy_bytes(int64_t ld, int p)
 {
     return (size_t)ld * (size_t)((p + kMT - 1) / kMT * kMT);
@@ -1616,6 +1633,12 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
         const int nblocks = nb * (nb + 1) / 2;
         int bsplits = splits;
         if (bsplits * (int64_t)nblocks > 16384) bsplits = 16384 / nblocks > 1 ? 16384 / nblocks : 1;
+        // A range's partials are written and read whatever its length: at least 8 chunks to a range, but
+        // a workgroup for every compute unit (N = 2e4, P = 800: 437 us with 256 ranges of one chunk
+        // and the product of Z, 274 with 24 of seven; the one-pass kernel 333)
+        const int per_cu = compute_units() / nblocks, by_length = (int)(K64 / (8 * kF8WideKC));
+        const int most = by_length > per_cu ? by_length : per_cu;
+        if (most < bsplits) bsplits = most >= 8 ? most / 8 * 8 : (most > 1 ? most : 1);
         int64_t kchunk = (K64 + bsplits - 1) / bsplits;
         kchunk = (kchunk + kF8WideKC - 1) / kF8WideKC * kF8WideKC;
         const size_t lds = (size_t)4 * kWideRows * kF8WideStride;
@@ -1628,14 +1651,7 @@ int syrk_fp8(const uint8_t *u, int64_t ldu, int p, const float *scale, const dou
         return hipGetLastError() == hipSuccess ? 0 : -3;
     }
     // two workgroups per compute unit are resident: size the grid to whole rounds of them
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-    }
-    int fit = (4 * cus) / ngroups;
+    int fit = (4 * compute_units()) / ngroups;
     if (fit >= 8) fit = fit / 8 * 8;   // whole groups of 8 K ranges: one XCD runs all groups of a range
     if (fit >= 1 && fit < splits) splits = fit;
     int64_t kchunk = (K64 + splits - 1) / splits;

@@ -9,7 +9,7 @@
 
 namespace coxmi {
 
-// Columns of the FP8 contraction (up to 256 every workgroup stages all p rows, beyond that
+// Columns of the FP8 contraction (up to 320 every workgroup stages all p rows, beyond that
 // blocks of tile pairs stage only their own rows): the Newton path's limit.
 constexpr int64_t kMaxFp8P = 4096;
 
