@@ -410,7 +410,7 @@ __device__ __forceinline__ double ccd_step(double beta, double g1, double g2, do
 // arrival times.  Every lane of the wave receives the total.  Returns false
 // (uniformly) once a wait has timed out or another workgroup aborted.  Packets
 // first .. first + NP - 1 of each record are polled.
-template <int NP, int PER>
+template <int NP, int PER, bool SHORT>
 __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uint32_t epoch, SyncCtl *ctl,
                                              u32x4 (&r)[PER][NP], int first = 0)
 {
@@ -443,7 +443,7 @@ __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uin
             }
         }
         if (all) break;
-        if (!wb.keep_waiting(ctl)) {
+        if (!wb.keep_waiting<SHORT>(ctl)) {
             ok = false;
             break;
         }
@@ -451,7 +451,7 @@ __device__ __forceinline__ bool poll_records(const PacketArray &part, int G, uin
     return __builtin_amdgcn_ballot_w64(!ok) == 0;
 }
 
-template <int PER>
+template <int PER, bool SHORT>
 __device__ __forceinline__ bool gather_records(const PacketArray &part, int G, uint32_t epoch, bool extra,
                                                SyncCtl *ctl, Partial &total)
 {
@@ -459,7 +459,7 @@ __device__ __forceinline__ bool gather_records(const PacketArray &part, int G, u
     Partial x = partial_identity();
     {
         u32x4 r[PER][2];
-        if (!poll_records<2, PER>(part, G, epoch, ctl, r)) return false;
+        if (!poll_records<2, PER, SHORT>(part, G, epoch, ctl, r)) return false;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             if (lane + kWave * k < G) {
@@ -474,7 +474,7 @@ __device__ __forceinline__ bool gather_records(const PacketArray &part, int G, u
         // the objective and the exact second moment (written with the two above): a second,
         // short poll on the first coordinate of a sweep and in evaluations only
         u32x4 r[PER][2];
-        if (!poll_records<2, PER>(part, G, epoch, ctl, r, 2)) return false;
+        if (!poll_records<2, PER, SHORT>(part, G, epoch, ctl, r, 2)) return false;
         double obj = 0.0, m2 = 0.0;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
@@ -498,11 +498,13 @@ __device__ __forceinline__ bool gather_records(const PacketArray &part, int G, u
     return true;
 }
 
+// SHORT: how a wait for four records per lane is laid out (WaitBudget::keep_waiting).
+template <bool SHORT>
 __device__ __forceinline__ bool gather_wave(const PacketArray &part, int G, uint32_t epoch, bool extra, SyncCtl *ctl,
                                             Partial &total)
 {
-    if (G <= kWave) return gather_records<1>(part, G, epoch, extra, ctl, total);
-    return gather_records<kMaxGroups / kWave>(part, G, epoch, extra, ctl, total);
+    if (G <= kWave) return gather_records<1, true>(part, G, epoch, extra, ctl, total);
+    return gather_records<kMaxGroups / kWave, SHORT>(part, G, epoch, extra, ctl, total);
 }
 
 // Tie-group terms of one row, added to v (Sec. 2.4 derivatives).  S = (S0, S1, S2): the
@@ -839,12 +841,10 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
     bool local = false;
     {
         Partial v = partial_identity();
+        float most = -INFINITY;   // fmaxf passes a NaN by: its row has no weight either (as a key it would be the largest)
 #pragma unroll
-        for (int i = 0; i < IPT; ++i)
-            if (!(meta[i] & kPadBit) && eta[i] == eta[i]) {   // a NaN would be the largest key: its row has no weight
-                const uint32_t key = float_key((float)eta[i]);
-                v.top = key > v.top ? key : v.top;
-            }
+        for (int i = 0; i < IPT; ++i) most = fmaxf(most, (float)eta[i]);   // -INFINITY at padding
+        v.top = float_key(most);
         v = block_reduce_partial<NW, false>(v, s_red);
         if (w == 0) {
             const double xcc = (double)xcc_id();
@@ -852,7 +852,7 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
             v.c2 = xcc * xcc;
             if (lane == NW - 1) publish_partial(part, G, b, v, epoch, false, false);
             Partial tot;
-            const bool ok = gather_wave(part, G, epoch, false, ctl, tot);
+            const bool ok = gather_wave<!WAVE>(part, G, epoch, false, ctl, tot);
             if (lane == 0) {
                 const bool one = ok && (G == 1 || (L.spread > 1 && (double)G * tot.c2 == tot.c1 * tot.c1));
                 s_word = StepWord{one ? 1.0 : 0.0, ok ? tot.top : 0u, ok ? 0u : (uint32_t)kFlagAbort};
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(BLOCK) void ccd_kernel(CcdLaunch L)
                 if (lane == NW - 1) publish_partial(part, G, b, v, epoch, extra, local);
                 Partial tot;
                 StepWord word = {0.0, 0u, kFlagAbort};
-                if (gather_wave(part, G, epoch, extra, ctl, tot)) {
+                if (gather_wave<!WAVE>(part, G, epoch, extra, ctl, tot)) {
                     uint32_t flags = tot.err ? kFlagNumeric : 0u;
                     const double g1 = -qj + tot.c1, g2 = tot.c2, m2 = tot.m2;
                     double step = 0.0;
