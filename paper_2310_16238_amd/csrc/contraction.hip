@@ -855,7 +855,7 @@ __global__ __launch_bounds__(64 * NWV, OCC) void syrk_bf16_lds_kernel(const uint
     const int64_t k1 = k0 + kchunk < K ? k0 + kchunk : K;
     const int rsub = lane & 31, ksub = 8 * (lane >> 5);
     // LDS offsets of this lane's A (weighted) and B (plain) rows for each tile pair, packed
-    // 16 bits each (at most 16 x 32 rows of kLdsStride elements: < 2^16)
+    // 16 bits each (at most 8 x 32 rows of kLdsStride elements: < 2^16)
     uint32_t offs[TPW];
     f32x16 acc[TPW];
 #pragma unroll
@@ -1547,7 +1547,7 @@ int launch_syrk_bf16(const uint16_t *u, int64_t ldu, int p, const double *c, int
 {
     const int nt = (p + kMT - 1) / kMT;
     if (nt <= 8) {
-        // two workgroups per compute unit, 64-row chunks (64.5 KB of LDS each with the weighted copy)
+        // two workgroups per compute unit, 64-row chunks (at most 72 KB of LDS each, 8 tiles with the weighted copy)
         const int ngroups = (npairs32(p) + kPairsPerGroup - 1) / kPairsPerGroup;
         *splits *= 2;
         int64_t kchunk = (K64 + *splits - 1) / *splits;

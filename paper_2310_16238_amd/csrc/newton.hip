@@ -1215,7 +1215,9 @@ bool segment_may_grow(int rows, int p) { return 2 * rows <= kSegRows && (int64_t
 // N = 2e3 ... 2e6, P = 5 ... 500, strata of 2 to 500 rows (within 13% and 9%); against the faster of the
 // two on those the rule loses 3% on average.  Tiles grow with N, and beyond 2^20 rows (8192 to a tile) they
 // lose to all segments but, with xbar, those of one long stratum each (N = 2e6, P = 20: strata of 20 rows
-// 780 us against 355, of 256 rows 790 against 480, of 350 rows 700 against 750).
+// 780 us against 355, of 256 rows 790 against 480, of 350 rows 700 against 750).  The widest sets of many
+// rows come out even: N = 1e7, P = 500 in strata of 20 rows 15.2 to 16.7 ms against 15.4, of 64 rows 12.3
+// against 15.1.
 // FP64 Z is [p][ldz]: 64-byte runs per column, which the segments' waves write at once, so that beyond
 // half a gigabyte of X (or 200 MB, with more than one segment per workgroup) the tiles' longer runs win
 // (N = 1e6, P = 200: 1.02 ms against 1.40; N = 5e5, P = 64: 0.20 against 0.23).
